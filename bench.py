@@ -72,7 +72,7 @@ def measured_traffic(key: dict):
     return None
 
 
-def layer_kernel(specs, l, dtype, folded):
+def layer_kernel(specs, l, dtype, folded, separate):
     """Name of the kernel that computes conv layer l (1-based) in the library."""
     ci, co, k, st, pd = specs[l - 1]
     if not (k == 3 and st == 1 and pd == 1):
@@ -83,7 +83,15 @@ def layer_kernel(specs, l, dtype, folded):
         return f"k_conv_first4_mfma<{co}>" if ci == 4 else f"k_conv_first_f32<{ci}, {co}>"
     if (ci, co) == (40, 80):                                     # weights resident in LDS
         return "k_conv_mfma_res<40, 80>" + (" (layer 1 folded in)" if folded else "")
-    return f"k_conv_mfma_staged<{ci}, {co}>"
+    return f"k_conv_mfma_{'staged' if separate else 'split'}<{ci}, {co}>"
+
+
+def mfma_peak(kernel, dtype):
+    """TFLOP/s of the layer's flops at the matrix cores' nominal rate: float32
+    layers on split operands run six bf16 products for one."""
+    if dtype == "bf16":
+        return PEAK_MFMA_BF16_TFLOPS
+    return PEAK_MFMA_BF16_TFLOPS / 6 if "split" in kernel else PEAK_MFMA_F32_TFLOPS
 
 
 def schedule(frames: int, length: int):
@@ -569,7 +577,7 @@ def main():
         rec = prof["layers"][l]
         if rec["launches"] == 0:
             continue                                            # layer 1 folded into layer 2
-        ent = {"kernel": layer_kernel(specs, l, args.dtype, folded and l == 2), "launches": rec["launches"],
+        ent = {"kernel": layer_kernel(specs, l, args.dtype, folded and l == 2, args.separate_first), "launches": rec["launches"],
                "ms_per_step": rec["ms"] / K, "us_per_launch": 1e3 * rec["ms"] / rec["launches"],
                "dirty_tiles_per_launch": float(dirty[:, l].sum() / rec["launches"])}
         if mfma_layer[l]:
@@ -592,7 +600,7 @@ def main():
                "head": args.head, "layer": l, "folded": bool(folded and l == 2)}
         traffic = measured_traffic(key)
         if mfma_layer[l]:
-            peak = PEAK_MFMA_BF16_TFLOPS if args.dtype == "bf16" else PEAK_MFMA_F32_TFLOPS
+            peak = mfma_peak(ent["kernel"], args.dtype)
             roof = {"bound": "mfma", "kernel": desc, "achieved": ent["tflops"], "peak": peak, "unit": "TFLOP/s",
                     "frac": ent["tflops"] / peak, "traffic": traffic}
         else:

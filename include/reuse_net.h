@@ -104,7 +104,11 @@ typedef struct {
  *     patch around it (the same arithmetic, so the same bits) instead of
  *     reading a layer-1 cache.  Layer-1 masks and work lists are produced
  *     either way; reuse_net_read_activation(layer 1) then computes the layer
- *     on demand. */
+ *     on demand.
+ *     It is the form for training, which reads every layer's cache; with it
+ *     float32 layers 64->128 and 128->128 of steps and full passes run on the
+ *     float32 matrix instructions.  By default these run on the bf16 ones with
+ *     operands split three ways (closer to the exact sums, other roundings). */
 #define RN_OPT_SEPARATE_FIRST 1
 
 typedef struct {                  /* HOST pointers, float32, read during create only */

@@ -755,105 +755,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_conv_mfma_res(ConvArgs a) {
     }
 }
 
-// Weights too large for LDS: a block works on a group of T tiles (8 for 64
-// input channels, 4 for 128: the halos that fit next to the weights) and
-// splits the outputs, not the tiles, across its waves (one per SIMD: the
-// float32 matrix op issues at full rate from a single wave): wave w computes
-// output channels [w COUT / 4, (w + 1) COUT / 4) of all T tiles.  The halos of
-// the T tiles sit in LDS for the whole group (wave w fetches and stores those
-// of tiles w, w + 4, ...);
-// each wave streams only its quarter of the weights through its own pair of
-// LDS buffers, in stages of one kernel position x SC input channels: stage
-// q + 1 goes straight from global memory into the free buffer at the start of
-// stage q (global_load_lds_dwordx4: no registers, no LDS store instructions)
-// and the wave waits for its own loads at the end of the stage.  No wave reads
-// another's weights, so the stages need no block barrier: two per group remain
-// (halos read by all waves before the epilogue reuses the LDS, halos of the
-// next group stored before its first stage).  Per 16-channel block a wave
-// reads T halo fragments and COUT / 64 weight fragments for T x COUT / 64 x 4
-// matrix ops.  Each wave fetches its halos of the next group into registers
-// in the group's last stage (every load issued, out-of-image and absent ones
-// from a fixed valid address and dropped when stored).
-template <int CIN, int COUT>
-struct Staged {
-    static constexpr int SC = (CIN > 64 && CIN % 64 == 0) ? 64 : CIN;   // channels per stage
-    static constexpr int NCH = CIN / SC;             // stages per kernel position
-    static constexpr int NQ = 9 * NCH;               // stages per group
-    static constexpr int SB = SC / 16;               // 16-channel blocks per stage
-    static constexpr int NBW = COUT / 64;            // 16-output blocks per wave
-    static constexpr int CW = 16 * NBW;              // output channels per wave
-    static constexpr int WSW = SC * CW;              // floats per stage and wave
-    static constexpr int WPW = WSW / 256;            // 1 KB wave loads per stage (16 bytes a lane)
-    static constexpr int SR = CW + 4;                // row stride of a tile's output staging (floats)
-    static constexpr int T = CIN <= 64 ? 8 : 4;      // tiles per group
-    static constexpr int TW = T / 4;                 // halos fetched per wave
-    static constexpr size_t lds_bytes = (size_t)(4 * 2 * WSW + T * Mfma<CIN, COUT>::HALO) * sizeof(float);
-    static_assert(COUT % 64 == 0 && SC % 16 == 0 && WSW % 256 == 0, "whole 16-output blocks and 1 KB loads per wave");
-    static_assert(4 * 16 * SR <= Mfma<CIN, COUT>::HALO, "four tiles' output staging fit one halo area");
-};
-
-// Stage q's weights for wave w (its CW output channels) straight from global
-// memory into the wave's LDS buffer dst, [block][n-block][lane][4]
-// (global_load_lds_dwordx4: lane i writes the 16 bytes at the wave-uniform
-// base + 16 i); the WPW loads are in flight on return.
-template <int CIN, int COUT>
-__device__ inline void dma_wstage(const float *wg, int q, float *dst, int w, int lane) {
-    using M = Mfma<CIN, COUT>;
-    using S = Staged<CIN, COUT>;
-    const int kpos = q / S::NCH, ch = q - kpos * S::NCH;
-    const uint32_t l0 = lds_addr(dst);
-#pragma unroll
-    for (int j = 0; j < S::WPW; ++j) {
-        const int b = j / S::NBW, nbw = j - b * S::NBW;
-        lds_dma16(wg + ((size_t)(kpos * M::NBLK + ch * S::SB + b) * M::NB + w * S::NBW + nbw) * 256 + 4 * lane,
-                  l0 + 1024u * j);
-    }
-}
-
-// Halo of tile r into registers with every load issued; bit j of `ok` says
-// whether element j counts (inside the image and `valid`).
-template <int CIN, int COUT, bool VAR>
-__device__ inline void fetch_halo_all(const ConvArgs &a, const TileRef &r, bool valid, floatx4 *regs, uint32_t &ok,
-                                      int lane) {
-    using M = Mfma<CIN, COUT>;
-    static_assert(M::HV <= 32, "halo mask width");
-    const float *base = static_cast<const float *>(a.in);
-    ok = 0;
-#pragma unroll
-    for (int j = 0; j < M::HV; ++j) {
-        const int h = lane + 64 * j;
-        const int pos = h / M::C4, c4 = h - pos * M::C4;
-        const int hy = pos / 6, hx = pos - hy * 6;
-        const int y = r.ty * kTile - 1 + hy, x = r.tx * kTile - 1 + hx;
-        const bool in = valid && h < 36 * M::C4 && y >= 0 && y < a.H && x >= 0 && x < a.W;
-        const float *src;
-        if constexpr (VAR) {
-            src = in ? var_src<float>(a, r.slot, y, x, CIN) + c4 * 4 : base;
-        } else {
-            src = base + (in ? (size_t)r.slot * a.in_stride +
-                                   ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CIN +
-                                   c4 * 4
-                             : 0);
-        }
-        regs[j] = *reinterpret_cast<const floatx4 *>(src);
-        ok |= (uint32_t)in << j;
-    }
-}
-
-template <int CIN, int COUT>
-__device__ inline void store_halo_masked(float *halo, const floatx4 *regs, uint32_t ok, int lane) {
-    using M = Mfma<CIN, COUT>;
-#pragma unroll
-    for (int j = 0; j < M::HV; ++j) {
-        const int h = lane + 64 * j;
-        if (h < 36 * M::C4) {
-            const int pos = h / M::C4, c4 = h - pos * M::C4;
-            *reinterpret_cast<floatx4 *>(halo + chunk_off<CIN, COUT>(pos, c4)) =
-                (ok >> j) & 1 ? regs[j] : floatx4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
-}
-
 // Operands of one 16-channel block: the A fragments of the T tiles and the B
 // fragments of the wave's NBW output blocks.
 template <int T, int NBW>
@@ -862,61 +763,13 @@ struct SplitOps {
     float4 b[NBW];
 };
 
-// Block b of stage (kpos, ch): A from the T halos (channels of block
-// ch * SB + b at kernel position kpos), B from the wave's stage buffer.
-template <int CIN, int COUT, int T, int NBW>
-__device__ inline void split_block(SplitOps<T, NBW> &o, const float *halos, const float *wst, int kpos, int ch, int b,
-                                   int lane) {
-    using M = Mfma<CIN, COUT>;
-    using S = Staged<CIN, COUT>;
-    static_assert(T == S::T && NBW == S::NBW, "operand shape");
-    const int mrow = lane & 15, kq = lane >> 4;
-    const int pix = (mrow & 3) * 6 + (mrow >> 2);   // column-major pixel rows
-    const int ky = kpos / 3, kx = kpos - ky * 3;
-    const int off = chunk_off<CIN, COUT>(pix + ky * 6 + kx, 4 * (ch * S::SB + b) + kq);
-#pragma unroll
-    for (int t = 0; t < T; ++t) o.a[t] = *reinterpret_cast<const float4 *>(halos + t * M::HALO + off);
-#pragma unroll
-    for (int nb = 0; nb < S::NBW; ++nb)
-        o.b[nb] = *reinterpret_cast<const float4 *>(wst + ((b * S::NBW + nb) * 64 + lane) * 4);
-}
-
-template <int T, int NBW>
-__device__ inline void split_mma(floatx4 (&acc)[T][NBW], const SplitOps<T, NBW> &o) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const float av = j == 0 ? o.a[t].x : j == 1 ? o.a[t].y : j == 2 ? o.a[t].z : o.a[t].w;
-#pragma unroll
-            for (int nb = 0; nb < NBW; ++nb) {
-                const float bv = j == 0 ? o.b[nb].x : j == 1 ? o.b[nb].y : j == 2 ? o.b[nb].z : o.b[nb].w;
-                acc[t][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[t][nb], 0, 0, 0);
-            }
-        }
-    }
-}
-
-// acc += the stage's channels (blocks ch * SB .. + SB) at kernel position
-// kpos; `cur` holds block 0's operands on entry, each later block's are read
-// during the previous block's matrix ops.
-template <int CIN, int COUT, int T, int NBW>
-__device__ inline void split_stage(floatx4 (&acc)[T][NBW], const float *halos, const float *wst, int kpos, int ch,
-                                   int lane, SplitOps<T, NBW> &cur) {
-    using S = Staged<CIN, COUT>;
-    static_assert(T == S::T && NBW == S::NBW, "accumulator shape");
-    SplitOps<T, NBW> nxt;
-#pragma unroll
-    for (int b = 0; b < S::SB; ++b) {
-        if (b + 1 < S::SB) split_block<CIN, COUT, T, NBW>(nxt, halos, wst, kpos, ch, b + 1, lane);
-        __builtin_amdgcn_sched_barrier(0);
-        split_mma<T, NBW>(acc, cur);
-        __builtin_amdgcn_sched_barrier(0);
-        cur = nxt;
-    }
-}
-
-// ---- staged layers, chunk-streamed form (launches without variant overlays)
+// ---- weights too large for LDS (64->128, 128->128) on the float32 matrix instructions
+//
+// The form of nets with RN_OPT_SEPARATE_FIRST, the option training uses: the
+// gradient depends on which side of 0 each pre-activation lies, so training
+// keeps the plain float32 sums (the split form of rn_conv_split.hip rounds
+// differently, and in layers that feed another a decision can then fall the
+// other way); a training step spends under 5% of its time here.
 //
 // A block of four waves computes a group of T tiles, each wave COUT / 4 output
 // channels of all of them, walking K one 16-channel chunk at a time and, within
@@ -1284,136 +1137,13 @@ __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // loads issued for a group that does not come
 }
 
-template <int CIN, int COUT, bool DENSE, bool VAR>
+template <int CIN, int COUT, bool DENSE>
 __global__ __launch_bounds__(256) void k_conv_mfma_staged(ConvArgs a) {
-    using M = Mfma<CIN, COUT>;
-    using S = Staged<CIN, COUT>;
-    static_assert(M::TAIL == 0, "staged layers take whole 16-channel blocks");
     extern __shared__ float smem[];
-    if constexpr (!VAR) {
-        // Launches without overlays stream the halos by chunk: groups of 8
-        // tiles when every block has at least 16 of them to do, else of 4.
-        const int cnt = work_count<DENSE>(a);
-        if (cnt >= 16 * 8 * (int)gridDim.x) chunk_path<CIN, COUT, DENSE, 8>(a, cnt, smem);
-        else chunk_path<CIN, COUT, DENSE, 4>(a, cnt, smem);
-    } else {
-    __shared__ float s_bias[COUT];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Groups of 8 tiles when every block has at least 16 of them to do, else of 4.
     const int cnt = work_count<DENSE>(a);
-    constexpr int T = S::T;
-    const XcdRange xr = xcd_range(cnt, T);
-    if (xr.first >= xr.end) return;                       // uniform per block
-    float *halos = smem;                                  // tile t's halo at t * HALO
-    float *wbuf = smem + T * M::HALO + wave * 2 * S::WSW; // this wave's two stage buffers
-    const float *wg = static_cast<const float *>(a.w);
-    for (int j = tid; j < COUT; j += blockDim.x) s_bias[j] = a.bias[j];
-    const int mrow = lane & 15, kq = lane >> 4;
-
-    // Prologue: the wave's halos (tiles wave + 4 h) of group 0; its stage 0 in LDS.
-    dma_wstage<CIN, COUT>(wg, 0, wbuf, wave, lane);
-    floatx4 hreg[S::TW][M::HV];
-    uint32_t hok[S::TW];
-#pragma unroll
-    for (int h = 0; h < S::TW; ++h) {
-        const int t = xr.first + wave + 4 * h;
-        const uint32_t e = t < xr.end ? item_word<DENSE>(a, t) : 0u;
-        fetch_halo_all<CIN, COUT, VAR>(a, item_ref(a, e), t < xr.end, hreg[h], hok[h], lane);
-    }
-#pragma unroll
-    for (int h = 0; h < S::TW; ++h) store_halo_masked<CIN, COUT>(halos + (wave + 4 * h) * M::HALO, hreg[h], hok[h], lane);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_barrier();
-
-    int buf = 0;
-    for (int g = xr.first; g < xr.end; g += xr.stride) {   // uniform per block
-        uint32_t e_nxt[S::TW];                            // the wave's items of the next group
-#pragma unroll
-        for (int h = 0; h < S::TW; ++h) {
-            const int tn = g + xr.stride + wave + 4 * h;
-            e_nxt[h] = tn < xr.end ? item_word<DENSE>(a, tn) : 0u;
-        }
-        uint32_t e_grp[T];                                // the group's items, for the epilogue
-#pragma unroll
-        for (int tt = 0; tt < T; ++tt) e_grp[tt] = g + tt < xr.end ? item_word<DENSE>(a, g + tt) : 0u;
-        floatx4 acc[T][S::NBW];
-#pragma unroll
-        for (int tt = 0; tt < T; ++tt)
-#pragma unroll
-            for (int nb = 0; nb < S::NBW; ++nb) acc[tt][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-        // Three stages per loop iteration where the group has 18: rolled one
-        // stage at a time the compiler permutes the accumulator registers
-        // within an iteration and moves them back at its end.
-        constexpr int QU = S::NQ == 18 ? 3 : 1;
-#pragma unroll QU
-        for (int q = 0; q < S::NQ; ++q) {
-            // The stage's first operands, then stage q + 1 (wrapping into the
-            // next group) straight into the wave's other buffer (its last
-            // reads, of stage q - 1, fed matrix ops that have issued) and,
-            // in the last stage, the wave's halos of the next group into
-            // registers; then the matrix work and the wait for the weight
-            // loads (the halo loads, issued after them, stay in flight: the
-            // waits count in issue order).
-            const int kpos = q / S::NCH, ch = q - kpos * S::NCH;
-            const float *wst = wbuf + buf * S::WSW;
-            SplitOps<T, S::NBW> first;
-            split_block<CIN, COUT, T, S::NBW>(first, halos, wst, kpos, ch, 0, lane);
-            dma_wstage<CIN, COUT>(wg, (q + 1) % S::NQ, wbuf + (buf ^ 1) * S::WSW, wave, lane);
-            const bool last = q == S::NQ - 1;
-            if (last) {
-#pragma unroll
-                for (int h = 0; h < S::TW; ++h) {
-                    const int tn = g + xr.stride + wave + 4 * h;
-                    fetch_halo_all<CIN, COUT, VAR>(a, item_ref(a, e_nxt[h]), tn < xr.end, hreg[h], hok[h], lane);
-                }
-            }
-            split_stage<CIN, COUT, T, S::NBW>(acc, halos, wst, kpos, ch, lane, first);
-            buf ^= 1;
-            if (last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(S::TW * M::HV) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        lds_barrier();                                    // every wave is past its last halo read
-        // Epilogue, tile by tile: bias, ReLU and the zero outside the image on
-        // the bit patterns (a float above zero has a positive int pattern),
-        // staged through LDS rows of the wave's CW channels, then stored 16
-        // bytes a lane.
-#pragma unroll
-        for (int tt = 0; tt < T; ++tt) {
-            const int it = g + tt;
-            if (it >= xr.end) break;                      // uniform
-            const TileRef r = item_ref(a, e_grp[tt]);
-            const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
-            // staging: the wave's own halo areas (tiles wave + 4 h), four tiles each
-            float *stg = halos + (wave + 4 * (tt / 4)) * M::HALO + (tt % 4) * 16 * S::SR;
-#pragma unroll
-            for (int nb = 0; nb < S::NBW; ++nb) {
-                const float bb = s_bias[(wave * S::NBW + nb) * 16 + mrow];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int keep = col_keep & ~((a.H - 1 - (r.ty * kTile + i)) >> 31);
-                    stg[(i * 4 + kq) * S::SR + nb * 16 + mrow] =
-                        __int_as_float(max(__float_as_int(acc[tt][nb][i] + bb), 0) & keep);
-                }
-            }
-            wave_sync();
-            float *dst = VAR ? static_cast<float *>(a.vov_out) + (size_t)it * kTilePx * COUT
-                             : static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride + (size_t)r.tile * kTilePx * COUT;
-            if (!VAR || a.vov_out != nullptr) {
-#pragma unroll
-                for (int j = 0; j < S::CW / 16; ++j) {    // 16 x CW / 4 float4 = 64 x CW / 16
-                    const int o4 = lane + 64 * j;
-                    const int m = (4 * o4) / S::CW, n = 4 * o4 - m * S::CW;
-                    *reinterpret_cast<float4 *>(dst + m * COUT + wave * S::CW + n) =
-                        *reinterpret_cast<const float4 *>(stg + m * S::SR + n);
-                }
-            }
-        }
-        wave_sync();                                      // staging reads done before the halo store
-#pragma unroll
-        for (int h = 0; h < S::TW; ++h) store_halo_masked<CIN, COUT>(halos + (wave + 4 * h) * M::HALO, hreg[h], hok[h], lane);
-        lds_barrier();                                    // the next group's halos visible to every wave
-    }
-    }
+    if (cnt >= 16 * 8 * (int)gridDim.x) chunk_path<CIN, COUT, DENSE, 8>(a, cnt, smem);
+    else chunk_path<CIN, COUT, DENSE, 4>(a, cnt, smem);
 }
 
 // ------------------------------------------------------------------ general layers
@@ -1640,11 +1370,6 @@ __global__ __launch_bounds__(256) void k_conv_gen(ConvArgs a) {
 
 // ------------------------------------------------------------------ dispatch
 
-constexpr size_t kLdsBudget = 160 * 1024 - 1024;   // 160 KiB per CU, less the static arrays
-
-template <int CIN, int COUT>
-constexpr bool use_resident() { return Resident<CIN, COUT, 8>::lds_bytes <= kLdsBudget; }
-
 // Static LDS of the fused variant: bias, layer-1 weights and bias.
 template <int CIN, int COUT>
 constexpr bool fused_fits() {
@@ -1672,19 +1397,19 @@ hipError_t run_resident(const ConvArgs &a, int cus, hipStream_t s) {
 
 template <int CIN, int COUT, bool DENSE, bool VAR>
 hipError_t run_mfma(const ConvArgs &a, int cus, hipStream_t s) {
-    if constexpr (use_resident<CIN, COUT>()) {
-        if (a.fuse_first) return run_resident<CIN, COUT, DENSE, true, VAR>(a, cus, s);
-        return run_resident<CIN, COUT, DENSE, false, VAR>(a, cus, s);
-    } else {
-        if (a.fuse_first || a.n_out > 0) return hipErrorInvalidValue;   // head partials come from their own kernel
-        constexpr size_t lds = VAR ? Staged<CIN, COUT>::lds_bytes : Chunked<CIN, COUT, 8>::lds_bytes;
-        static_assert(lds <= kLdsBudget && Chunked<CIN, COUT, 4>::lds_bytes <= lds, "staged layer exceeds LDS");
-        auto kern = k_conv_mfma_staged<CIN, COUT, DENSE, VAR>;
-        static hipError_t attr = set_lds(kern, lds);
-        if (attr != hipSuccess) return attr;
-        const int grid = persistent_grid(cus, (a.max_tiles + Staged<CIN, COUT>::T - 1) / Staged<CIN, COUT>::T);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, a);
-    }
+    if (a.fuse_first) return run_resident<CIN, COUT, DENSE, true, VAR>(a, cus, s);
+    return run_resident<CIN, COUT, DENSE, false, VAR>(a, cus, s);
+}
+
+template <int CIN, int COUT, bool DENSE>
+hipError_t run_staged(const ConvArgs &a, int cus, hipStream_t s) {
+    if (a.fuse_first || a.n_out > 0) return hipErrorInvalidValue;   // head partials come from their own kernel
+    constexpr size_t lds = std::max(Chunked<CIN, COUT, 8>::lds_bytes, Chunked<CIN, COUT, 4>::lds_bytes);
+    static_assert(lds <= 160 * 1024, "staged layer exceeds LDS");
+    auto kern = k_conv_mfma_staged<CIN, COUT, DENSE>;
+    static hipError_t attr = set_lds(kern, lds);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, (a.max_tiles + 3) / 4)), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1702,7 +1427,9 @@ hipError_t run_first(const ConvArgs &a, int cus, hipStream_t s) {
     return hipGetLastError();
 }
 
-#define RN_MFMA_SHAPES(X) X(40, 80) X(64, 128) X(128, 128)
+// Layers whose weights stay in LDS; larger ones are in rn_conv_split.hip.
+#define RN_MFMA_SHAPES(X) X(40, 80)
+#define RN_STAGED_SHAPES(X) X(64, 128) X(128, 128)
 // General layers: (k, stride, cin, cout); first layers read the input frames.
 #define RN_GEN_FIRST_SHAPES(X) X(8, 4, 4, 32) X(8, 4, 1, 32) X(5, 1, 1, 32) X(7, 2, 1, 32) X(5, 2, 4, 32)
 #define RN_GEN_SHAPES(X) X(4, 2, 32, 64) X(3, 1, 64, 64) X(3, 1, 32, 64) X(3, 2, 32, 64) X(5, 2, 32, 64) X(5, 1, 32, 32)
@@ -1794,12 +1521,12 @@ bool conv_mfma_supported(int cin, int cout, rn_dtype dt) {
 #define X(ci, co) if (cin == ci && cout == co) return true;
     RN_MFMA_SHAPES(X)
 #undef X
-    return false;
+    return conv_split_supported(cin, cout);
 }
 
 bool conv_fused_first_supported(int c1, int c2, rn_dtype dt) {
     if (dt != RN_F32) return false;
-#define X(ci, co) if (c1 == ci && c2 == co) return use_resident<ci, co>() && fused_fits<ci, co>();
+#define X(ci, co) if (c1 == ci && c2 == co) return fused_fits<ci, co>();
     RN_MFMA_SHAPES(X)
 #undef X
     return false;
@@ -1814,7 +1541,7 @@ bool conv_first_supported(int cin, int cout, rn_dtype dt) {
 }
 
 // cus: compute units of the device; the persistent grid is at most one block
-// (resident or staged MFMA kernel) or eight blocks (first layer) per CU.
+// (resident MFMA kernel) or eight blocks (first layer) per CU.
 hipError_t launch_conv_mfma(const ConvArgs &a, rn_dtype dt, int cus, hipStream_t s, bool var) {
     (void)dt;
     const bool dense = a.wl == nullptr;
@@ -1824,6 +1551,16 @@ hipError_t launch_conv_mfma(const ConvArgs &a, rn_dtype dt, int cus, hipStream_t
         return var ? run_mfma<ci, co, false, true>(a, cus, s)                              \
                    : dense ? run_mfma<ci, co, true, false>(a, cus, s) : run_mfma<ci, co, false, false>(a, cus, s);
     RN_MFMA_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s) {
+    const bool dense = a.wl == nullptr;
+#define X(ci, co)                     \
+    if (a.cin == ci && a.cout == co) \
+        return dense ? run_staged<ci, co, true>(a, cus, s) : run_staged<ci, co, false>(a, cus, s);
+    RN_STAGED_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
 }
@@ -1839,14 +1576,6 @@ hipError_t launch_conv_first(const ConvArgs &a, rn_dtype dt, int cus, hipStream_
     RN_FIRST_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
-}
-
-bool conv_mfma_is_staged(int cin, int cout) {
-#define X(ci, co) \
-    if (cin == ci && cout == co) return !use_resident<ci, co>();
-    RN_MFMA_SHAPES(X)
-#undef X
-    return false;
 }
 
 size_t conv_first_packed_elems(int cin, int cout) { return (size_t)cin * 9 * cout; }

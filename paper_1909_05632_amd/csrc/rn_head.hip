@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256) void k_tile_part_bf16(ConvArgs a) {
 
 // ------------------------------------------------------------------ float32 tile partials
 
-// The same product for a float32 last layer on the staged conv kernel, whose
+// The same product for a float32 last layer on the split conv kernel, whose
 // epilogue would otherwise read the tile's whole n_out x 16 C slice of head
 // weights from L2 for every tile:
 //   hpart[tile][o] = sum_k act_tile[k] * hw[P][k][o],  k = pixel * C + channel,

@@ -57,6 +57,10 @@ struct Plan {
     // conv layers 2..L).
     const char *train_why = nullptr;        // NULL: training supported
     size_t o_wt[RN_MAX_CONV] = {0};
+    // Layers on launch_conv_split: the bf16 planes of their weights.
+    bool split[RN_MAX_CONV] = {false};
+    size_t o_ws[RN_MAX_CONV] = {0};
+    bool plain = false;                     // RN_OPT_SEPARATE_FIRST: steps and full passes sum in plain float32
     size_t wt_elems[RN_MAX_CONV] = {0};
     size_t act_stride[RN_MAX_CONV + 1] = {0};   // elements per slot
     size_t total = 0;
@@ -166,6 +170,7 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
     p->K = (size_t)p->ntl[p->L] * kTilePx * p->C[p->L];
     p->fuse_first = !(cfg->options & RN_OPT_SEPARATE_FIRST) && p->L >= 2 && p->C[0] == 1 && p->stack == 1 &&
                     !p->gen[0] && !p->gen[1] && conv_fused_first_supported(p->C[1], p->C[2], p->dt);
+    p->plain = (cfg->options & RN_OPT_SEPARATE_FIRST) != 0;
     // The tile-partial head lives in the epilogue of an MFMA layer (float32) or
     // in its own matrix kernel after the last layer (bf16).
     p->head_mode = (cfg->head_mode == RN_HEAD_TILES && (p->L >= 2 || p->gen[p->L - 1]) &&
@@ -173,7 +178,7 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
                        ? RN_HEAD_TILES
                        : RN_HEAD_FULL;
     p->part_f32 = p->head_mode == RN_HEAD_TILES && !bf && p->L >= 2 && !p->gen[p->L - 1] &&
-                  conv_mfma_is_staged(p->C[p->L - 1], p->C[p->L]) && tile_part_f32_supported(p->C[p->L]);
+                  conv_split_supported(p->C[p->L - 1], p->C[p->L]) && tile_part_f32_supported(p->C[p->L]);
     p->head_sg = head_streams_per_block(p->N);
     size_t part = 0;
     for (int n = 1; n <= p->S; ++n) {
@@ -210,6 +215,8 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
         p->w_bytes[l] = p->w_elems[l] * ((l > 0 && p->dt == RN_BF16) ? 2 : 4);
         p->o_w[l] = take(p->w_bytes[l]);
         p->o_b[l] = take((size_t)p->C[l + 1] * 4);
+        p->split[l] = l > 0 && !p->gen[l] && p->dt == RN_F32 && conv_split_supported(p->C[l], p->C[l + 1]);
+        p->o_ws[l] = take(p->split[l] ? conv_split_bytes(p->C[l], p->C[l + 1]) : 0);
     }
     if (p->dt != RN_F32) p->train_why = "training needs a float32 net";
     else if (p->any_gen) p->train_why = "training needs 3x3 stride-1 pad-1 layers";
@@ -238,7 +245,7 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
     const bool tiles_head = p->head_mode == RN_HEAD_TILES;
     p->o_part = take(tiles_head ? 0 : p->part_elems * 4);
     // Epilogue head weights: float32 last layers whose conv kernel forms the
-    // tile partials (a staged last layer leaves them to k_tile_part_f32, o_hw2).
+    // tile partials (a split last layer leaves them to k_tile_part_f32, o_hw2).
     p->o_hw = take(!tiles_head || p->part_f32 ? 0
                    : p->dt == RN_BF16 ? tile_part_bf16_elems(p->ntl[p->L], p->C[p->L], p->N) * 2
                                       : tile_head_w_elems(p->ntl[p->L], p->C[p->L], p->N) * 4);
@@ -261,7 +268,7 @@ struct VarPlan {
 };
 
 // Layer l's recomputed tiles are read back by layer l + 1 (unless layer 1 is
-// folded into layer 2) or, bf16 or staged float32 last layer, by the
+// folded into layer 2) or, bf16 or split float32 last layer, by the
 // head-partial kernel; another float32 last layer feeds the head from its
 // epilogue and stores nothing.
 VarPlan plan_variants(const Plan &p, int n, int max_tiles) {
@@ -430,6 +437,22 @@ MaskGeom make_geom(reuse_net *net) {
     return g;
 }
 
+// Layers 2..L other than the general ones.
+hipError_t launch_conv_later(const Plan &p, const ConvArgs &cv, int l, int cus, hipStream_t s, bool var) {
+    if (p.dt == RN_BF16) return launch_conv_mfma_bf16(cv, cus, s, var);
+    if (!p.split[l - 1]) return launch_conv_mfma(cv, p.dt, cus, s, var);
+    return p.plain && !var ? launch_conv_staged(cv, cus, s) : launch_conv_split(cv, cus, s, var);
+}
+
+// The split planes of the weights, from their float32 packing.
+hipError_t split_weights(reuse_net *net, hipStream_t s) {
+    const Plan &p = net->p;
+    hipError_t e = hipSuccess;
+    for (int l = 1; l < p.L && e == hipSuccess; ++l)
+        if (p.split[l]) e = launch_pack_split(net->at<float>(p.o_w[l]), p.C[l], p.C[l + 1], net->at<void>(p.o_ws[l]), s);
+    return e;
+}
+
 // Conv layers 1..L (list mode: the work lists; dense mode: every tile), then the head.
 // identity: the batch is slots 0..n-1 in order (ids is then the identity table;
 // kernels that only need a stream's slot skip loading it).
@@ -448,6 +471,7 @@ hipError_t run_layers(reuse_net *net, int n, const int32_t *ids, bool identity, 
         cv.in = l == 1 ? static_cast<const void *>(net->at<float>(p.o_xin)) : net->at<void>(p.o_act[l - 1]);
         cv.out = net->at<void>(p.o_act[l]);
         cv.w = net->at<void>(p.o_w[l - 1]);
+        if (p.split[l - 1]) cv.w_split = net->at<void>(p.o_ws[l - 1]);
         cv.bias = net->at<float>(p.o_b[l - 1]);
         cv.ring_head = net->at<int32_t>(p.o_ring);
         cv.H = p.Hl[l];
@@ -490,12 +514,12 @@ hipError_t run_layers(reuse_net *net, int n, const int32_t *ids, bool identity, 
             }, l);
         else
             e = timed(net, RN_PHASE_CONVN, s, [&] {
-                return bf ? launch_conv_mfma_bf16(cv, net->cus, s) : launch_conv_mfma(cv, p.dt, net->cus, s);
+                return launch_conv_later(p, cv, l, net->cus, s, false);
             }, l);
         if (e != hipSuccess) return e;
     }
     if (tiles_head && (p.dt == RN_BF16 || p.part_f32)) {
-        // bf16, or a float32 last layer on the staged kernel: the tiles of the
+        // bf16, or a float32 last layer on the split kernel: the tiles of the
         // last work list (every tile in dense mode) get their partials from a
         // matrix kernel by position, reading the updated cache.
         last.in = net->at<void>(p.o_act[p.L]);
@@ -679,6 +703,7 @@ rn_status run_variants(reuse_net *net, int32_t base, int32_t n, const void *fram
         cv.cnt = va.cnt + l;
         cv.in = l == 1 ? static_cast<const void *>(net->at<float>(p.o_xin)) : net->at<void>(p.o_act[l - 1]);
         cv.w = net->at<void>(p.o_w[l - 1]);
+        if (p.split[l - 1]) cv.w_split = net->at<void>(p.o_ws[l - 1]);
         cv.bias = net->at<float>(p.o_b[l - 1]);
         cv.H = p.H;
         cv.W = p.W;
@@ -728,7 +753,7 @@ rn_status run_variants(reuse_net *net, int32_t base, int32_t n, const void *fram
             }, l);
         else
             e = timed(net, RN_PHASE_CONVN, s, [&] {
-                return bf ? launch_conv_mfma_bf16(cv, net->cus, s, true) : launch_conv_mfma(cv, p.dt, net->cus, s, true);
+                return launch_conv_later(p, cv, l, net->cus, s, true);
             }, l);
         if (e != hipSuccess) return net->fail(RN_EHIP, std::string("conv kernels: ") + hipGetErrorString(e));
     }
@@ -882,6 +907,7 @@ hipError_t upload_weights(reuse_net *net, const rn_weights *w, hipStream_t s) {
         up(p.o_hw2, hw2.data(), hw2.size() * 4);
     }
     up(p.o_bd, w->dense_b, (size_t)p.N * 4);
+    if (e == hipSuccess) e = split_weights(net, s);
     // pageable host buffers: the copies are done with the vectors before they go
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     return e;
@@ -993,6 +1019,7 @@ rn_status write_packed(reuse_net *net, const float *src, float lr, bool assign, 
         upd(p.o_hw, tile_head_w_elems(p.ntl[p.L], p.C[p.L], p.N), SGD_TILE_HEAD, src + gl.dw, 0, 0);
     if (p.part_f32) upd(p.o_hw2, tile_part_f32_elems(p.ntl[p.L], p.C[p.L], p.N), SGD_TILE_PART, src + gl.dw, 0, 0);
     upd(p.o_bd, p.N, SGD_PLAIN, src + gl.db, 0, 0);
+    if (e == hipSuccess) e = timed(net, RN_PHASE_SGD, s, [&] { return split_weights(net, s); });
     if (e == hipSuccess) e = timed(net, RN_PHASE_SGD, s, [&] { return launch_unprime(net->at<int32_t>(p.o_primed), p.S, s); });
     if (e != hipSuccess) return net->fail(RN_EHIP, std::string(what) + ": " + hipGetErrorString(e));
     net->last_stream = s;

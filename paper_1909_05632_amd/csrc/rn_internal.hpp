@@ -102,6 +102,7 @@ struct ConvArgs {
     const void *in;               // previous layer cache (layer 1: float32 input ring)
     void *out;                    // this layer's cache [S][TH][TW][16][cout]
     const void *w;                // packed weights
+    const void *w_split;          // their three bf16 planes (layers of launch_conv_split)
     const float *bias;            // [cout]
     const int32_t *ring_head;     // stack=4 only
     int H, W, TH, TW;             // this layer's output grid and its tile grid
@@ -210,6 +211,15 @@ hipError_t launch_var_lists(const VarMaskArgs &a, hipStream_t s);
 hipError_t launch_conv_first(const ConvArgs &a, rn_dtype dt, int grid, hipStream_t s, bool var = false);
 hipError_t launch_conv_mfma(const ConvArgs &a, rn_dtype dt, int grid, hipStream_t s, bool var = false);
 bool conv_mfma_supported(int cin, int cout, rn_dtype dt);
+// Float32 layers on the bf16 matrix cores with split operands: the split
+// weights are packed on the device from the float32 packing (pack_conv_mfma).
+bool conv_split_supported(int cin, int cout);
+size_t conv_split_bytes(int cin, int cout);
+hipError_t launch_pack_split(const float *w, int cin, int cout, void *dst, hipStream_t s);
+hipError_t launch_conv_split(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
+// The same layers on the float32 matrix instructions (nets with
+// RN_OPT_SEPARATE_FIRST), not for variants.
+hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s);
 bool conv_first_supported(int cin, int cout, rn_dtype dt);
 // General layers (any k <= 8, stride 1, 2 or 4, pad <= (k - 1) / 2; float32):
 // first = the layer reads the input frames.
@@ -231,10 +241,9 @@ bool tile_part_bf16_supported(int C);
 size_t tile_part_bf16_elems(int ntiles, int C, int n_out);
 void pack_tile_part_bf16(const float *dense_w, int n_out, int C, int H, int W, int TH, int TW, uint16_t *dst);
 hipError_t launch_tile_part_bf16(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
-// float32 tile partials by position for a last layer on the staged conv
-// kernel (its epilogue then computes none): hw the packed weights of
+// float32 tile partials by position for a last layer on the split conv
+// kernel (its epilogue computes none): hw the packed weights of
 // pack_tile_part_f32, `in` the last cache, cout its channels.
-bool conv_mfma_is_staged(int cin, int cout);
 bool tile_part_f32_supported(int C);
 size_t tile_part_f32_elems(int ntiles, int C, int n_out);
 void pack_tile_part_f32(const float *dense_w, int n_out, int C, int H, int W, int TH, int TW, float *dst);

@@ -1,0 +1,86 @@
+"""Float32 layers on the bf16 matrix cores with split operands: group sizes and
+their remainders against the oracle and each other, and values the split cannot
+carry (infinities, magnitudes that round up to infinity in bf16)."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import frames as synth
+from gpu_util import ATOL_F32, make_net, oracle_net
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = pytest.importorskip("torch")
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+# 88 tiles a stream (ragged bottom row): groups of 4 (88 and 440 tiles), of 8
+# (1144) and of 16 (2112), whose last groups are part empty on every XCD's share.
+@pytest.mark.parametrize("n", [1, 5, 13, 24])
+def test_group_sizes(torch, n):
+    wl = synth.Workload(cid=201, streams=n, frames=1, h=42, w=32, convs=(64, 128, 128), n_out=18,
+                        n_sprites=3, smin=3, smax=6, vmin=1, vmax=3)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]
+    dev = torch.from_numpy(x).cuda()
+    a, b, one = make_net(wl, n, weights), make_net(wl, n, weights), make_net(wl, 1, weights)
+    full = a.full(dev).cpu().numpy()
+    step = b.step(dev).cpu().numpy()                     # all dirty: the same tiles by list
+    assert np.array_equal(full.view(np.uint32), step.view(np.uint32))
+    for i in sorted({0, n // 2, n - 1}):
+        alone = one.full(dev[i:i + 1].contiguous()).cpu().numpy()
+        assert np.array_equal(full[i:i + 1].view(np.uint32), alone.view(np.uint32)), i
+        ref, acts = oracle.forward(oracle_net(wl), *weights, x[i:i + 1], want_acts=True)
+        assert np.abs(full[i] - ref[0]).max() <= ATOL_F32
+        for l in (2, 3):
+            assert np.array_equal(a.activation(i, l), one.activation(0, l)), (i, l)
+            assert np.abs(a.activation(i, l) - acts[l - 1][0]).max() <= ATOL_F32, (i, l)
+    for net in (a, b, one):
+        net.close()
+
+
+def _weights(wl, rng, scale):
+    """Layer 1 copies the frame into channel 0 (others: -frame and plain random taps); later layers random."""
+    w = list(synth.net_weights(wl, bias_std=0.05))
+    cw = [np.array(v) for v in w[0]]
+    cw[0][0] = cw[0][1] = 0.0
+    cw[0][0, 0, 1, 1], cw[0][1, 0, 1, 1] = 1.0, -1.0
+    for l in (1, 2):
+        cw[l] = (rng.normal(0.0, scale, cw[l].shape)).astype(np.float32)
+    return (cw, *w[1:])
+
+
+@pytest.mark.parametrize("value", [3.4e38, -3.4e38, np.inf, -np.inf])
+def test_values_beyond_the_split(torch, value):
+    # One pixel of the frame holds `value`.  Plain float32 arithmetic (torch on
+    # the CPU, sums in another order) gives the expected result wherever it is
+    # not NaN; where it is, the GPU's ReLU may give NaN or 0 (the sign of a NaN).
+    # 3.4e38 is finite in float32 and infinite in bf16; the layer weights keep
+    # its products and their sums finite.  Tolerance: 1152 float32 roundings.
+    import torch.nn.functional as F
+    wl = synth.Workload(cid=202, streams=2, frames=1, h=20, w=24, convs=(64, 128, 128), n_out=18)
+    weights = _weights(wl, np.random.default_rng(5), 1e-4)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
+    x[0, 0, 9, 10] = value
+    net = make_net(wl, 2, weights)
+    net.full(torch.from_numpy(x).cuda())
+    cur = torch.from_numpy(x)
+    for l in range(1, 4):
+        z = F.conv2d(cur, torch.from_numpy(weights[0][l - 1]), torch.from_numpy(weights[1][l - 1]), padding=1)
+        size = F.conv2d(cur.abs(), torch.from_numpy(np.abs(weights[0][l - 1])), torch.from_numpy(np.abs(weights[1][l - 1])),
+                        padding=1).numpy()               # sum of the terms' magnitudes
+        want = torch.clamp_min(z, 0.0).numpy()
+        got = np.stack([net.activation(i, l) for i in range(2)])
+        known = ~np.isnan(z.numpy())
+        fin = known & np.isfinite(want) & np.isfinite(size)
+        assert np.array_equal(np.isinf(got[known]), np.isinf(want[known])), l
+        assert np.all((got[~known] == 0.0) | ~np.isfinite(got[~known])), l
+        with np.errstate(over="ignore"):
+            assert np.all(np.abs(got[fin] - want[fin]) <= 1152 * 2.0 ** -24 * size[fin] + 1e-30), l
+        cur = torch.from_numpy(got)                       # the next layer's input as the GPU has it
+    net.close()

@@ -313,7 +313,10 @@ __global__ __launch_bounds__(256) void k_tile_part_bf16(ConvArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cnt = work_count<DENSE>(a);
-    const XcdRange xr = xcd_range(cnt, 64);
+    // At most 64 items a block, as many as give every block some: each position
+    // among them is a pass that waits for memory (see k_tile_part_f32).
+    const int G = min(64, max(1, (cnt + (int)gridDim.x - 1) / (int)gridDim.x));
+    const XcdRange xr = xcd_range(cnt, G);
     const uint16_t *act = static_cast<const uint16_t *>(a.in);
     const uint16_t *hw = reinterpret_cast<const uint16_t *>(a.hw);
     const int ntiles = a.TH * a.TW;
@@ -331,13 +334,14 @@ __global__ __launch_bounds__(256) void k_tile_part_bf16(ConvArgs a) {
     }
     for (int g = xr.first; g < xr.end; g += xr.stride) {   // uniform per block
         // This lane's A rows: row `row` of each group (items g + 16 rg + row).
+        const int end = min(g + G, xr.end);
         uint32_t e[4];
         int pos[4];
         const uint16_t *arow[4];
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
             const int it = g + 16 * rg + row;
-            const bool valid = it < xr.end;
+            const bool valid = it < end;
             e[rg] = valid ? item_word<DENSE>(a, it) : 0u;
             const TileRef r = item_ref(a, e[rg]);
             pos[rg] = valid ? r.tile : -1;
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(256) void k_tile_part_bf16(ConvArgs a) {
         }
         if (tid < 64) {
             const int t2 = g + tid;
-            s_pos[tid] = t2 < xr.end ? item_ref(a, item_word<DENSE>(a, t2)).tile : -1;
+            s_pos[tid] = t2 < end ? item_ref(a, item_word<DENSE>(a, t2)).tile : -1;
         }
         lds_barrier();
         // Lane q of every wave holds row q's position; the passes take the
@@ -469,18 +473,28 @@ __global__ __launch_bounds__(256) void k_tile_part_bf16(ConvArgs a) {
 // wave order as in k_tile_part_bf16, so list and dense passes agree bit for
 // bit.  VAR: variant work items, as in k_tile_part_bf16 (activations from the
 // item's overlay row, partials to the same row of the variant partials).
+//
+// A block takes a group of at most 64 items, as many as give every block of
+// the grid one: with few dirty tiles a group's items lie at as many positions,
+// and each position is a pass over its weights that waits for memory, one
+// after the other in the block (64 items whatever the count: 271 us for the
+// 165 items of one 210x160 stream, 718 us for 689 of four).  A wave loads the
+// weights of KB K blocks at once (128 registers), then the activations of each
+// row group that holds rows at the position; two blocks per CU are resident.
 template <int C, int NBO, bool DENSE, bool VAR>
-__global__ __launch_bounds__(256) void k_tile_part_f32(ConvArgs a) {
+__global__ __launch_bounds__(256, 2) void k_tile_part_f32(ConvArgs a) {
     constexpr int KBL = C;                    // 16-deep K blocks per tile (16 C / 16)
     constexpr int KW = KBL / 4;               // blocks per wave
-    constexpr int KB = 4;                     // blocks per batch of loads
+    constexpr int KB = NBO < 4 ? 32 / NBO : 4;   // blocks per batch of loads
+    constexpr int RG = 4;                     // row groups of 16 items
     static_assert(KW % KB == 0, "whole batches");
     __shared__ int s_pos[64];
-    __shared__ floatx4 s_acc[4][4][NBO][64];  // [wave][row group][n-block][lane]
+    __shared__ floatx4 s_acc[4][RG][NBO][64]; // [wave][row group][n-block][lane]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cnt = work_count<DENSE>(a);
-    const XcdRange xr = xcd_range(cnt, 64);
+    const int G = min(64, max(1, (cnt + (int)gridDim.x - 1) / (int)gridDim.x));
+    const XcdRange xr = xcd_range(cnt, G);
     const float *act = static_cast<const float *>(a.in);
     const int ntiles = a.TH * a.TW;
     const int row = lane & 15, kq = lane >> 4;
@@ -494,13 +508,14 @@ __global__ __launch_bounds__(256) void k_tile_part_f32(ConvArgs a) {
         boff[nb] = (kq * a.n_out + o) * 4;
     }
     for (int g = xr.first; g < xr.end; g += xr.stride) {   // uniform per block
-        uint32_t e[4];
-        int pos[4];
-        const float *arow[4];
+        const int end = min(g + G, xr.end);
+        uint32_t e[RG];
+        int pos[RG];
+        const float *arow[RG];
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
+        for (int rg = 0; rg < RG; ++rg) {
             const int it = g + 16 * rg + row;
-            const bool valid = it < xr.end;
+            const bool valid = it < end;
             e[rg] = valid ? item_word<DENSE>(a, it) : 0u;
             const TileRef r = item_ref(a, e[rg]);
             pos[rg] = valid ? r.tile : -1;
@@ -510,7 +525,7 @@ __global__ __launch_bounds__(256) void k_tile_part_f32(ConvArgs a) {
         }
         if (tid < 64) {
             const int t2 = g + tid;
-            s_pos[tid] = t2 < xr.end ? item_ref(a, item_word<DENSE>(a, t2)).tile : -1;
+            s_pos[tid] = t2 < end ? item_ref(a, item_word<DENSE>(a, t2)).tile : -1;
         }
         lds_barrier();
         const int my_sp = s_pos[lane];
@@ -520,51 +535,58 @@ __global__ __launch_bounds__(256) void k_tile_part_f32(ConvArgs a) {
             const uint64_t pmask = __ballot(my_sp == P);
             left &= ~pmask;
             const float *wp = a.hw + ((size_t)P * KBL + KW * wave) * blk_elems;
-            floatx4 acc[4][NBO];
+            floatx4 acc[RG][NBO];
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg)
+            for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
                 for (int nb = 0; nb < NBO; ++nb) acc[rg][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
             // Row groups with no row at P skip their loads and matrix ops
             // (the flags are uniform: whole groups, from the ballot).
-            bool gact[4];
+            bool gact[RG];
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) gact[rg] = ((pmask >> (16 * rg)) & 0xFFFFu) != 0;
+            for (int rg = 0; rg < RG; ++rg) gact[rg] = ((pmask >> (16 * rg)) & 0xFFFFu) != 0;
+#pragma unroll 1
             for (int s0 = 0; s0 < KW; s0 += KB) {
-                floatx4 av[KB][4], bv[KB][NBO];
+                floatx4 bv[KB][NBO];
 #pragma unroll
-                for (int s = 0; s < KB; ++s) {
+                for (int s = 0; s < KB; ++s)
 #pragma unroll
                     for (int nb = 0; nb < NBO; ++nb)
                         bv[s][nb] = bval[nb] ? *reinterpret_cast<const floatx4 *>(wp + (size_t)(s0 + s) * blk_elems + boff[nb])
                                              : floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg)
-                        av[s][rg] = gact[rg] && pos[rg] == P ? *reinterpret_cast<const floatx4 *>(arow[rg] + 16 * (s0 + s))
-                                                             : floatx4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
+                for (int rg = 0; rg < RG; ++rg) {
                     if (!gact[rg]) continue;
+                    constexpr int KA = 16 / NBO;              // of activations
 #pragma unroll
-                    for (int s = 0; s < KB; ++s)
+                    for (int s1 = 0; s1 < KB; s1 += KA) {
+                        floatx4 av[KA];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
+                        for (int s = 0; s < KA; ++s)
+                            av[s] = pos[rg] == P ? *reinterpret_cast<const floatx4 *>(arow[rg] + 16 * (s0 + s1 + s))
+                                                 : floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                            for (int nb = 0; nb < NBO; ++nb)
-                                acc[rg][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][rg][j], bv[s][nb][j],
-                                                                                   acc[rg][nb], 0, 0, 0);
+                        for (int s = 0; s < KA; ++s)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                                for (int nb = 0; nb < NBO; ++nb)
+                                    acc[rg][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][j], bv[s1 + s][nb][j],
+                                                                                       acc[rg][nb], 0, 0, 0);
+                    }
                 }
             }
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg)
+            for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
                 for (int nb = 0; nb < NBO; ++nb) s_acc[wave][rg][nb][lane] = acc[rg][nb];
             lds_barrier();
             // Wave `wave` finishes row group `wave`: the K quarters in wave order.
             const uint64_t gmask = (pmask >> (16 * wave)) & 0xFFFFu;
             if (gmask) {                                     // uniform per wave
-                const uint32_t ew = wave == 0 ? e[0] : wave == 1 ? e[1] : wave == 2 ? e[2] : e[3];
+                uint32_t ew = e[0];
+#pragma unroll
+                for (int rg = 1; rg < RG; ++rg) ew = wave == rg ? e[rg] : ew;
 #pragma unroll
                 for (int nb = 0; nb < NBO; ++nb) {
                     const floatx4 v = s_acc[0][wave][nb][lane] + s_acc[1][wave][nb][lane] +
@@ -650,7 +672,7 @@ template <int C, bool DENSE, bool VAR>
 hipError_t run_tile_part_bf16(const ConvArgs &a, int cus, hipStream_t s) {
     // Two blocks per CU are resident (registers), so a larger grid would only
     // run in a second generation.
-    const int grid = dev::persistent_grid(cus * (a.n_out <= 32 ? 2 : 1), (a.max_tiles + 63) / 64);
+    const int grid = dev::persistent_grid(cus * (a.n_out <= 32 ? 2 : 1), a.max_tiles);
     if (a.n_out <= 16) hipLaunchKernelGGL((k_tile_part_bf16<C, 1, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);
     else if (a.n_out <= 32) hipLaunchKernelGGL((k_tile_part_bf16<C, 2, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_tile_part_bf16<C, 4, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);
@@ -674,7 +696,7 @@ hipError_t launch_tile_part_bf16(const ConvArgs &a, int cus, hipStream_t s, bool
 
 template <int C, bool DENSE, bool VAR>
 hipError_t run_tile_part_f32(const ConvArgs &a, int cus, hipStream_t s) {
-    const int grid = dev::persistent_grid(cus * 2, (a.max_tiles + 63) / 64);
+    const int grid = dev::persistent_grid(cus * 2, a.max_tiles);
     if (a.n_out <= 16) hipLaunchKernelGGL((k_tile_part_f32<C, 1, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);
     else if (a.n_out <= 32) hipLaunchKernelGGL((k_tile_part_f32<C, 2, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_tile_part_f32<C, 4, DENSE, VAR>), dim3(grid), dim3(256), 0, s, a);

@@ -84,3 +84,26 @@ def test_values_beyond_the_split(torch, value):
             assert np.all(np.abs(got[fin] - want[fin]) <= 1152 * 2.0 ** -24 * size[fin] + 1e-30), l
         cur = torch.from_numpy(got)                       # the next layer's input as the GPU has it
     net.close()
+
+
+# Head partials by position: groups of 1 item (88 tiles), 5 (2112) and 18 (8800)
+# a block, one to three column blocks; a stream's logits are those it has alone,
+# and the oracle's.
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("n_out", [6, 18, 40])
+def test_head_groups(torch, act, n_out):
+    wl = synth.Workload(cid=203, streams=100, frames=1, h=42, w=32, convs=(64, 128, 128), n_out=n_out,
+                        n_sprites=3, smin=3, smax=6, vmin=1, vmax=3)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(100), frames=1))[0][:, None]
+    dev = torch.from_numpy(x).cuda()
+    net, one = make_net(wl, 100, weights, act_dtype=act), make_net(wl, 1, weights, act_dtype=act)
+    got = {n: net.full(dev[:n].contiguous()).cpu().numpy() for n in (24, 100)}
+    for i in (0, 11, 23):
+        alone = one.full(dev[i:i + 1].contiguous()).cpu().numpy()[0]
+        assert np.array_equal(alone, got[24][i]) and np.array_equal(alone, got[100][i]), i
+        ref, _ = oracle.forward(oracle_net(wl, act == "bf16"), *weights, x[i:i + 1])
+        tol = ATOL_F32 if act == "f32" else 1e-2 * np.abs(ref).max()
+        assert np.abs(alone - ref[0]).max() <= tol, i
+    net.close()
+    one.close()

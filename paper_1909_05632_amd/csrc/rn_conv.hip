@@ -26,7 +26,7 @@
 // are a sum over tiles of each tile's own contribution.  The epilogue computes
 // that contribution for the tiles it recomputes and stores it per (stream,
 // tile); clean tiles keep theirs.  The head then only adds partials.
-#include "rn_device.hpp"
+#include "rn_split.hpp"
 
 namespace rn {
 namespace {
@@ -284,96 +284,15 @@ __global__ __launch_bounds__(256) void k_conv_first4_mfma(ConvArgs a) {
 
 // ------------------------------------------------------------------ MFMA layers
 
-// Implicit GEMM per tile: M = 16 pixels, N = COUT, K = 9 * CIN.
 // v_mfma_f32_16x16x4_f32 operand layout (lane l, kq = l / 16):
 //   A: row l % 16, k-row kq;  B: k-row kq, column l % 16;
 //   D: rows 4 kq + i, column l % 16, i = 0..3.
 // Rows are tile pixels in column-major order, row m = pixel (m % 4, m / 4), so
-// lane l of D holds pixels (i, kq), i = 0..3, of channel l % 16 + 16 nb.
-// K is walked per kernel position in channel blocks of 16 (plus one block of
-// 8 when CIN % 16 = 8).  Inside a block, k-step j gives lane group kq the
-// channel c0 + 4 kq + j (c0 + 2 kq + j in a block of 8), so each lane's A
-// values for the block's 4 (2) k-steps are contiguous channels of one halo
-// pixel: one 16-byte (8-byte) LDS read.  The weights are packed to match,
-// [kpos][block][nb][lane][j], so the B values are one 16-byte read per nb.
-// Bank layout of the halo: the LDS serves 16 lanes of a 16-byte read per
-// clock (64 banks), and the A reads of such a group touch 16 pixels of the
-// 6x6 halo, one chunk each.  The halo is stored unpadded (pixel stride CIN,
-// which lets 8 waves' halos fit in LDS next to the 40->80 weights) with the
-// 16-byte chunk index of halo pixel (hy, hx) XOR-ed with g(hy, hx): hy % 2
-// for 10 chunks per pixel, hy % 4 for 20, (hy % 4) + 4 (hx % 4) for 16 or
-// 32; every group then falls in 16 distinct bank groups for all 9 kernel
-// positions, and the 8-byte reads of the 8-channel tail block in distinct
-// banks too (checked exhaustively on the host).  Blocks are double-buffered:
-// the operands of the next block are read while the matrix cores work on the
-// current one.
-template <int CIN, int COUT>
-struct Mfma {
-    static constexpr int NB = COUT / 16;
-    static constexpr int CS = CIN;            // halo pixel stride in LDS (floats)
-    static constexpr int NF = CIN / 16;       // full channel blocks per kernel position
-    static constexpr int TAIL = (CIN % 16) ? 1 : 0;
-    static constexpr int NBLK = NF + TAIL;
-    static constexpr int C4 = CIN / 4;        // float4 per halo pixel
-    static constexpr int HALO = 36 * CS;      // floats of one halo in LDS
-    static constexpr int SR = COUT + 4;       // row stride of the output staging area
-    static constexpr int HV = (36 * C4 + 63) / 64;   // 16-byte halo loads per lane
-    static constexpr int WTOT = 9 * CIN * COUT;
-    static_assert(16 * SR <= HALO, "output staging must fit in the halo area");
-    static_assert(COUT % 16 == 0 && CIN % 8 == 0, "MFMA tiling");
-    static_assert(C4 == 10 || C4 == 20 || C4 == 16 || C4 == 32, "halo swizzle defined for 40, 64, 80, 128 channels");
-};
+// lane l of D holds pixels (i, kq), i = 0..3, of channel l % 16 + 16 nb (D is
+// the same for v_mfma_f32_16x16x32_bf16, whose lanes hold eight K values each).
 
-// Global -> registers: the halo of one tile, 16 bytes per lane per load.
-template <int CIN, int COUT, bool VAR>
-__device__ inline void fetch_halo(const ConvArgs &a, const TileRef &r, float4 *regs, int lane) {
-    using M = Mfma<CIN, COUT>;
-    const float *src = static_cast<const float *>(a.in) + (VAR ? 0 : (size_t)r.slot * a.in_stride);
-#pragma unroll
-    for (int j = 0; j < M::HV; ++j) {
-        const int h = lane + 64 * j;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (h < 36 * M::C4) {
-            const int pos = h / M::C4, c4 = h - pos * M::C4;
-            const int hy = pos / 6, hx = pos - hy * 6;
-            const int y = r.ty * kTile - 1 + hy, x = r.tx * kTile - 1 + hx;
-            if (y >= 0 && y < a.H && x >= 0 && x < a.W)
-                v = *reinterpret_cast<const float4 *>(
-                    (VAR ? var_src<float>(a, r.slot, y, x, CIN)
-                         : src + ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CIN) +
-                    c4 * 4);
-        }
-        regs[j] = v;
-    }
-}
-
-// Offset (floats) of 16-byte channel chunk c of halo pixel p.
-template <int CIN, int COUT>
-__device__ inline int chunk_off(int p, int c) {
-    using M = Mfma<CIN, COUT>;
-    const int hy = p / 6, hx = p - 6 * hy;
-    const int g = M::C4 == 10 ? (hy & 1) : M::C4 == 20 ? (hy & 3) : (hy & 3) | ((hx & 3) << 2);
-    return p * M::CS + 4 * (c ^ g);
-}
-
-template <int CIN, int COUT>
-__device__ inline void store_halo(float *halo, const float4 *regs, int lane) {
-    using M = Mfma<CIN, COUT>;
-#pragma unroll
-    for (int j = 0; j < M::HV; ++j) {
-        const int h = lane + 64 * j;
-        if (h < 36 * M::C4) {
-            const int pos = h / M::C4, c4 = h - pos * M::C4;
-            *reinterpret_cast<float4 *>(halo + chunk_off<CIN, COUT>(pos, c4)) = regs[j];
-        }
-    }
-}
-
-// Layer 1 folded into the halo staging (one input channel): the 6x6 x CIN
-// layer-1 activations around the tile are computed from the 8x8 input patch
-// around it, in the same FMA order as k_conv_first_f32 (so the values are the
-// bits that kernel would have cached).  Halo pixels outside the image are the
-// layer-2 zero padding.
+// Layer 1 folded into layer 2 (one input channel): the 8x8 input patch around
+// a tile, one pixel a lane; pixels outside the image are 0.
 template <bool VAR>
 __device__ inline float fetch_patch(const ConvArgs &a, const TileRef &r, int lane) {
     const int y = r.ty * kTile - 2 + (lane >> 3), x = r.tx * kTile - 2 + (lane & 7);
@@ -381,134 +300,6 @@ __device__ inline float fetch_patch(const ConvArgs &a, const TileRef &r, int lan
     if constexpr (VAR) return in ? var_input(a, r.slot, 0, y, x) : 0.f;
     const float *plane = static_cast<const float *>(a.in) + (size_t)r.slot * a.in_stride;
     return in ? plane[(size_t)y * a.W + x] : 0.f;
-}
-
-// The 8x8 input patch sits in the last 64 floats of the wave's halo area
-// (written there by the caller before the previous tile's epilogue, whose
-// output staging ends below it).
-template <int CIN, int COUT>
-__device__ inline float *patch_area(float *halo) {
-    return halo + Mfma<CIN, COUT>::HALO - 64;
-}
-
-template <int CIN, int COUT>
-__device__ inline void build_halo_fused(float *halo, const ConvArgs &a, const TileRef &r, const float *s_w1,
-                                        const float *s_b1, int lane) {
-    using M = Mfma<CIN, COUT>;
-    constexpr int NU = 36 * M::C4;            // 4-channel units of the halo
-    constexpr int UV = (NU + 63) / 64;
-    static_assert(16 * M::SR <= M::HALO - 64, "output staging must end below the patch");
-    const float *patch = patch_area<CIN, COUT>(halo);
-    wave_sync();
-    float4 v[UV];
-#pragma unroll
-    for (int k = 0; k < UV; ++k) {
-        const int u = lane + 64 * k;
-        v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (u < NU) {
-            const int pos = u / M::C4, c4 = u - pos * M::C4;
-            const int hy = pos / 6, hx = pos - hy * 6;
-            const int y = r.ty * kTile - 1 + hy, x = r.tx * kTile - 1 + hx;
-            if (y >= 0 && y < a.H && x >= 0 && x < a.W) {
-                float o[4];
-#pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    const int c = 4 * c4 + cc;
-                    float acc = 0.0f;
-#pragma unroll
-                    for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-                        for (int kx = 0; kx < 3; ++kx)
-                            acc = fmaf(s_w1[(ky * 3 + kx) * CIN + c], patch[(hy + ky) * 8 + hx + kx], acc);
-                    const float t = acc + s_b1[c];
-                    o[cc] = t > 0.0f ? t : 0.0f;
-                }
-                v[k] = make_float4(o[0], o[1], o[2], o[3]);
-            }
-        }
-    }
-    wave_sync();                              // patch reads done before the halo overwrites it
-#pragma unroll
-    for (int k = 0; k < UV; ++k) {
-        const int u = lane + 64 * k;
-        if (u < NU) {
-            const int pos = u / M::C4, c4 = u - pos * M::C4;
-            *reinterpret_cast<float4 *>(halo + chunk_off<CIN, COUT>(pos, c4)) = v[k];
-        }
-    }
-}
-
-template <int NB>
-struct BlockOps {
-    float4 a;
-    float4 b[NB];
-};
-
-// Operands of channel block `blk` at kernel position `kpos` (s_w holds the
-// weights from kernel position k0 on).
-template <int CIN, int COUT>
-__device__ inline void load_block(BlockOps<Mfma<CIN, COUT>::NB> &o, const float *halo, int pix, const float *s_w,
-                                  int kpos, int k0, int blk, int lane) {
-    using M = Mfma<CIN, COUT>;
-    const int kq = lane >> 4;
-    const int ky = kpos / 3, kx = kpos - ky * 3;
-    const int p = pix + ky * 6 + kx;
-    const float *wb = s_w + (size_t)(kpos - k0) * CIN * COUT + blk * 16 * COUT;
-    if (blk < M::NF) {
-        o.a = *reinterpret_cast<const float4 *>(halo + chunk_off<CIN, COUT>(p, 4 * blk + kq));
-#pragma unroll
-        for (int nb = 0; nb < M::NB; ++nb)
-            o.b[nb] = *reinterpret_cast<const float4 *>(wb + (nb * 64 + lane) * 4);
-    } else {
-        const float2 a2 = *reinterpret_cast<const float2 *>(
-            halo + chunk_off<CIN, COUT>(p, 4 * blk + (kq >> 1)) + 2 * (kq & 1));
-        o.a = make_float4(a2.x, a2.y, 0.f, 0.f);
-#pragma unroll
-        for (int nb = 0; nb < M::NB; ++nb) {
-            const float2 b2 = *reinterpret_cast<const float2 *>(wb + (nb * 64 + lane) * 2);
-            o.b[nb] = make_float4(b2.x, b2.y, 0.f, 0.f);
-        }
-    }
-}
-
-template <int CIN, int COUT>
-__device__ inline void mma_block(floatx4 *acc, const BlockOps<Mfma<CIN, COUT>::NB> &o, int blk) {
-    using M = Mfma<CIN, COUT>;
-    const int steps = blk < M::NF ? 4 : 2;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (j >= steps) break;
-        const float av = j == 0 ? o.a.x : j == 1 ? o.a.y : j == 2 ? o.a.z : o.a.w;
-#pragma unroll
-        for (int nb = 0; nb < M::NB; ++nb) {
-            const float bv = j == 0 ? o.b[nb].x : j == 1 ? o.b[nb].y : j == 2 ? o.b[nb].z : o.b[nb].w;
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[nb], 0, 0, 0);
-        }
-    }
-}
-
-// acc += A(halo, kernel positions [k0, k0 + NK)) x B(weights in LDS from kernel position k0).
-template <int CIN, int COUT, int NK>
-__device__ inline void mfma_positions(floatx4 *acc, const float *halo, const float *s_w, int k0, int lane) {
-    using M = Mfma<CIN, COUT>;
-    const int mrow = lane & 15;
-    const int pix = (mrow & 3) * 6 + (mrow >> 2);   // column-major pixel rows
-    BlockOps<M::NB> cur, nxt;
-    load_block<CIN, COUT>(cur, halo, pix, s_w, k0, k0, 0, lane);
-    for (int kp = 0; kp < NK; ++kp) {
-        const int kpos = k0 + kp;
-#pragma unroll
-        for (int blk = 0; blk < M::NBLK; ++blk) {
-            if (blk + 1 < M::NBLK) load_block<CIN, COUT>(nxt, halo, pix, s_w, kpos, k0, blk + 1, lane);
-            else if (kp + 1 < NK) load_block<CIN, COUT>(nxt, halo, pix, s_w, kpos + 1, k0, 0, lane);
-            // Keep the next block's LDS reads ahead of this block's matrix ops
-            // (the scheduler would otherwise sink them to their first use).
-            __builtin_amdgcn_sched_barrier(0);
-            mma_block<CIN, COUT>(acc, cur, blk);
-            __builtin_amdgcn_sched_barrier(0);
-            cur = nxt;
-        }
-    }
 }
 
 // Bias, ReLU, zero outside the image, coalesced store of the 16 x COUT tile
@@ -616,28 +407,14 @@ __device__ inline void epilogue(const ConvArgs &a, const TileRef &r, floatx4 *ac
     wave_sync();
 }
 
-// Weights resident in LDS for the whole persistent kernel, 8 waves per block
-// (two per SIMD: waves w and w + 4 share one); every wave walks its own tiles
-// independently.  A tile's input (the next halo, or fused, the next 8x8 input
-// patch) is fetched into registers a whole tile ahead.  Measured on gfx950: a
-// wave's VALU work makes no progress while the other wave of its SIMD issues
-// float32 matrix ops, so the two add up and the per-tile VALU work is what
-// this kernel keeps small (item words 64 at a time, one per lane, read with
-// readlane; the epilogue masks on bit patterns).
-template <int CIN, int COUT, int WAVES>
-struct Resident {
-    static constexpr size_t lds_bytes =
-        (size_t)(Mfma<CIN, COUT>::WTOT + WAVES * Mfma<CIN, COUT>::HALO) * sizeof(float);
-};
-
-// Item words of a wave's items, 64 at a time: lane j of chunk c holds the
-// word of the wave's item 64 c + j (items past the last repeat the range's
-// last word, so every load reads a valid entry).  The words of a whole chunk
-// arrive in one load, long before they are read with readlane, so no per-tile
-// word load is waited for.
+// Item words of a wave's items (the block's items t, t + G, ..), 64 at a time:
+// lane j of chunk c holds the word of the wave's item 64 c + j (past the last:
+// the block's last item's word, so every load reads a valid entry).  The words
+// of a whole chunk arrive in one load, long before they are read with
+// readlane, so no per-tile word load is waited for.
 template <bool DENSE>
-__device__ inline uint32_t word_chunk(const ConvArgs &a, int first, int stride, int end, int c, int lane) {
-    return item_word<DENSE>(a, (int)min((long long)first + (long long)(64 * c + lane) * stride, (long long)end - 1));
+__device__ inline uint32_t word_chunk(const ConvArgs &a, const RunRange &rr, int t, int G, int c, int lane) {
+    return item_word<DENSE>(a, rr.at(min(t + (64 * c + lane) * G, rr.count - 1)));
 }
 
 // Word of item j, held in chunk c0 (w0) or c0 + 1 (w1); j is wave-uniform.
@@ -646,112 +423,420 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
     return item_ref(a, (uint32_t)__builtin_amdgcn_readlane((int)src, j & 63));
 }
 
-// Halo of tile r into LDS, then the input loads of tile rn (when there is
-// one) into the registers just freed (fused: the patch was written to its
-// area, above the output staging, before the previous tile's epilogue).
-template <int CIN, int COUT, bool FUSE, bool VAR>
-__device__ inline void res_build(const ConvArgs &a, float *halo, const float *s_w1, const float *s_b1, float4 *pre,
-                                 float &pin, const TileRef &r, const TileRef &rn, bool next, int lane) {
-    if constexpr (FUSE) {
-        if (next) pin = fetch_patch<VAR>(a, rn, lane);
-        build_halo_fused<CIN, COUT>(halo, a, r, s_w1, s_b1, lane);
-    } else {
-        store_halo<CIN, COUT>(halo, pre, lane);
-        if (next) fetch_halo<CIN, COUT, VAR>(a, rn, pre, lane);
+// ---- 40 -> 80: weights in registers, bf16 matrix cores with split operands
+//
+// Bound: matrix issue.  A tile is 2 * 16 * 80 * 360 flops six times over on
+// v_mfma_f32_16x16x32_bf16 (rn_split.hpp): 360 ops with K padded from 360 to
+// 384, 1440 cycles a tile when one wave of each SIMD issues nothing else (the
+// float32 instruction: 450 ops of 32 cycles, 3600).  Split, the weights take
+// 184 KB: more than LDS, but they fit the registers of four waves that each
+// hold a quarter of K (three k-steps x 80 channels x three planes, 180
+// registers).  So a block of eight waves splits the work by role, two waves a
+// SIMD, and the vector work runs beside the matrix ops:
+//   waves 0-3 (one per SIMD) read the pixels of both tiles of a group from LDS
+//     and sum their quarter of K into partial products in LDS;
+//   waves 4, 5 add a tile's four partial products (in wave order) and run the
+//     epilogue;
+//   waves 6, 7 build a tile's halo: the 6 x 6 x 40 layer-1 activations, loaded
+//     or (FUSE) computed from the 8 x 8 input patch, split into three bf16
+//     planes.  Lane c4 + 10 hy has four channels of a halo row, so the folded
+//     layer's weights stay in its registers too.
+// The roles work on consecutive groups: in a period groups i (halo), i - 1
+// (products) and i - 2 (epilogue), one block barrier a period.
+//
+// K is walked in octets of channels, octet g = position g / 5, channels
+// 8 (g % 5): k-step s of 32 gives lane group kq octet 4 s + kq (octets 45 to 47
+// have zero weights).  A plane's halo pixel (hy, hx) starts at 16-byte slot
+// 36 hy + 5 hx, so the 16 pixels of a 16-lane read lie in 16 distinct bank
+// groups at every octet.
+//
+// A result that is not finite (an operand the split cannot carry), or, but for
+// variants, that lies within 2^-20 of 0 relative to the largest of its lane, is
+// taken from the plain float32 product of its tile instead (about 2 tiles in
+// 1000, some 8 us of one wave each; two float32 roundings of the sums differ by
+// 2^-22 of it): ReLU decisions are then those of the float32 sums, which the
+// gradient depends on.
+struct Res {
+    static constexpr int CIN = 40, COUT = 80, NB = COUT / 16, KS = 12, KW = KS / 4;
+    static constexpr int OCT = 45;                    // octets of K
+    static constexpr int ROW = 36 * 16;               // bytes of a halo row
+    static constexpr int PLANE = 6 * ROW;
+    static constexpr int HALO = 3 * PLANE;            // one tile
+    static constexpr int PART = 4 * NB * 64 * 16;     // partial products of one tile
+    // Two tiles a group: three halo buffers (built, read, kept for the check
+    // of the sums), two of partial products.
+    static constexpr int OPART = 3 * 2 * HALO, OSMALL = OPART + 2 * 2 * PART;
+    static constexpr size_t lds_bytes = (size_t)OSMALL + 2 * 64 * 4 + COUT * 4;
+    static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");
+    static constexpr size_t w_bytes = (size_t)KS * NB * 3 * 1024;
+};
+
+// The plain float32 product of a tile from its halo planes (their sum is the
+// float32 value), in the order of v_mfma_f32_16x16x4_f32 over (position,
+// 16-channel block, k-step): float32 weights as pack_conv_mfma lays them out.
+__device__ inline void res_plain(const float *w, const unsigned char *halo, floatx4 (&acc)[Res::NB], int lane) {
+    using R = Res;
+    const int m = lane & 15, kq = lane >> 4;
+    const unsigned char *px = halo + (m & 3) * R::ROW + (m >> 2) * 80;
+    auto value = [&](int off) {
+        const unsigned char *p = px + off;
+        return (float)*reinterpret_cast<const __bf16 *>(p) + (float)*reinterpret_cast<const __bf16 *>(p + R::PLANE) +
+               (float)*reinterpret_cast<const __bf16 *>(p + 2 * R::PLANE);
+    };
+#pragma unroll
+    for (int nb = 0; nb < R::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // Blocks u = 3 kpos + blk of 16, 16 and 8 channels; a block's weights are
+    // loaded while the previous one's products run.
+    auto load = [&](floatx4 (&b)[R::NB], int u) __attribute__((always_inline)) {
+        const int kpos = u / 3, blk = u - 3 * kpos;
+        const float *p = w + kpos * R::CIN * R::COUT + blk * 16 * R::COUT;
+#pragma unroll
+        for (int nb = 0; nb < R::NB; ++nb) {
+            if (blk < 2) {
+                b[nb] = *reinterpret_cast<const floatx4 *>(p + (nb * 64 + lane) * 4);
+            } else {
+                const float2 v = *reinterpret_cast<const float2 *>(p + (nb * 64 + lane) * 2);
+                b[nb] = floatx4{v.x, v.y, 0.f, 0.f};
+            }
+        }
+    };
+    floatx4 b[R::NB], next[R::NB];
+    load(b, 0);
+#pragma unroll 1
+    for (int u = 0; u < 27; ++u) {
+        load(next, min(u + 1, 26));
+        const int kpos = u / 3, blk = u - 3 * kpos, steps = blk < 2 ? 4 : 2;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= steps) break;                        // uniform
+            const float av = value(kpos / 3 * R::ROW + kpos % 3 * 80 + 2 * (16 * blk + steps * kq + j));
+#pragma unroll
+            for (int nb = 0; nb < R::NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[nb][j], acc[nb], 0, 0, 0);
+        }
+#pragma unroll
+        for (int nb = 0; nb < R::NB; ++nb) b[nb] = next[nb];
     }
 }
 
-template <int CIN, int COUT, int WAVES, bool DENSE, bool FUSE, int NO, bool VAR>
-__global__ __launch_bounds__(WAVES * 64) void k_conv_mfma_res(ConvArgs a) {
-    using M = Mfma<CIN, COUT>;
-    static_assert(WAVES == 8, "item mapping for two waves per SIMD");
-    extern __shared__ float smem[];
-    __shared__ float s_bias[COUT];
-    __shared__ float s_w1[FUSE ? 9 * CIN : 1];
-    __shared__ float s_b1[FUSE ? CIN : 1];
+template <bool DENSE, bool FUSE, int NO, bool VAR>
+__global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
+    using R = Res;
+    extern __shared__ __align__(16) unsigned char lds[];
+    float *s_patch = reinterpret_cast<float *>(lds + R::OSMALL);
+    float *s_bias = s_patch + 128;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cnt = work_count<DENSE>(a);
-    const XcdRangeW xr = xcd_range_simd2(cnt, wave);
-    if (xr.block_first >= xr.end) return;                 // uniform per block
-    const int stride = xr.stride;
-    const int n_me = xr.first < xr.end ? (xr.end - xr.first + stride - 1) / stride : 0;
-    float *s_w = smem;
-    float *halo = smem + M::WTOT + wave * M::HALO;
+    const RunRange rr = run_range(cnt);
+    if (rr.count <= 0) return;                            // uniform per block
+    const int G = rr.count > 1 ? 2 : 1;                   // tiles a group
+    const int groups = (rr.count + G - 1) / G;
+    auto halo_of = [&](int i, int t) { return lds + (2 * (i % 3) + t) * R::HALO; };
+    auto part_of = [&](int i, int t) { return reinterpret_cast<floatx4 *>(lds + R::OPART + (2 * (i & 1) + t) * R::PART); };
+    if (tid < R::COUT) s_bias[tid] = a.bias[tid];
 
-    // Item words in two chunks of 64 (w0: chunk c0, w1: chunk c0 + 1); the
-    // first tile's input is fetched before the weights are staged.
-    int c0 = 0;
-    uint32_t w0 = word_chunk<DENSE>(a, xr.first, stride, xr.end, 0, lane);
-    uint32_t w1 = word_chunk<DENSE>(a, xr.first, stride, xr.end, 1, lane);
-    constexpr int HVR = FUSE ? 1 : M::HV;
-    float4 pre[HVR];
-    float pin = 0.f;
-    if (n_me > 0) {
-        if constexpr (FUSE) pin = fetch_patch<VAR>(a, item_of(a, w0, w1, c0, 0), lane);
-        else fetch_halo<CIN, COUT, VAR>(a, item_of(a, w0, w1, c0, 0), pre, lane);
-    }
-    // Weights into LDS in batches of 8 loads per thread, each batch issued
-    // before any of it is written (indices past the end read the last
-    // element and are not stored): a few memory round trips, not one per
-    // 16 bytes.
-    // The biases and the folded layer's weights (at most one value of each
-    // per thread) are loaded up front, in flight with the weights below.
-    static_assert(COUT <= WAVES * 64 && 9 * CIN <= WAVES * 64, "one small value per thread");
-    const float bias_v = tid < COUT ? a.bias[tid] : 0.f;
-    float w1_v = 0.f, b1_v = 0.f;
-    if constexpr (FUSE) {
-        if (tid < 9 * CIN) w1_v = a.w1[tid];
-        if (tid < CIN) b1_v = a.b1[tid];
-    }
-    const float4 *wg = static_cast<const float4 *>(a.w);
-    constexpr int NW4 = M::WTOT / 4, WPER = (NW4 + WAVES * 64 - 1) / (WAVES * 64), WB = 8;
+    if (wave < 4) {
+        bf16x8 w[R::KW][R::NB][3];
+        const bf16x8 *wg = static_cast<const bf16x8 *>(a.w_split) + (size_t)wave * R::KW * R::NB * 3 * 64 + lane;
 #pragma unroll
-    for (int k0 = 0; k0 < WPER; k0 += WB) {
-        float4 wv[WB];
+        for (int s = 0; s < R::KW; ++s)
 #pragma unroll
-        for (int k = 0; k < WB; ++k)
-            if (k0 + k < WPER) wv[k] = wg[min(tid + (k0 + k) * WAVES * 64, NW4 - 1)];
+            for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
-        for (int k = 0; k < WB; ++k) {
-            const int j = tid + (k0 + k) * WAVES * 64;
-            if (k0 + k < WPER && j < NW4) reinterpret_cast<float4 *>(s_w)[j] = wv[k];
+                for (int pl = 0; pl < 3; ++pl) w[s][nb][pl] = wg[((s * R::NB + nb) * 3 + pl) * 64];
+        const int m = lane & 15, kq = lane >> 4;
+        int off[R::KW];
+#pragma unroll
+        for (int s = 0; s < R::KW; ++s) {
+            const int g = min(4 * (wave * R::KW + s) + kq, R::OCT - 1), pos = g / 5;
+            off[s] = ((m & 3) + pos / 3) * R::ROW + ((m >> 2) + pos % 3) * 80 + (g - 5 * pos) * 16;
         }
-    }
-    if (tid < COUT) s_bias[tid] = bias_v;
-    if constexpr (FUSE) {
-        if (tid < 9 * CIN) s_w1[tid] = w1_v;
-        if (tid < CIN) s_b1[tid] = b1_v;
-    }
-    lds_barrier();                                        // the first input loads stay in flight
-
-    if (n_me == 0) return;                                // no block barrier after this point
-
-    // Per tile: halo (issuing the next tile's input loads first), matrix
-    // work, epilogue; fused, the next patch goes to its area after the
-    // epilogue, its load having had the whole tile to arrive.
-    if constexpr (FUSE) patch_area<CIN, COUT>(halo)[lane] = pin;
-    for (int k = 0; k < n_me; ++k) {
-        if (k >= 64 * (c0 + 1)) {                         // tile k starts the next chunk of words
-            w0 = w1;
-            ++c0;
-            w1 = word_chunk<DENSE>(a, xr.first, stride, xr.end, c0 + 1, lane);
-        }
-        res_build<CIN, COUT, FUSE, VAR>(a, halo, s_w1, s_b1, pre, pin, item_of(a, w0, w1, c0, k),
-                                        item_of(a, w0, w1, c0, k + 1), k + 1 < n_me, lane);
-        wave_sync();
-        floatx4 acc[M::NB];
+        for (int i = 0; i < groups + 2; ++i) {
+            if (i >= 1 && i <= groups) {
+                bf16x8 x[R::KW][3];
+                auto load_x = [&](int s, int t) __attribute__((always_inline)) {
+                    const unsigned char *h = halo_of(i - 1, t) + off[s];
 #pragma unroll
-        for (int nb = 0; nb < M::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-        // A wave in its matrix phase issues ahead of the other wave of its SIMD.
-        __builtin_amdgcn_s_setprio(2);
-        mfma_positions<CIN, COUT, 9>(acc, halo, s_w, 0, lane);
-        __builtin_amdgcn_s_setprio(0);
-        wave_sync();
-        epilogue<COUT, NO, VAR>(a, item_of(a, w0, w1, c0, k), acc, s_bias, halo, lane, xr.first + k * stride);
+                    for (int pl = 0; pl < 3; ++pl) x[s][pl] = *reinterpret_cast<const bf16x8 *>(h + pl * R::PLANE);
+                };
+#pragma unroll
+                for (int s = 0; s < R::KW; ++s) load_x(s, 0);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    if (t >= G) break;                    // uniform
+                    floatx4 acc[R::NB];
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    // (pixel plane, weight plane), small terms first
+                    constexpr int px[6] = {2, 0, 1, 1, 0, 0}, pw[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                    for (int s = 0; s < R::KW; ++s) {
+#pragma unroll
+                        for (int k = 0; k < 6; ++k)
+#pragma unroll
+                            for (int nb = 0; nb < R::NB; ++nb)
+                                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[s][px[k]], w[s][nb][pw[k]], acc[nb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (t == 0) load_x(s, 1);         // (one tile a group: read, not used)
+                    }
+                    floatx4 *p = part_of(i - 1, t) + wave * R::NB * 64 + lane;
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
+                }
+            }
+            lds_barrier();
+        }
+    } else if (wave < 6) {
+        const int t = wave - 4;
+        const int mine = t < G ? (rr.count - t + G - 1) / G : 0;
+        const int mrow = lane & 15, kq = lane >> 4;
+        int c0 = 0;
+        uint32_t w0 = word_chunk<DENSE>(a, rr, t, G, 0, lane);
+        uint32_t w1 = word_chunk<DENSE>(a, rr, t, G, 1, lane);
+        // Head weights of a position for NQ logits from o0 on (indices clamped).
+        // The first ones stay in registers while the position is the same, and
+        // are loaded at the previous tile's end when it changes.
+        const int n_out = NO >= 0 ? NO : a.n_out, ntiles = a.TH * a.TW;
+        constexpr int NQ = NO == 6 ? 6 : 4;
+        floatx4 hw[NO == 0 ? 1 : NQ][R::NB];
+        auto load_hw = [&](int tile, int o0) __attribute__((always_inline)) {
+            if constexpr (NO != 0) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const floatx4 *src = reinterpret_cast<const floatx4 *>(
+                                             a.hw + ((size_t)min(o0 + q, n_out - 1) * ntiles + tile) * kTilePx * R::COUT) + lane;
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) hw[q][nb] = src[nb * 64];
+                }
+            }
+        };
+        int held = -1;                                    // position of the weights in hw, o0 = 0
+        if (mine > 0) load_hw(held = item_of(a, w0, w1, 0, 0).tile, 0);
+        for (int i = 0; i < groups + 2; ++i) {
+            const int k = i - 2;
+            if (k >= 0 && k < mine) {
+                if (k >= 64 * (c0 + 1)) {
+                    w0 = w1;
+                    ++c0;
+                    w1 = word_chunk<DENSE>(a, rr, t, G, c0 + 1, lane);
+                }
+                const floatx4 *p = part_of(k, t) + lane;
+                // Sums and bias, the largest and smallest magnitude of the lane.
+                floatx4 acc[R::NB];
+                float most = 0.f, least = __builtin_inff(), seen = 0.f;
+#pragma unroll
+                for (int nb = 0; nb < R::NB; ++nb) {
+                    acc[nb] = p[nb * 64];
+#pragma unroll
+                    for (int q = 1; q < 4; ++q) acc[nb] += p[(q * R::NB + nb) * 64];
+                    acc[nb] += s_bias[nb * 16 + mrow];
+#pragma unroll
+                    for (int e = 0; e < 4; e += 2) {
+                        most = fmaxf(fmaxf(fabsf(acc[nb][e]), fabsf(acc[nb][e + 1])), most);
+                        least = fminf(fminf(fabsf(acc[nb][e]), fabsf(acc[nb][e + 1])), least);
+                        seen = nonfinite(acc[nb][e + 1], nonfinite(acc[nb][e], seen));
+                    }
+                }
+                const float near = VAR ? 0.f : most * 0x1p-20f;
+                if (__any(seen != 0.f || (!VAR && least <= near))) {
+                    // exact zeros (all products zero) stay
+                    auto doubtful = [&](float z) { return !is_finite(z) || (z != 0.f && fabsf(z) <= near); };
+                    bool any = false;
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) any = any || doubtful(acc[nb][e]);
+                    if (__any(any)) {
+                        floatx4 plain[R::NB];
+                        res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, lane);
+#pragma unroll
+                        for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (doubtful(acc[nb][e])) acc[nb][e] = plain[nb][e] + s_bias[nb * 16 + mrow];
+                    }
+                }
+                // As epilogue(), with the head weights in registers already.
+                const TileRef r = item_of(a, w0, w1, c0, k);
+                const int widx = rr.at(t + k * G);
+                const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
+#pragma unroll
+                for (int nb = 0; nb < R::NB; ++nb) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int keep = col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31);
+                        acc[nb][e] = __int_as_float(max(__float_as_int(acc[nb][e]), 0) & keep);
+                    }
+                }
+                if constexpr (NO != 0) {
+                    for (int o0 = 0; o0 < n_out; o0 += NQ) {
+                        if (o0 > 0) {
+                            load_hw(r.tile, o0);
+                            held = -1;
+                        }
+                        float d[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            d[q] = 0.f;
+                            if (q >= NQ) continue;
+#pragma unroll
+                            for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) d[q] = fmaf(acc[nb][e], hw[q][nb][e], d[q]);
+                        }
+                        const float v = lane_sums8(d, lane);
+                        const int q = (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+                        if ((lane & 7) == 0 && q < NQ && o0 + q < n_out) {
+                            float *hp = VAR ? a.vhpart + (size_t)widx * n_out
+                                            : a.hpart + ((size_t)r.slot * ntiles + r.tile) * n_out;
+                            hp[o0 + q] = v;
+                        }
+                    }
+                    if (k + 1 < mine) {
+                        const int next = item_of(a, w0, w1, c0, k + 1).tile;
+                        if (next != held) load_hw(held = next, 0);
+                    }
+                }
+                if (!VAR || n_out == 0) {
+                    // 16 channels (64 bytes) of four pixels a store, straight
+                    // from the registers.
+                    float *dst = (VAR ? static_cast<float *>(a.vov_out) + (size_t)widx * kTilePx * R::COUT
+                                      : static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride +
+                                            (size_t)r.tile * kTilePx * R::COUT) + kq * R::COUT + mrow;
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) dst[e * 4 * R::COUT + nb * 16] = acc[nb][e];
+                }
+            }
+            lds_barrier();
+        }
+    } else {
+        const int t = wave - 6;
+        const int c4 = lane % 10, hy = lane / 10;         // lanes 60 to 63: none
+        int c0 = 0;
+        uint32_t w0 = word_chunk<DENSE>(a, rr, t, G, 0, lane);
+        uint32_t w1 = word_chunk<DENSE>(a, rr, t, G, 1, lane);
+        auto has = [&](int k) { return t < G && t + k * G < rr.count; };
+        float wr[FUSE ? 9 : 1][4], br[4], pin = 0.f;
+        float *patch = s_patch + t * 64;
         if constexpr (FUSE) {
-            if (k + 1 < n_me) patch_area<CIN, COUT>(halo)[lane] = pin;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) wr[q][e] = a.w1[q * R::CIN + 4 * c4 + e];
+                br[e] = a.b1[4 * c4 + e];
+            }
         }
+        floatx4 pre[6];
+        // Input of group k's tile into registers: the patch, or the halo row.
+        auto fetch = [&](const TileRef &r) __attribute__((always_inline)) {
+            if constexpr (FUSE) {
+                pin = fetch_patch<VAR>(a, r, lane);
+            } else {
+                const int y = r.ty * kTile - 1 + hy;
+#pragma unroll
+                for (int hx = 0; hx < 6; ++hx) {
+                    const int x = r.tx * kTile - 1 + hx;
+                    pre[hx] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    if (hy < 6 && y >= 0 && y < a.H && x >= 0 && x < a.W) {
+                        const float *src =
+                            VAR ? var_src<float>(a, r.slot, y, x, R::CIN)
+                                : static_cast<const float *>(a.in) + (size_t)r.slot * a.in_stride +
+                                      ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * R::CIN;
+                        pre[hx] = *reinterpret_cast<const floatx4 *>(src + 4 * c4);
+                    }
+                }
+            }
+        };
+        if (has(0)) fetch(item_of(a, w0, w1, c0, 0));
+        for (int i = 0; i < groups + 2; ++i) {
+            if (has(i)) {
+                if (i >= 64 * (c0 + 1)) {
+                    w0 = w1;
+                    ++c0;
+                    w1 = word_chunk<DENSE>(a, rr, t, G, c0 + 1, lane);
+                }
+                const TileRef r = item_of(a, w0, w1, c0, i);
+                unsigned char *h = halo_of(i, t) + hy * R::ROW + c4 * 8;
+                floatx4 v[6];
+                if constexpr (FUSE) {
+                    patch[lane] = pin;
+                    wave_sync();
+                    if (has(i + 1)) fetch(item_of(a, w0, w1, c0, i + 1));
+                    float p[3][8];
+#pragma unroll
+                    for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+                        for (int x = 0; x < 8; ++x) p[ky][x] = patch[min(hy + ky, 7) * 8 + x];
+#pragma unroll
+                    for (int hx = 0; hx < 6; ++hx)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float acc = 0.0f;
+#pragma unroll
+                            for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+                                for (int kx = 0; kx < 3; ++kx) acc = fmaf(wr[ky * 3 + kx][e], p[ky][hx + kx], acc);
+                            const float z = acc + br[e];
+                            v[hx][e] = z > 0.0f ? z : 0.0f;
+                        }
+                    // The halo's pixels outside the image (edge tiles only) are 0.
+                    const int y0 = r.ty * kTile - 1, x0 = r.tx * kTile - 1;
+                    if (y0 < 0 || x0 < 0 || y0 + 6 > a.H || x0 + 6 > a.W) {
+#pragma unroll
+                        for (int hx = 0; hx < 6; ++hx)
+                            if (y0 + hy < 0 || y0 + hy >= a.H || x0 + hx < 0 || x0 + hx >= a.W)
+                                v[hx] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+                    wave_sync();                          // patch reads done before the next tile's write
+                } else {
+#pragma unroll
+                    for (int hx = 0; hx < 6; ++hx) v[hx] = pre[hx];
+                    if (has(i + 1)) fetch(item_of(a, w0, w1, c0, i + 1));
+                }
+                float big = 0.f;
+#pragma unroll
+                for (int hx = 0; hx < 6; ++hx)
+#pragma unroll
+                    for (int e = 0; e < 4; e += 2) big = fmaxf(fmaxf(fabsf(v[hx][e]), fabsf(v[hx][e + 1])), big);
+                const bool wide = __any(big >= kWide);
+                if (hy < 6) {
+#pragma unroll
+                    for (int hx = 0; hx < 6; ++hx) {
+                        bf16x4 q[3];
+                        if (wide) split4_wide(v[hx], q[0], q[1], q[2]);
+                        else split4(v[hx], q[0], q[1], q[2]);
+#pragma unroll
+                        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<bf16x4 *>(h + pl * R::PLANE + hx * 80) = q[pl];
+                    }
+                }
+            }
+            lds_barrier();
+        }
+    }
+}
+
+// The split weights in the order the waves hold them, [k-step][16-channel
+// block][plane][lane][8], from the float32 packing.
+__global__ void k_pack_res(const float *w, __bf16 *dst) {
+    using R = Res;
+    const int u = blockIdx.x * blockDim.x + threadIdx.x;  // (k-step, block, lane)
+    if (u >= R::KS * R::NB * 64) return;
+    const int l = u & 63, nb = u / 64 % R::NB, s = u / 64 / R::NB;
+    const int g = 4 * s + (l >> 4), kpos = g / 5;
+    for (int q = 0; q < 2; ++q) {
+        floatx4 v{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < 4; ++e) {
+            const int c = 8 * (g - 5 * kpos) + 4 * q + e, blk = c / 16, steps = blk < 2 ? 4 : 2;
+            const int lw = (c - 16 * blk) / steps * 16 + (l & 15);
+            if (g < R::OCT)
+                v[e] = w[kpos * R::CIN * R::COUT + blk * 16 * R::COUT + (nb * 64 + lw) * steps + c % steps];
+        }
+        bf16x4 p[3];
+        split4(v, p[0], p[1], p[2]);
+        for (int pl = 0; pl < 3; ++pl)
+            *reinterpret_cast<bf16x4 *>(dst + ((size_t)((s * R::NB + nb) * 3 + pl) * 64 + l) * 8 + 4 * q) = p[pl];
     }
 }
 
@@ -1370,35 +1455,26 @@ __global__ __launch_bounds__(256) void k_conv_gen(ConvArgs a) {
 
 // ------------------------------------------------------------------ dispatch
 
-// Static LDS of the fused variant: bias, layer-1 weights and bias.
-template <int CIN, int COUT>
-constexpr bool fused_fits() {
-    return Resident<CIN, COUT, 8>::lds_bytes + (COUT + 10 * CIN) * sizeof(float) <= 160 * 1024;
-}
-
-template <int CIN, int COUT, bool DENSE, bool FUSE, int NO, bool VAR>
+template <bool DENSE, bool FUSE, int NO, bool VAR>
 hipError_t run_resident_no(const ConvArgs &a, int cus, hipStream_t s) {
-    constexpr size_t lds = Resident<CIN, COUT, 8>::lds_bytes;
-    auto kern = k_conv_mfma_res<CIN, COUT, 8, DENSE, FUSE, NO, VAR>;
-    static hipError_t attr = set_lds(kern, lds);
+    auto kern = k_conv_mfma_res<DENSE, FUSE, NO, VAR>;
+    static hipError_t attr = set_lds(kern, Res::lds_bytes);
     if (attr != hipSuccess) return attr;
-    const int grid = persistent_grid(cus, (a.max_tiles + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, a.max_tiles)), dim3(512), Res::lds_bytes, s, a);
     return hipGetLastError();
 }
 
 // Logit count as a template argument where it is a common one.
-template <int CIN, int COUT, bool DENSE, bool FUSE, bool VAR>
+template <bool DENSE, bool FUSE, bool VAR>
 hipError_t run_resident(const ConvArgs &a, int cus, hipStream_t s) {
-    if (a.n_out == 0) return run_resident_no<CIN, COUT, DENSE, FUSE, 0, VAR>(a, cus, s);
-    if (a.n_out == 6) return run_resident_no<CIN, COUT, DENSE, FUSE, 6, VAR>(a, cus, s);
-    return run_resident_no<CIN, COUT, DENSE, FUSE, -1, VAR>(a, cus, s);
+    if (a.n_out == 0) return run_resident_no<DENSE, FUSE, 0, VAR>(a, cus, s);
+    if (a.n_out == 6) return run_resident_no<DENSE, FUSE, 6, VAR>(a, cus, s);
+    return run_resident_no<DENSE, FUSE, -1, VAR>(a, cus, s);
 }
 
-template <int CIN, int COUT, bool DENSE, bool VAR>
+template <bool DENSE, bool VAR>
 hipError_t run_mfma(const ConvArgs &a, int cus, hipStream_t s) {
-    if (a.fuse_first) return run_resident<CIN, COUT, DENSE, true, VAR>(a, cus, s);
-    return run_resident<CIN, COUT, DENSE, false, VAR>(a, cus, s);
+    return a.fuse_first ? run_resident<DENSE, true, VAR>(a, cus, s) : run_resident<DENSE, false, VAR>(a, cus, s);
 }
 
 template <int CIN, int COUT, bool DENSE>
@@ -1427,8 +1503,6 @@ hipError_t run_first(const ConvArgs &a, int cus, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Layers whose weights stay in LDS; larger ones are in rn_conv_split.hip.
-#define RN_MFMA_SHAPES(X) X(40, 80)
 #define RN_STAGED_SHAPES(X) X(64, 128) X(128, 128)
 // General layers: (k, stride, cin, cout); first layers read the input frames.
 #define RN_GEN_FIRST_SHAPES(X) X(8, 4, 4, 32) X(8, 4, 1, 32) X(5, 1, 1, 32) X(7, 2, 1, 32) X(5, 2, 4, 32)
@@ -1516,20 +1590,20 @@ void pack_conv_gen(const float *oihw, int k, int cin, int cout, float *dst) {
                 }
 }
 
+static bool is_resident(int cin, int cout) { return cin == Res::CIN && cout == Res::COUT; }
+
 bool conv_mfma_supported(int cin, int cout, rn_dtype dt) {
-    if (dt != RN_F32) return false;
-#define X(ci, co) if (cin == ci && cout == co) return true;
-    RN_MFMA_SHAPES(X)
-#undef X
-    return conv_split_supported(cin, cout);
+    return dt == RN_F32 && (is_resident(cin, cout) || conv_split_supported(cin, cout));
 }
 
-bool conv_fused_first_supported(int c1, int c2, rn_dtype dt) {
-    if (dt != RN_F32) return false;
-#define X(ci, co) if (c1 == ci && c2 == co) return fused_fits<ci, co>();
-    RN_MFMA_SHAPES(X)
-#undef X
-    return false;
+bool conv_fused_first_supported(int c1, int c2, rn_dtype dt) { return dt == RN_F32 && is_resident(c1, c2); }
+
+size_t conv_res_bytes(int cin, int cout) { return is_resident(cin, cout) ? Res::w_bytes : 0; }
+
+hipError_t launch_pack_res(const float *w, void *dst, hipStream_t s) {
+    const int units = Res::KS * Res::NB * 64;
+    hipLaunchKernelGGL(k_pack_res, dim3((units + 255) / 256), dim3(256), 0, s, w, static_cast<__bf16 *>(dst));
+    return hipGetLastError();
 }
 
 bool conv_first_supported(int cin, int cout, rn_dtype dt) {
@@ -1542,17 +1616,10 @@ bool conv_first_supported(int cin, int cout, rn_dtype dt) {
 
 // cus: compute units of the device; the persistent grid is at most one block
 // (resident MFMA kernel) or eight blocks (first layer) per CU.
-hipError_t launch_conv_mfma(const ConvArgs &a, rn_dtype dt, int cus, hipStream_t s, bool var) {
-    (void)dt;
+hipError_t launch_conv_mfma(const ConvArgs &a, int cus, hipStream_t s, bool var) {
     const bool dense = a.wl == nullptr;
-    if (var && dense) return hipErrorInvalidValue;
-#define X(ci, co)                                                                          \
-    if (a.cin == ci && a.cout == co)                                                       \
-        return var ? run_mfma<ci, co, false, true>(a, cus, s)                              \
-                   : dense ? run_mfma<ci, co, true, false>(a, cus, s) : run_mfma<ci, co, false, false>(a, cus, s);
-    RN_MFMA_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
+    if ((var && dense) || !is_resident(a.cin, a.cout)) return hipErrorInvalidValue;
+    return var ? run_mfma<false, true>(a, cus, s) : dense ? run_mfma<true, false>(a, cus, s) : run_mfma<false, false>(a, cus, s);
 }
 
 hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s) {

@@ -195,28 +195,31 @@ __device__ inline XcdRange xcd_range(int cnt, int units) {
     return r;
 }
 
-// The same segments for blocks of 8 waves, two per SIMD (waves w and w + 4 of
-// a block share one), returning wave `wave`'s own first item.  A round of the
-// segment holds 8 B items (B blocks on the XCD): its first 4 B go to waves 0-3,
-// four consecutive items per block (neighbouring tiles stay on one CU), the
-// next 4 B to waves 4-7.  The partial last round then gives every SIMD of the
-// XCD one extra item before any SIMD gets a second, where a block-major split
-// would give both waves of a SIMD one.  `block_first` is the block's smallest
-// item (wave 0's), for a block-uniform early exit.
-struct XcdRangeW {
-    int first, block_first, end, stride;
+// The same XCD segments dealt to their blocks in runs of R consecutive items
+// (up to 8, about eight runs a block): the items of a list are ordered by
+// position, so a block meets the same position's head weights several times in
+// a row, while no block gets all the streams of one position.
+struct RunRange {
+    int seg, k, blocks_x, shift, count;               // R = 1 << shift; items of this block
+
+    __device__ inline int at(int n) const {           // its n-th item, n in [0, count)
+        return seg + ((((n >> shift) * blocks_x + k) << shift) | (n & ((1 << shift) - 1)));
+    }
 };
 
-__device__ inline XcdRangeW xcd_range_simd2(int cnt, int wave) {
+__device__ inline RunRange run_range(int cnt) {
     constexpr int kXcd = 8;
-    const int x = blockIdx.x % kXcd, k = blockIdx.x / kXcd;
-    const int blocks_x = ((int)gridDim.x - x + kXcd - 1) / kXcd;
-    const int seg = (int)((long long)cnt * x / kXcd);
-    XcdRangeW r;
-    r.block_first = seg + 4 * k;
-    r.first = r.block_first + (wave & 3) + (wave >> 2) * 4 * blocks_x;
-    r.end = (int)((long long)cnt * (x + 1) / kXcd);
-    r.stride = blocks_x * 8;
+    const int x = blockIdx.x % kXcd;
+    RunRange r;
+    r.k = blockIdx.x / kXcd;
+    r.blocks_x = ((int)gridDim.x - x + kXcd - 1) / kXcd;
+    r.seg = (int)((long long)cnt * x / kXcd);
+    const int len = (int)((long long)cnt * (x + 1) / kXcd) - r.seg;
+    r.shift = 0;
+    while (r.shift < 3 && len >= (16 << r.shift) * r.blocks_x) ++r.shift;
+    const int runs = (len + (1 << r.shift) - 1) >> r.shift;
+    r.count = r.k < runs ? ((runs - r.k + r.blocks_x - 1) / r.blocks_x) << r.shift : 0;
+    if (runs > 0 && (runs - 1) % r.blocks_x == r.k) r.count -= (runs << r.shift) - len;
     return r;
 }
 

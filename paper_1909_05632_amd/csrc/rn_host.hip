@@ -57,7 +57,7 @@ struct Plan {
     // conv layers 2..L).
     const char *train_why = nullptr;        // NULL: training supported
     size_t o_wt[RN_MAX_CONV] = {0};
-    // Layers on launch_conv_split: the bf16 planes of their weights.
+    // The bf16 planes of float32 layers' weights; split: a layer of launch_conv_split.
     bool split[RN_MAX_CONV] = {false};
     size_t o_ws[RN_MAX_CONV] = {0};
     bool plain = false;                     // RN_OPT_SEPARATE_FIRST: steps and full passes sum in plain float32
@@ -216,7 +216,8 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
         p->o_w[l] = take(p->w_bytes[l]);
         p->o_b[l] = take((size_t)p->C[l + 1] * 4);
         p->split[l] = l > 0 && !p->gen[l] && p->dt == RN_F32 && conv_split_supported(p->C[l], p->C[l + 1]);
-        p->o_ws[l] = take(p->split[l] ? conv_split_bytes(p->C[l], p->C[l + 1]) : 0);
+        p->o_ws[l] = take(p->split[l] ? conv_split_bytes(p->C[l], p->C[l + 1])
+                          : l > 0 && !p->gen[l] && p->dt == RN_F32 ? conv_res_bytes(p->C[l], p->C[l + 1]) : 0);
     }
     if (p->dt != RN_F32) p->train_why = "training needs a float32 net";
     else if (p->any_gen) p->train_why = "training needs 3x3 stride-1 pad-1 layers";
@@ -440,7 +441,7 @@ MaskGeom make_geom(reuse_net *net) {
 // Layers 2..L other than the general ones.
 hipError_t launch_conv_later(const Plan &p, const ConvArgs &cv, int l, int cus, hipStream_t s, bool var) {
     if (p.dt == RN_BF16) return launch_conv_mfma_bf16(cv, cus, s, var);
-    if (!p.split[l - 1]) return launch_conv_mfma(cv, p.dt, cus, s, var);
+    if (!p.split[l - 1]) return launch_conv_mfma(cv, cus, s, var);
     return p.plain && !var ? launch_conv_staged(cv, cus, s) : launch_conv_split(cv, cus, s, var);
 }
 
@@ -450,6 +451,7 @@ hipError_t split_weights(reuse_net *net, hipStream_t s) {
     hipError_t e = hipSuccess;
     for (int l = 1; l < p.L && e == hipSuccess; ++l)
         if (p.split[l]) e = launch_pack_split(net->at<float>(p.o_w[l]), p.C[l], p.C[l + 1], net->at<void>(p.o_ws[l]), s);
+        else if (!p.gen[l] && p.dt == RN_F32) e = launch_pack_res(net->at<float>(p.o_w[l]), net->at<void>(p.o_ws[l]), s);
     return e;
 }
 
@@ -471,7 +473,7 @@ hipError_t run_layers(reuse_net *net, int n, const int32_t *ids, bool identity, 
         cv.in = l == 1 ? static_cast<const void *>(net->at<float>(p.o_xin)) : net->at<void>(p.o_act[l - 1]);
         cv.out = net->at<void>(p.o_act[l]);
         cv.w = net->at<void>(p.o_w[l - 1]);
-        if (p.split[l - 1]) cv.w_split = net->at<void>(p.o_ws[l - 1]);
+        cv.w_split = net->at<void>(p.o_ws[l - 1]);
         cv.bias = net->at<float>(p.o_b[l - 1]);
         cv.ring_head = net->at<int32_t>(p.o_ring);
         cv.H = p.Hl[l];
@@ -703,7 +705,7 @@ rn_status run_variants(reuse_net *net, int32_t base, int32_t n, const void *fram
         cv.cnt = va.cnt + l;
         cv.in = l == 1 ? static_cast<const void *>(net->at<float>(p.o_xin)) : net->at<void>(p.o_act[l - 1]);
         cv.w = net->at<void>(p.o_w[l - 1]);
-        if (p.split[l - 1]) cv.w_split = net->at<void>(p.o_ws[l - 1]);
+        cv.w_split = net->at<void>(p.o_ws[l - 1]);
         cv.bias = net->at<float>(p.o_b[l - 1]);
         cv.H = p.H;
         cv.W = p.W;

@@ -102,7 +102,7 @@ struct ConvArgs {
     const void *in;               // previous layer cache (layer 1: float32 input ring)
     void *out;                    // this layer's cache [S][TH][TW][16][cout]
     const void *w;                // packed weights
-    const void *w_split;          // their three bf16 planes (layers of launch_conv_split)
+    const void *w_split;          // their three bf16 planes (float32 layers 2..L that are not general)
     const float *bias;            // [cout]
     const int32_t *ring_head;     // stack=4 only
     int H, W, TH, TW;             // this layer's output grid and its tile grid
@@ -209,7 +209,9 @@ hipError_t launch_var_lists(const VarMaskArgs &a, hipStream_t s);
 // Conv launchers: list mode (a.wl set), dense mode (a.wl NULL), or variant
 // mode (var = true, a.wl set).
 hipError_t launch_conv_first(const ConvArgs &a, rn_dtype dt, int grid, hipStream_t s, bool var = false);
-hipError_t launch_conv_mfma(const ConvArgs &a, rn_dtype dt, int grid, hipStream_t s, bool var = false);
+hipError_t launch_conv_mfma(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
+size_t conv_res_bytes(int cin, int cout);   // its split weights (0: another kernel's layer)
+hipError_t launch_pack_res(const float *w, void *dst, hipStream_t s);
 bool conv_mfma_supported(int cin, int cout, rn_dtype dt);
 // Float32 layers on the bf16 matrix cores with split operands: the split
 // weights are packed on the device from the float32 packing (pack_conv_mfma).

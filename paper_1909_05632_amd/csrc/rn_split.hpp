@@ -23,13 +23,53 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// bf16 pairs rounded to nearest even, and the float32 values of a pair (a shift
+// and a mask; converting element by element back would round each again).
+__device__ inline uint32_t round_pair(float x, float y) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{x, y}, bf16x2));
+}
+__device__ inline float pair_lo(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ inline float pair_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
+
 // The three bf16 planes of four values.
 __device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
-    h = __builtin_convertvector(v, bf16x4);
-    const floatx4 r = v - __builtin_convertvector(h, floatx4);
-    m = __builtin_convertvector(r, bf16x4);
-    l = __builtin_convertvector(r - __builtin_convertvector(m, floatx4), bf16x4);
+    uint32_t p[3][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        float x = v[2 * i], y = v[2 * i + 1];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+            p[pl][i] = round_pair(x, y);
+            x -= pair_lo(p[pl][i]);
+            y -= pair_hi(p[pl][i]);
+        }
+    }
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    h = __builtin_bit_cast(bf16x4, u32x2{p[0][0], p[0][1]});
+    m = __builtin_bit_cast(bf16x4, u32x2{p[1][0], p[1][1]});
+    l = __builtin_bit_cast(bf16x4, u32x2{p[2][0], p[2][1]});
 }
+
+// The same where some value is infinite or rounds up to infinity in bf16: the
+// planes of a finite value then still add up to it (leading plane clamped), an
+// infinity is its leading plane alone.
+__device__ inline void split4_wide(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
+    constexpr float kMost = 0x1.fep127f;              // largest finite bf16
+    floatx4 lead, rest;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool inf = fabsf(v[i]) == __builtin_inff();
+        lead[i] = inf || __builtin_isnan(v[i]) ? v[i] : fminf(fmaxf(v[i], -kMost), kMost);
+    }
+    h = __builtin_convertvector(lead, bf16x4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rest[i] = fabsf(v[i]) <= 0x1.fffffep127f ? v[i] - (float)h[i] : 0.f;
+    m = __builtin_convertvector(rest, bf16x4);
+    l = __builtin_convertvector(rest - __builtin_convertvector(m, floatx4), bf16x4);
+}
+constexpr float kWide = 0x1.ffp127f;                  // the smallest float32 that rounds to infinity
 
 // 0 while every value seen was finite, NaN after one that was not.
 __device__ inline float nonfinite(float v, float seen) { return fmaf(v, 0.0f, seen); }

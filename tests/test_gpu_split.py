@@ -50,27 +50,28 @@ def _weights(wl, rng, scale):
     cw = [np.array(v) for v in w[0]]
     cw[0][0] = cw[0][1] = 0.0
     cw[0][0, 0, 1, 1], cw[0][1, 0, 1, 1] = 1.0, -1.0
-    for l in (1, 2):
+    for l in range(1, len(cw)):
         cw[l] = (rng.normal(0.0, scale, cw[l].shape)).astype(np.float32)
     return (cw, *w[1:])
 
 
+@pytest.mark.parametrize("convs", [(64, 128, 128), (40, 80)])
 @pytest.mark.parametrize("value", [3.4e38, -3.4e38, np.inf, -np.inf])
-def test_values_beyond_the_split(torch, value):
+def test_values_beyond_the_split(torch, value, convs):
     # One pixel of the frame holds `value`.  Plain float32 arithmetic (torch on
     # the CPU, sums in another order) gives the expected result wherever it is
     # not NaN; where it is, the GPU's ReLU may give NaN or 0 (the sign of a NaN).
     # 3.4e38 is finite in float32 and infinite in bf16; the layer weights keep
     # its products and their sums finite.  Tolerance: 1152 float32 roundings.
     import torch.nn.functional as F
-    wl = synth.Workload(cid=202, streams=2, frames=1, h=20, w=24, convs=(64, 128, 128), n_out=18)
+    wl = synth.Workload(cid=202, streams=2, frames=1, h=20, w=24, convs=convs, n_out=18)
     weights = _weights(wl, np.random.default_rng(5), 1e-4)
     x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
     x[0, 0, 9, 10] = value
     net = make_net(wl, 2, weights)
     net.full(torch.from_numpy(x).cuda())
     cur = torch.from_numpy(x)
-    for l in range(1, 4):
+    for l in range(1, len(convs) + 1):
         z = F.conv2d(cur, torch.from_numpy(weights[0][l - 1]), torch.from_numpy(weights[1][l - 1]), padding=1)
         size = F.conv2d(cur.abs(), torch.from_numpy(np.abs(weights[0][l - 1])), torch.from_numpy(np.abs(weights[1][l - 1])),
                         padding=1).numpy()               # sum of the terms' magnitudes
@@ -107,3 +108,46 @@ def test_head_groups(torch, act, n_out):
         assert np.abs(alone - ref[0]).max() <= tol, i
     net.close()
     one.close()
+
+
+def _chain(x, w, b):
+    """Pre-activations of a 40 -> 80 layer for x [40][H][W], summed one float32 fma at a time in the float32
+    kernel's order (position, 16-channel block, k-step, quarter): float64 holds a product exactly, and its
+    sum with a float32 before rounding to within 2^-53 of itself."""
+    H, W = x.shape[1:]
+    xp = np.zeros((40, H + 2, W + 2))
+    xp[:, 1:-1, 1:-1] = x
+    acc = np.zeros((80, H, W), np.float32)
+    for kpos in range(9):
+        for blk, steps in ((0, 4), (1, 4), (2, 2)):
+            for j in range(steps):
+                for kq in range(4):
+                    c = 16 * blk + steps * kq + j
+                    win = xp[c, kpos // 3:kpos // 3 + H, kpos % 3:kpos % 3 + W]
+                    acc = (w[:, c, kpos // 3, kpos % 3].astype(np.float64)[:, None, None] * win + acc).astype(np.float32)
+    return acc + b[:, None, None]
+
+
+@pytest.mark.parametrize("fuse", [True, False])
+def test_decisions_near_zero_are_float32s(torch, fuse):
+    # Results within 2^-20 of 0 relative to the largest of their lane (channels c,
+    # c + 16, .. of a tile column) come from the float32 product: up to half of
+    # that they are the chain's, bit for bit; the others only to rounding.
+    from paper_1909_05632_amd import ReuseNet
+    wl = synth.Workload(cid=205, streams=4, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(4), frames=1))[0][:, None]
+    net = ReuseNet(1, wl.h, wl.w, wl.convs, 6, 4, weights, fuse_first=fuse)
+    net.full(torch.from_numpy(x).cuda())
+    seen = 0
+    for i in range(4):
+        z = _chain(net.activation(i, 1), weights[0][1], weights[1][1])
+        m = np.abs(np.pad(z, ((0, 0), (0, 3), (0, 0)))).reshape(5, 16, 26, 4, 80).max((0, 3))   # rows past the image: less
+        m = np.broadcast_to(m[None, :, :, None], (5, 16, 26, 4, 80)).reshape(80, 104, 80)[:, :101]
+        near = np.abs(z) <= m * 2.0 ** -21
+        got, want = net.activation(i, 2), np.maximum(z, np.float32(0))
+        assert np.array_equal(got[near], want[near])
+        assert np.abs(got - want).max() <= 360 * 2.0 ** -24 * np.abs(z).max()
+        seen += int(near.sum())
+    assert seen > 0
+    net.close()

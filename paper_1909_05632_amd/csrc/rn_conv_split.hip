@@ -1,14 +1,18 @@
-// Float32 3x3 layers whose weights do not fit in LDS (64->128, 128->128) on the
-// bf16 matrix cores with operands split three ways (rn_split.hpp).
+// Float32 3x3 layers of many channels (64->128, 128->128), and the input
+// gradients of training, on the bf16 matrix cores with operands split three
+// ways (rn_split.hpp).
 //
 // Bound: matrix issue.  A tile is 2 * 16 * COUT * 9 CIN flops six times over on
 // v_mfma_f32_32x32x16_bf16 (~2.06 PFLOP/s from one wave per SIMD in a bare loop,
 // 344 TFLOP/s of float32 work; the float32 instruction gives 150).
 //
-// A block of four waves computes a group of T tiles x all COUT channels, two
-// waves along the tiles and two along the channels; a wave holds T / 4 tile
-// pairs (32 pixels) x COUT / 64 blocks of 32 channels, twice (large and small
-// sums): 256 accumulator registers at T = 16, so one block per CU.  The product
+// A block of four waves computes a group of T tiles x all COUT channels, a wave
+// 32 channels of all tiles (of half of them where COUT has two such blocks): T /
+// 2 tile pairs (32 pixels), twice (large and small sums), 256 accumulator
+// registers at T = 16, so one block per CU.  (Two waves along the channels, two
+// along the tiles: the weights of a stage are read twice, 3824 against 3579 us
+// at T = 8, layer 3 of 1024 210x160 streams; T = 16 then 3370, where the
+// float32 instructions took 6233.)  The product
 // is transposed (rows = channels, columns = pixels): a lane ends with four
 // neighbouring channels of one pixel and stores 16 bytes.
 // K runs over chunks of 16 input channels and, within one, the nine kernel
@@ -23,8 +27,8 @@
 //   16 pixels of a 16-lane read then lie in 16 distinct bank groups at every
 //   kernel position.
 //   Weights: packed in fragment order (pack below) and read straight into
-//   registers a stage ahead; the two waves that share channels read the same
-//   lines.  Larger groups read fewer weight bytes per tile: 12 KB a stage.
+//   registers two stages ahead (one stage: T = 4 alone on its CU 30 instead of
+//   24 us).  Larger groups read fewer weight bytes per tile: 12 KB a stage.
 // The sums over K of an output run in one order whatever T is, so a tile's
 // outputs do not depend on the group size a launch picks, and a dense pass, a
 // reuse step and a variant give the same bits.
@@ -38,11 +42,19 @@ using namespace dev;
 // Source of halo values that lie outside the image or past the work list.
 __device__ __align__(16) float g_zero_halo[128];
 
+// What a launch computes: a layer's outputs for a work list, for every tile, or
+// for variants; or the gradient at a layer's input (INPUT_GRAD): a convolution
+// of dJ/dz (CIN channels) with the transposed, flipped weights, kept where the
+// layer's input (COUT channels, the layer before's activations) is above 0.
+enum { LIST = 0, DENSE_PASS = 1, VARIANTS = 2, INPUT_GRAD = 3 };
+
 template <int CIN, int COUT, int T>
 struct SplitConv {
     static constexpr int NCH = CIN / 16;             // chunks of 16 channels
-    static constexpr int NN = COUT / 32;             // blocks of 32 channels
-    static constexpr int MB = T / 2;                 // tile pairs, each wave all of them
+    static constexpr int C16 = (COUT + 15) / 16 * 16;   // columns of the float32 packing
+    static constexpr int NN = (COUT + 31) / 32;      // blocks of 32 channels, one per wave
+    static constexpr int WM = 4 / NN;                // waves along the tiles
+    static constexpr int MB = T / 2 / WM;            // tile pairs per wave
     static constexpr int PLANE = 72 * 16;            // bytes of one plane of one tile's chunk
     static constexpr int TILE = 3 * PLANE;
     static constexpr int BUF = T * TILE;             // bytes of a chunk buffer
@@ -55,7 +67,7 @@ struct SplitConv {
     static constexpr int UPT = JY * JX;
     static constexpr size_t WSTAGE = (size_t)3 * NN * 512;   // bf16 weights per stage
     static constexpr size_t lds_bytes = 2 * (size_t)BUF + COUT * sizeof(float);
-    static_assert(CIN % 32 == 0 && COUT == 128 && T % 4 == 0, "whole chunk pairs, a block of 32 channels per wave");
+    static_assert(CIN % 16 == 0 && NCH >= 3 && COUT % 4 == 0 && NN * WM == 4 && T % 4 == 0, "chunks in flight, waves");
     static_assert(UPT <= 9 && RY * RX * 4 <= TPT, "at most one unit per stage, all of them covered");
     static_assert(CIN <= 128, "zero source");
 };
@@ -87,8 +99,9 @@ __device__ inline const float *halo_src(const ConvArgs &a, const TileRef &r, int
     return in ? src + ((y & 3) * 4 + (x & 3)) * CIN : g_zero_halo;
 }
 
-// One output before bias in plain float32, for results the split cannot carry.
-template <int CIN, int COUT, bool VAR>
+// One output before bias in plain float32, for results the split cannot carry
+// (C16: columns of the float32 packing).
+template <int CIN, int C16, bool VAR>
 __device__ float plain_output(const ConvArgs &a, const TileRef &r, int p, int n) {
     float acc = 0.f;
     const float *w = static_cast<const float *>(a.w);
@@ -96,7 +109,7 @@ __device__ float plain_output(const ConvArgs &a, const TileRef &r, int p, int n)
         for (int kpos = 0; kpos < 9; ++kpos) {
             const int y = r.ty * kTile + (p >> 2) + kpos / 3 - 1, x = r.tx * kTile + (p & 3) + kpos % 3 - 1;
             const float *src = halo_src<CIN, VAR>(a, r, y, x, true);
-            for (int ci = ci0; ci < ci0 + 16; ++ci) acc = fmaf(src[ci], w[f32_weight(kpos, ci, n, CIN, COUT)], acc);
+            for (int ci = ci0; ci < ci0 + 16; ++ci) acc = fmaf(src[ci], w[f32_weight(kpos, ci, n, CIN, C16)], acc);
         }
     return acc;
 }
@@ -108,15 +121,18 @@ __device__ inline float *out_tile(const ConvArgs &a, const TileRef &r, int t) {
                : static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride + (size_t)r.tile * kTilePx * COUT;
 }
 
-template <int CIN, int COUT, bool DENSE, bool VAR, int T>
+template <int CIN, int COUT, int MODE, int T>
 __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     using C = SplitConv<CIN, COUT, T>;
+    constexpr bool DENSE = MODE == DENSE_PASS || MODE == INPUT_GRAD, VAR = MODE == VARIANTS, GRAD = MODE == INPUT_GRAD;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % C::NN, wm = wave / C::NN;       // the wave's channel block and share of the tiles
     const XcdRange xr = xcd_range(cnt, T);
     if (xr.first >= xr.end) return;                       // uniform per block
     float *s_bias = reinterpret_cast<float *>(lds + 2 * C::BUF);
-    for (int j = tid; j < COUT; j += 256) s_bias[j] = a.bias[j];
+    if constexpr (!GRAD)
+        for (int j = tid; j < COUT; j += 256) s_bias[j] = a.bias[j];
 
     // Item word of tile lane % T of a group (past the end: the last item).
     auto items = [&](int g) __attribute__((always_inline)) {
@@ -152,7 +168,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
         }
     };
     // Weight fragments of a stage: [plane][channel block][lane] 16 bytes.
-    const bf16x8 *wg = reinterpret_cast<const bf16x8 *>(a.w_split) + wave * 64 + lane;
+    const bf16x8 *wg = reinterpret_cast<const bf16x8 *>(a.w_split) + wn * 64 + lane;
     auto load_w = [&](bf16x8 (&w)[3], int s) __attribute__((always_inline)) {
         const bf16x8 *p = wg + (size_t)s * (C::WSTAGE / 8);
 #pragma unroll
@@ -160,7 +176,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     };
     // Pixel fragments of tile pair m at kernel position kpos.
     const int pix = lane & 15;
-    const unsigned char *xa = lds + ((lane >> 4) & 1) * C::TILE +
+    const unsigned char *xa = lds + (2 * wm * C::MB + ((lane >> 4) & 1)) * C::TILE +
                               ((pix >> 2) * 12 + (lane >> 5) * 6 + (pix & 3)) * 16;
     auto load_x = [&](bf16x8 (&x)[3], int buf, int m, int kpos) __attribute__((always_inline)) {
         const unsigned char *p = xa + buf * C::BUF + 2 * m * C::TILE + (kpos / 3 * 12 + kpos % 3) * 16;
@@ -183,6 +199,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     }
     lds_barrier();
 
+    int buf = 0;                                          // buffer of the current chunk
     for (int g = xr.first; g < xr.end; g += xr.stride) {   // uniform per block
         floatx16 hi[C::MB], lo[C::MB];
 #pragma unroll
@@ -192,7 +209,6 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
         it_next = items(min(g + xr.stride, xr.end - 1));
 #pragma unroll 1
         for (int c = 0; c < C::NCH; ++c) {
-            const int buf = c & 1;
             // From here on the loads are the next group's (chunk c + 2).
             if (c == C::NCH - 2) sources(g + xr.stride, it_next);
             const int cl = c + 2 < C::NCH ? c + 2 : c + 2 - C::NCH;
@@ -210,7 +226,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
                     if (m == 0) load_w(w[(kp + 2) % 3], s >= 9 * C::NCH ? s - 9 * C::NCH : s);
                     if (m + 1 < C::MB) load_x(xn, buf, m + 1, kp);
                     else if (kp < 8) load_x(xn, buf, 0, kp + 1);
-                    if (m == 1 && kp < C::UPT) {
+                    if (m == (C::MB > 1 ? 1 : 0) && kp < C::UPT) {
                         store_unit(kp, buf ^ 1);
                         load_unit(kp, cl);
                     }
@@ -235,6 +251,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
                 }
             }
             lds_barrier();                                // chunk c read, chunk c + 1 written by every wave
+            buf ^= 1;
         }
         // Epilogue: bias, ReLU and the zero outside the image on the bit
         // patterns (a float above zero has a positive int pattern), 16 bytes
@@ -248,16 +265,23 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
             // Each pair's sums leave the accumulator registers on their own
             // (all at once they would push everything else to scratch).
             asm volatile("" : "+a"(hi[m]), "+a"(lo[m]));
-            const int t = 2 * m + ((lane >> 4) & 1);
+            const int t = 2 * (wm * C::MB + m) + ((lane >> 4) & 1);
             const TileRef r = item_ref(a, (uint32_t)__shfl((int)it, t));
             const int keep = ~((a.W - 1 - (r.tx * kTile + (pix & 3))) >> 31) & ~((a.H - 1 - (r.ty * kTile + (pix >> 2))) >> 31);
-            const int ch = wave * 32 + 4 * (lane >> 5);
+            const int ch = wn * 32 + 4 * (lane >> 5);
             float *dst = out_tile<COUT, VAR>(a, r, min(g + t, xr.end - 1)) + pix * COUT + ch;
+            floatx4 mask[4];
+            if constexpr (GRAD) {
+                const float *src = a.mask + (size_t)a.mask_ids[r.slot] * a.mask_stride + ((size_t)r.tile * kTilePx + pix) * COUT;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) mask[q] = *reinterpret_cast<const floatx4 *>(src + min(ch + 8 * q, COUT - 4));
+            }
             float seen = 0.f;
             floatx16 v;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const floatx4 b = *reinterpret_cast<const floatx4 *>(s_bias + ch + 8 * q);
+                floatx4 b{0.f, 0.f, 0.f, 0.f};
+                if constexpr (!GRAD) b = *reinterpret_cast<const floatx4 *>(s_bias + ch + 8 * q);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[4 * q + e] = (hi[m][4 * q + e] + lo[m][4 * q + e]) + b[e];
@@ -273,24 +297,27 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
             if (g + t < xr.end && (!VAR || a.vov_out != nullptr)) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
+                    if (ch + 8 * q >= COUT) continue;
                     floatx4 o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = __int_as_float(max(__float_as_int(v[4 * q + e]), 0) & keep);
+                    for (int e = 0; e < 4; ++e)
+                        o[e] = GRAD ? (mask[q][e] > 0.f ? v[4 * q + e] : 0.f)
+                                    : __int_as_float(max(__float_as_int(v[4 * q + e]), 0) & keep);
                     *reinterpret_cast<floatx4 *>(dst + 8 * q) = o;
                 }
             }
         }
         if (bad) {                                        // uniform per wave
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            for (int k = 0; k < 2 * T; ++k) {             // 8 pixels x 8 lanes x 4 channels a pass
+            for (int k = 4 * wm * C::MB; k < 4 * (wm + 1) * C::MB; ++k) {   // 8 pixels x 8 lanes x 4 channels a pass
                 const int t = k >> 1, p = (k & 1) * 8 + (lane >> 3);
                 if (g + t >= xr.end || (VAR && a.vov_out == nullptr)) continue;
                 const TileRef r = item_ref(a, (uint32_t)__shfl((int)it, t));
                 float *dst = out_tile<COUT, VAR>(a, r, g + t) + p * COUT;
-                for (int n = wave * 32 + (lane & 7); n < wave * 32 + 32; n += 8)
+                for (int n = wn * 32 + (lane & 7); n < min(wn * 32 + 32, COUT); n += 8)
                     if (__builtin_isnan(dst[n])) {
-                        const float f = plain_output<CIN, COUT, VAR>(a, r, p, n) + s_bias[n];
-                        dst[n] = __int_as_float(max(__float_as_int(f), 0));
+                        const float f = plain_output<CIN, C::C16, VAR>(a, r, p, n);
+                        dst[n] = GRAD ? f : __int_as_float(max(__float_as_int(f + s_bias[n]), 0));
                     }
             }
         }
@@ -298,40 +325,44 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     }
 }
 
-template <int CIN, int COUT, bool DENSE, bool VAR>
+// The group size by the rounds a launch takes: a group of 16, 8 or 4 tiles of a
+// 128 -> 128 layer takes 69, 41 or 26 us with every CU busy (an MI355X; the
+// other layers in proportion).
+template <int CIN, int COUT, int MODE>
 __global__ __launch_bounds__(256, 1) void k_conv_mfma_split(ConvArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int cnt = work_count<DENSE>(a);
+    const int cnt = work_count<MODE == DENSE_PASS || MODE == INPUT_GRAD>(a);
     auto rounds = [&](int T) { return (cnt + T * (int)gridDim.x - 1) / (T * (int)gridDim.x); };
     const int c16 = rounds(16) * 69, c8 = rounds(8) * 41, c4 = rounds(4) * 26;
-    if (c16 <= c8 && c16 <= c4) split_path<CIN, COUT, DENSE, VAR, 16>(a, cnt, lds);
-    else if (c8 <= c4) split_path<CIN, COUT, DENSE, VAR, 8>(a, cnt, lds);
-    else split_path<CIN, COUT, DENSE, VAR, 4>(a, cnt, lds);
+    if (c16 <= c8 && c16 <= c4) split_path<CIN, COUT, MODE, 16>(a, cnt, lds);
+    else if (c8 <= c4) split_path<CIN, COUT, MODE, 8>(a, cnt, lds);
+    else split_path<CIN, COUT, MODE, 4>(a, cnt, lds);
 }
 
 // Split weights in fragment order, [chunk][kernel position][plane][32-channel
 // block][lane][8]: element i of lane l is input channel 16 chunk + 8 (l / 32) + i
-// of output channel 32 block + l % 32, from the float32 packing.
-__global__ void k_pack_split(const float *w, int cin, int cout, __bf16 *dst) {
-    const int NN = cout / 32;
+// of output channel 32 block + l % 32, from the float32 packing of c16 columns
+// (zero past them).
+__global__ void k_pack_split(const float *w, int cin, int c16, int NN, __bf16 *dst) {
     const size_t u = (size_t)blockIdx.x * blockDim.x + threadIdx.x;      // (chunk, position, block, lane)
-    if (u >= (size_t)9 * cin * cout / 8) return;
+    if (u >= (size_t)9 * (cin / 16) * NN * 64) return;
     const int l = u % 64, n0 = u / 64 % NN, kpos = u / 64 / NN % 9, c = (int)(u / 64 / NN / 9);
     const int n = 32 * n0 + l % 32, ci = 16 * c + 8 * (l / 32);
     __bf16 *d = dst + ((size_t)(c * 9 + kpos) * 3 * NN + n0) * 512 + l * 8;
     for (int q = 0; q < 2; ++q) {
-        const floatx4 v = *reinterpret_cast<const floatx4 *>(w + f32_weight(kpos, ci + 4 * q, n, cin, cout));
+        floatx4 v{0.f, 0.f, 0.f, 0.f};
+        if (n < c16) v = *reinterpret_cast<const floatx4 *>(w + f32_weight(kpos, ci + 4 * q, n, cin, c16));
         bf16x4 p[3];
         split4(v, p[0], p[1], p[2]);
         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<bf16x4 *>(d + (size_t)pl * NN * 512 + 4 * q) = p[pl];
     }
 }
 
-template <int CIN, int COUT, bool DENSE, bool VAR>
+template <int CIN, int COUT, int MODE>
 hipError_t run_split(const ConvArgs &a, int cus, hipStream_t s) {
     constexpr size_t lds = SplitConv<CIN, COUT, 16>::lds_bytes;
     static_assert(lds <= 160 * 1024, "chunk buffers exceed LDS");
-    auto kern = k_conv_mfma_split<CIN, COUT, DENSE, VAR>;
+    auto kern = k_conv_mfma_split<CIN, COUT, MODE>;
     static hipError_t attr = set_lds(kern, lds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, (a.max_tiles + 3) / 4)), dim3(256), lds, s, a);
@@ -339,6 +370,8 @@ hipError_t run_split(const ConvArgs &a, int cus, hipStream_t s) {
 }
 
 #define RN_SPLIT_SHAPES(X) X(64, 128) X(128, 128)
+// Input gradients: channels of dJ/dz, of the layer's input.
+#define RN_DX_SHAPES(X) X(80, 40) X(128, 64) X(128, 128)
 
 }  // namespace
 
@@ -349,11 +382,19 @@ bool conv_split_supported(int cin, int cout) {
     return false;
 }
 
-size_t conv_split_bytes(int cin, int cout) { return (size_t)9 * cin * cout * 6; }
+bool train_dx_supported(int cz, int ca) {
+#define X(ci, co) if (cz == ci && ca == co) return true;
+    RN_DX_SHAPES(X)
+#undef X
+    return false;
+}
+
+size_t conv_split_bytes(int cin, int cout) { return (size_t)9 * cin * ((cout + 31) / 32 * 32) * 6; }
 
 hipError_t launch_pack_split(const float *w, int cin, int cout, void *dst, hipStream_t s) {
-    const int units = 9 * cin * cout / 8;
-    hipLaunchKernelGGL(k_pack_split, dim3((units + 255) / 256), dim3(256), 0, s, w, cin, cout, static_cast<__bf16 *>(dst));
+    const int NN = (cout + 31) / 32, units = 9 * (cin / 16) * NN * 64;
+    hipLaunchKernelGGL(k_pack_split, dim3((units + 255) / 256), dim3(256), 0, s, w, cin, (cout + 15) / 16 * 16, NN,
+                       static_cast<__bf16 *>(dst));
     return hipGetLastError();
 }
 
@@ -361,11 +402,20 @@ hipError_t launch_conv_split(const ConvArgs &a, int cus, hipStream_t s, bool var
     const bool dense = a.wl == nullptr;
     if (var && dense) return hipErrorInvalidValue;
     if (a.fuse_first || a.n_out > 0) return hipErrorInvalidValue;   // head partials come from their own kernel
-#define X(ci, co)                                                                      \
-    if (a.cin == ci && a.cout == co)                                                   \
-        return var ? run_split<ci, co, false, true>(a, cus, s)                         \
-                   : dense ? run_split<ci, co, true, false>(a, cus, s) : run_split<ci, co, false, false>(a, cus, s);
+#define X(ci, co)                                                      \
+    if (a.cin == ci && a.cout == co)                                   \
+        return var ? run_split<ci, co, VARIANTS>(a, cus, s)            \
+                   : dense ? run_split<ci, co, DENSE_PASS>(a, cus, s) : run_split<ci, co, LIST>(a, cus, s);
     RN_SPLIT_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_bwd_dx(const ConvArgs &a, int cus, hipStream_t s) {
+    if (a.wl != nullptr || a.mask == nullptr) return hipErrorInvalidValue;
+#define X(ci, co) \
+    if (a.cin == ci && a.cout == co) return run_split<ci, co, INPUT_GRAD>(a, cus, s);
+    RN_DX_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
 }

@@ -62,6 +62,7 @@ struct Plan {
     size_t o_ws[RN_MAX_CONV] = {0};
     bool plain = false;                     // RN_OPT_SEPARATE_FIRST: steps and full passes sum in plain float32
     size_t wt_elems[RN_MAX_CONV] = {0};
+    size_t o_wts[RN_MAX_CONV] = {0};        // their bf16 planes
     size_t act_stride[RN_MAX_CONV + 1] = {0};   // elements per slot
     size_t total = 0;
 };
@@ -228,6 +229,7 @@ rn_status plan_config(const rn_config *cfg, Plan *p, std::string *err) {
     for (int l = 1; l < p->L; ++l) {
         p->wt_elems[l] = p->train_why ? 0 : dx_weights_elems(p->C[l + 1], p->C[l]);
         p->o_wt[l] = take(p->wt_elems[l] * 4);
+        p->o_wts[l] = take(p->wt_elems[l] ? conv_split_bytes(p->C[l + 1], p->C[l]) : 0);
     }
     p->o_wd = take((size_t)p->N * p->K * 4);
     p->o_bd = take((size_t)p->N * 4);
@@ -452,6 +454,8 @@ hipError_t split_weights(reuse_net *net, hipStream_t s) {
     for (int l = 1; l < p.L && e == hipSuccess; ++l)
         if (p.split[l]) e = launch_pack_split(net->at<float>(p.o_w[l]), p.C[l], p.C[l + 1], net->at<void>(p.o_ws[l]), s);
         else if (!p.gen[l] && p.dt == RN_F32) e = launch_pack_res(net->at<float>(p.o_w[l]), net->at<void>(p.o_ws[l]), s);
+    for (int l = 1; l < p.L && e == hipSuccess; ++l)
+        if (p.wt_elems[l]) e = launch_pack_split(net->at<float>(p.o_wt[l]), p.C[l + 1], p.C[l], net->at<void>(p.o_wts[l]), s);
     return e;
 }
 
@@ -1264,8 +1268,6 @@ rn_status reuse_net_backward(reuse_net *net, int32_t n, const int32_t *ids_in, c
         ba.stack = p.stack;
         ba.cin0 = p.in_c;
         ba.ring_head = net->at<int32_t>(p.o_ring);
-        ba.dz_out = dz[cur ^ 1];
-        ba.wt = l > 0 ? net->at<float>(p.o_wt[l]) : nullptr;
         ba.part = reinterpret_cast<float *>(sc + bp.o_part);
         ba.teams = bp.teams[l];
         ba.gw = grads + gl.w[l];
@@ -1274,7 +1276,26 @@ rn_status reuse_net_backward(reuse_net *net, int32_t n, const int32_t *ids_in, c
         e = timed(net, RN_PHASE_BWD_DW, s, [&] { return launch_bwd_dw(ba, net->cus, s); });
         if (e != hipSuccess) return net->fail(RN_EHIP, std::string("weight gradient: ") + hipGetErrorString(e));
         if (l > 0) {
-            e = timed(net, RN_PHASE_BWD_DX, s, [&] { return launch_bwd_dx(ba, net->cus, s); });
+            ConvArgs xa{};
+            xa.ids = net->at<int32_t>(p.o_ids);           // dz by batch index
+            xa.in = dz[cur];
+            xa.out = dz[cur ^ 1];
+            xa.w = net->at<float>(p.o_wt[l]);
+            xa.w_split = net->at<void>(p.o_wts[l]);
+            xa.H = p.Hl[l + 1];
+            xa.W = p.Wl[l + 1];
+            xa.TH = p.THl[l + 1];
+            xa.TW = p.TWl[l + 1];
+            xa.cin = p.C[l + 1];
+            xa.cout = p.C[l];
+            xa.in_stride = p.act_stride[l + 1];
+            xa.out_stride = p.act_stride[l];
+            xa.dense_n = n;
+            xa.max_tiles = n * p.ntl[l + 1];
+            xa.mask = net->at<float>(p.o_act[l]);
+            xa.mask_stride = p.act_stride[l];
+            xa.mask_ids = ids;
+            e = timed(net, RN_PHASE_BWD_DX, s, [&] { return launch_bwd_dx(xa, net->cus, s); });
             if (e != hipSuccess) return net->fail(RN_EHIP, std::string("input gradient: ") + hipGetErrorString(e));
             cur ^= 1;
         }

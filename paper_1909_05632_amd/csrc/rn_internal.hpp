@@ -142,6 +142,11 @@ struct ConvArgs {
     int vframe_u8;
     int vframe_shared;            // 1: every variant reads frame 0
     const float *lut;             // [256] level -> float32
+    // Input gradients (launch_bwd_dx): results are kept where `mask`, the
+    // activations of slot mask_ids[i] of batch index i, is above 0.
+    const float *mask;            // [S][TH][TW][16][cout]
+    size_t mask_stride;
+    const int32_t *mask_ids;      // [n]
 };
 
 // Dense path: copy the frames into the input cache and mark the slots primed.
@@ -219,6 +224,11 @@ bool conv_split_supported(int cin, int cout);
 size_t conv_split_bytes(int cin, int cout);
 hipError_t launch_pack_split(const float *w, int cin, int cout, void *dst, hipStream_t s);
 hipError_t launch_conv_split(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
+// Gradient at a layer's input from dJ/dz in `in` ([n][ntiles][16][cin], by
+// batch index: ids is the identity table), w / w_split the packings of
+// pack_dx_weights: dense mode with a mask.
+bool train_dx_supported(int cz, int ca);
+hipError_t launch_bwd_dx(const ConvArgs &a, int cus, hipStream_t s);
 // The same layers on the float32 matrix instructions (nets with
 // RN_OPT_SEPARATE_FIRST), not for variants.
 hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s);

@@ -132,244 +132,6 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
     }
 }
 
-// ------------------------------------------------------------------ dx
-
-// Offset (floats) of 16-byte channel chunk c4 of halo pixel p (6x6 halo,
-// pixel stride CZ): the chunk index XOR-ed with a function of the pixel, so
-// the 16 pixels one 16-lane group reads at a kernel position fall in distinct
-// bank groups (the scheme of the forward MFMA kernels).
-template <int CZ>
-__device__ inline int hoff(int p, int c4) {
-    constexpr int C4 = CZ / 4;
-    static_assert(C4 == 10 || C4 == 20 || C4 == 16 || C4 == 32, "halo swizzle defined for 40, 64, 80, 128 channels");
-    const int hy = p / 6, hx = p - 6 * hy;
-    const int g = C4 == 10 ? (hy & 1) : C4 == 20 ? (hy & 3) : (hy & 3) | ((hx & 3) << 2);
-    return p * CZ + 4 * (c4 ^ g);
-}
-
-// Input gradients dz_{l-1} = (W_l^T * dz_l) where a_{l-1} > 0, as a forward
-// convolution of dz_l (CZ channels) with the transposed, flipped weights
-// (pack_dx_weights) into CA channels.  A block works on a group of WV tiles
-// of layer l-1 (one per wave: 8 where two weight stages and eight halos fit
-// one CU's LDS, so two waves per SIMD, else 4) and streams the weights
-// through LDS in stages of one kernel position x SC channels of dz_l, two
-// buffers: stage q + 1 goes straight from global memory into the free buffer
-// at the start of stage q (lds_dma16, the block's loads split over its
-// waves), each wave waits for its own loads and a block barrier ends the
-// stage.  So each weight byte brought from L2 serves WV tiles.  Each wave
-// keeps its tile's 6x6 x CZ halo of dz_l in its own LDS area (the next
-// group's fetched into registers three stages before the group ends, stored
-// after the epilogue: fetched in the last stage it arrived late, 14% of the
-// time).  Operand layout of v_mfma_f32_16x16x4_f32 as in the forward
-// kernels: A row m = tile pixel (m % 4, m / 4), lane group kq takes
-// K = 16 b + 4 kq + j; D lane (n, kq) holds pixels (i, kq), i = 0..3, of
-// output channel 16 nb + n.
-template <int CZ, int CA>
-struct Dx {
-    static constexpr int NB = (CA + 15) / 16;   // 16-column output blocks (CA padded with zero weights)
-    static constexpr int SC = (CZ > 64 && CZ % 64 == 0) ? 64 : CZ;   // channels of dz_l per stage
-    static constexpr int NCH = CZ / SC;         // stages per kernel position
-    static constexpr int NQ = 9 * NCH;          // stages per group
-    static constexpr int SB = SC / 16;          // 16-deep K blocks per stage
-    static constexpr int KBP = CZ / 16;         // K blocks per kernel position
-    static constexpr int WL = SB * NB;          // 1 KB wave loads per stage
-    static constexpr int WST = WL * 256;        // floats per stage
-    static constexpr int HALO = 36 * CZ;        // floats of one tile's halo
-    static constexpr int HV = (9 * CZ + 63) / 64;   // 16-byte halo loads per lane
-    // waves (tiles of a group) per block: 8 where two weight stages and 8 halos fit one CU
-    static constexpr int WV = (2 * WST + 8 * HALO) * 4 <= 160 * 1024 ? 8 : 4;
-    static constexpr size_t lds_bytes = (size_t)(2 * WST + WV * HALO) * sizeof(float);
-    static_assert(CZ % 16 == 0 && SC % 16 == 0, "whole 16-channel K blocks per stage");
-    static_assert(CA % 4 == 0, "whole 16-byte channel groups in the epilogue");
-    static_assert(HV <= 32, "halo mask width");
-};
-
-template <int CZ, int CA>
-__device__ inline void dx_fetch_halo(const BwdArgs &a, int tid, bool valid, float4 *regs, uint32_t &ok, int lane) {
-    using D = Dx<CZ, CA>;
-    constexpr int C4 = CZ / 4;
-    const int i = valid ? tid / a.ntiles : 0, t = valid ? tid - i * a.ntiles : 0;
-    const int ty = t / a.TW, tx = t - ty * a.TW;
-    const float *src = a.dz_in + (size_t)i * a.ntiles * kTilePx * CZ;
-    ok = 0;
-#pragma unroll
-    for (int k = 0; k < D::HV; ++k) {
-        const int e = lane + 64 * k;
-        const int pos = e / C4, c4 = e - pos * C4;
-        const int y = ty * kTile - 1 + pos / 6, x = tx * kTile - 1 + pos % 6;
-        const bool in = valid && e < 36 * C4 && y >= 0 && y < a.H && x >= 0 && x < a.W;
-        // every load issued (an absent one reads the tile's first chunk)
-        regs[k] = *reinterpret_cast<const float4 *>(
-            src + (in ? ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CZ + 4 * c4 : 0));
-        ok |= (uint32_t)in << k;
-    }
-}
-
-template <int CZ, int CA>
-__device__ inline void dx_store_halo(float *halo, const float4 *regs, uint32_t ok, int lane) {
-    using D = Dx<CZ, CA>;
-    constexpr int C4 = CZ / 4;
-#pragma unroll
-    for (int k = 0; k < D::HV; ++k) {
-        const int e = lane + 64 * k;
-        if (e < 36 * C4) {
-            const int pos = e / C4, c4 = e - pos * C4;
-            *reinterpret_cast<float4 *>(halo + hoff<CZ>(pos, c4)) = (ok >> k) & 1 ? regs[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    }
-}
-
-// The block's share of stage q's weights straight into LDS: wave w issues
-// the stage's wave loads w, w + 4, ...
-template <int CZ, int CA>
-__device__ inline void dx_dma_stage(const float *wt, int q, float *dst, int wave, int lane) {
-    using D = Dx<CZ, CA>;
-    const int kpos = q / D::NCH, ch = q - kpos * D::NCH;
-    const float *src = wt + (size_t)(kpos * D::KBP + ch * D::SB) * D::NB * 256;
-    const uint32_t l0 = dev::lds_addr(dst);
-#pragma unroll
-    for (int j = 0; j < (D::WL + D::WV - 1) / D::WV; ++j) {
-        const int wl = wave + D::WV * j;
-        if (wl < D::WL) dev::lds_dma16(src + wl * 256 + 4 * lane, l0 + 1024u * wl);   // uniform per wave
-    }
-}
-
-// One exchange of a quad transpose: lanes that differ in lane bit BIT swap
-// the elements that differ in element bit BIT (DPP quad permutation [1,0,3,2]
-// for bit 0, [2,3,0,1] for bit 1).
-template <int BIT>
-__device__ inline void dx_quad_xchg(float (&v)[4], int b) {
-    constexpr int step = 1 << BIT, ctrl = BIT == 0 ? 0xb1 : 0x4e;
-    const bool hi = b & step;
-    float r[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int lo = BIT == 0 ? 2 * k : k;              // the pair (lo, lo + step)
-        r[k] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(hi ? v[lo] : v[lo + step]), ctrl, 0xf, 0xf, false));
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {                         // selects on values: constant indices only
-        const int lo = BIT == 0 ? 2 * k : k;
-        v[lo] = hi ? r[k] : v[lo];
-        v[lo + step] = hi ? v[lo + step] : r[k];
-    }
-}
-
-// 4 x 4 transpose inside each lane quad: lane 4 m + b holds v[i] = X[i][b]
-// on entry and X[b][i] on return.
-__device__ inline void dx_quad_transpose(float (&v)[4], int b) {
-    dx_quad_xchg<0>(v, b);
-    dx_quad_xchg<1>(v, b);
-}
-
-template <int CZ, int CA>
-__global__ __launch_bounds__((64 * Dx<CZ, CA>::WV)) void k_bwd_dx(BwdArgs a) {
-    using D = Dx<CZ, CA>;
-    extern __shared__ float smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int NT = a.n * a.ntiles, NG = (NT + D::WV - 1) / D::WV;
-    if ((int)blockIdx.x >= NG) return;                             // uniform per block
-    float *wbuf = smem;                                            // two stages
-    float *halo = smem + 2 * D::WST + wave * D::HALO;              // this wave's tile
-    const int mrow = lane & 15, kq = lane >> 4;
-    const int pix = (mrow & 3) * 6 + (mrow >> 2);
-
-    int g = blockIdx.x;
-    dx_dma_stage<CZ, CA>(a.wt, 0, wbuf, wave, lane);
-    float4 hreg[D::HV];
-    uint32_t hok;
-    dx_fetch_halo<CZ, CA>(a, D::WV * g + wave, D::WV * g + wave < NT, hreg, hok, lane);
-    dx_store_halo<CZ, CA>(halo, hreg, hok, lane);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    dev::lds_barrier();
-    int buf = 0;
-    for (; g < NG; g += gridDim.x) {                               // uniform per block
-        const int tid = D::WV * g + wave, tidn = D::WV * (g + (int)gridDim.x) + wave;
-        floatx4 acc[D::NB];
-#pragma unroll
-        for (int nb = 0; nb < D::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-        // The epilogue's view, after a quad transpose of the accumulators:
-        // lane (qb, qm, kq) holds pixel qb * 4 + kq of the tile, channels
-        // c0(nb) = 16 nb + 4 qm .. + 3.  Its ReLU mask (a_{l-1} at those
-        // places, 16 bytes per block) is loaded now, waited for by the end of
-        // this stage, so the epilogue waits for no load.
-        const int qb = lane & 3, qm = (lane >> 2) & 3, em = qb * 4 + kq;
-        float4 msk[D::NB];
-        {
-            const bool tv = tid < NT;
-            const int i = tv ? tid / a.ntiles : 0, t = tv ? tid - i * a.ntiles : 0;
-            const float *ap = a.act_prev + (size_t)a.ids[i] * a.prev_stride + ((size_t)t * kTilePx + em) * CA;
-#pragma unroll
-            for (int nb = 0; nb < D::NB; ++nb) {
-                const int c0 = nb * 16 + 4 * qm;
-                msk[nb] = *reinterpret_cast<const float4 *>(ap + (c0 < CA ? c0 : 0));
-            }
-        }
-        for (int q = 0; q < D::NQ; ++q) {
-            const int kpos = q / D::NCH, ch = q - kpos * D::NCH;
-            const int ky = kpos / 3, kx = kpos - ky * 3;
-            const float *wst = wbuf + buf * D::WST;
-            float4 av = *reinterpret_cast<const float4 *>(halo + hoff<CZ>(pix + ky * 6 + kx, 4 * ch * D::SB + kq));
-            float4 bv[D::NB];
-#pragma unroll
-            for (int nb = 0; nb < D::NB; ++nb) bv[nb] = *reinterpret_cast<const float4 *>(wst + (nb * 64 + lane) * 4);
-            dx_dma_stage<CZ, CA>(a.wt, q + 1 < D::NQ ? q + 1 : 0, wbuf + (buf ^ 1) * D::WST, wave, lane);
-            // The next group's halo is fetched three stages before the end
-            // (issued after this stage's weight loads: the wait below leaves
-            // it in flight, the next stages' waits find it arrived).
-            const bool hstage = q == (D::NQ >= 3 ? D::NQ - 3 : 0);
-            if (hstage) dx_fetch_halo<CZ, CA>(a, tidn, tidn < NT, hreg, hok, lane);
-#pragma unroll
-            for (int b = 0; b < D::SB; ++b) {
-                float4 an = av, bn[D::NB];
-#pragma unroll
-                for (int nb = 0; nb < D::NB; ++nb) bn[nb] = bv[nb];
-                if (b + 1 < D::SB) {                               // the next block's operands during this one's ops
-                    an = *reinterpret_cast<const float4 *>(halo + hoff<CZ>(pix + ky * 6 + kx, 4 * (ch * D::SB + b + 1) + kq));
-#pragma unroll
-                    for (int nb = 0; nb < D::NB; ++nb)
-                        bn[nb] = *reinterpret_cast<const float4 *>(wst + (((b + 1) * D::NB + nb) * 64 + lane) * 4);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                const float al[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int nb = 0; nb < D::NB; ++nb) {
-                        const float bj = j == 0 ? bv[nb].x : j == 1 ? bv[nb].y : j == 2 ? bv[nb].z : bv[nb].w;
-                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(al[j], bj, acc[nb], 0, 0, 0);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-                av = an;
-#pragma unroll
-                for (int nb = 0; nb < D::NB; ++nb) bv[nb] = bn[nb];
-            }
-            buf ^= 1;
-            if (hstage) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(D::HV) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            dev::lds_barrier();
-        }
-        if (tid < NT) {                                            // uniform per wave
-            const int i = tid / a.ntiles, t = tid - i * a.ntiles;
-            float *dst = a.dz_out + (((size_t)i * a.ntiles + t) * kTilePx + em) * CA;
-#pragma unroll
-            for (int nb = 0; nb < D::NB; ++nb) {
-                float v[4] = {acc[nb][0], acc[nb][1], acc[nb][2], acc[nb][3]};   // pixels r * 4 + kq, channel 16 nb + 4 qm + qb
-                dx_quad_transpose(v, qb);
-                const int c0 = nb * 16 + 4 * qm;
-                if (c0 < CA)                                       // CA % 4 == 0: whole float4s
-                    *reinterpret_cast<float4 *>(dst + c0) =
-                        make_float4(msk[nb].x > 0.f ? v[0] : 0.f, msk[nb].y > 0.f ? v[1] : 0.f,
-                                    msk[nb].z > 0.f ? v[2] : 0.f, msk[nb].w > 0.f ? v[3] : 0.f);
-            }
-        }
-        dev::wave_sync();                                          // this wave's halo reads are done
-        dx_store_halo<CZ, CA>(halo, hreg, hok, lane);
-        dev::wave_sync();
-    }
-}
-
 // ------------------------------------------------------------------ dW
 
 // dW for layers 2..L (a_{l-1} a tiled cache), operands read 16 bytes at a
@@ -989,7 +751,6 @@ __global__ __launch_bounds__(256) void k_unprime(int32_t *primed, int S) {
 
 #define RN_DW_FIRST_SHAPES(X) X(1, 20) X(1, 40) X(1, 64) X(1, 80) X(4, 20) X(4, 40) X(4, 64) X(4, 80)
 #define RN_DW_SHAPES(X) X(40, 80) X(64, 128) X(128, 128)
-#define RN_DX_SHAPES(X) X(80, 40) X(128, 64) X(128, 128)
 
 int dw_blocks_per_team(int ca, int cz, bool first) {
 #define X(a_, z_) \
@@ -1035,30 +796,9 @@ hipError_t run_dw2(const BwdArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int CZ, int CA>
-hipError_t run_dx(const BwdArgs &a, int cus, hipStream_t s) {
-    using D = Dx<CZ, CA>;
-    auto kern = k_bwd_dx<CZ, CA>;
-    static hipError_t attr = dev::set_lds(kern, D::lds_bytes);
-    if (attr != hipSuccess) return attr;
-    const long long groups = ((long long)a.n * a.ntiles + D::WV - 1) / D::WV;
-    const int per_cu = D::lds_bytes <= 78 * 1024 ? 2 : 1;       // blocks that fit one CU's LDS
-    const int grid = (int)std::min<long long>(groups, (long long)per_cu * cus);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * D::WV), D::lds_bytes, s, a);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 bool train_shapes_supported(int ca, int cz, bool first) { return dw_blocks_per_team(ca, cz, first) > 0; }
-
-bool train_dx_supported(int cz, int ca) {
-#define X(z_, a_) \
-    if (cz == z_ && ca == a_) return true;
-    RN_DX_SHAPES(X)
-#undef X
-    return false;
-}
 
 size_t dx_weights_elems(int cz, int ca) { return (size_t)9 * cz * ((ca + 15) / 16) * 16; }
 
@@ -1128,14 +868,6 @@ hipError_t launch_bwd_dw(const BwdArgs &a, int cus, hipStream_t s) {
 #define X(a_, z_) \
     if (!first && a.ca == a_ && a.cz == z_) return run_dw2<a_, z_>(a, s);
     RN_DW_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_bwd_dx(const BwdArgs &a, int cus, hipStream_t s) {
-#define X(z_, a_) \
-    if (a.cz == z_ && a.ca == a_) return run_dx<z_, a_>(a, cus, s);
-    RN_DX_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
 }

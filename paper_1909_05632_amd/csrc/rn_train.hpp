@@ -27,8 +27,7 @@ struct HeadBwdArgs {
 
 // One conv layer l's backward: dz_in = dJ/dz_l [n][ntiles][16][cz]; act_prev
 // the layer-(l-1) activations (a tiled cache, or the float32 input planes for
-// layer 1); dW (split over teams of blocks into part, then reduced) and, for
-// l >= 2, dz_out = dJ/dz_{l-1} = (W_l^T * dz_l) where a_{l-1} > 0.
+// layer 1); dW (split over teams of blocks into part, then reduced).
 struct BwdArgs {
     int n, H, W, TH, TW, ntiles;
     int ca, cz;                   // channels of a_{l-1} and of layer l
@@ -39,8 +38,6 @@ struct BwdArgs {
     int first;                    // act_prev is the input cache (planar; a ring of 4 frames when stacking)
     int stack, cin0;              // layer 1: frames stacked, channels per frame
     const int32_t *ring_head;
-    float *dz_out;                // l >= 2
-    const float *wt;              // dx weights (pack_dx_weights)
     float *part;                  // [cz][9 ca + 1][teams]
     int teams;
     float *gw, *gb;               // OIHW [cz][ca][3][3], [cz]
@@ -67,7 +64,6 @@ struct SgdArgs {
 };
 
 bool train_shapes_supported(int ca, int cz, bool first);
-bool train_dx_supported(int cz, int ca);
 size_t dx_weights_elems(int cz, int ca);
 // W_l (OIHW, cz outputs, ca inputs) -> the B operand of the dx product.
 void pack_dx_weights(const float *oihw, int ca, int cz, float *dst);
@@ -80,7 +76,6 @@ hipError_t launch_reinforce(int n, int n_out, const float *logits, const int32_t
                             float *g, hipStream_t s);
 hipError_t launch_bwd_head(const HeadBwdArgs &a, hipStream_t s);
 hipError_t launch_bwd_dw(const BwdArgs &a, int cus, hipStream_t s);   // partials, then the reduction
-hipError_t launch_bwd_dx(const BwdArgs &a, int cus, hipStream_t s);
 hipError_t launch_sgd(const SgdArgs &a, hipStream_t s);
 hipError_t launch_unprime(int32_t *primed, int S, hipStream_t s);
 

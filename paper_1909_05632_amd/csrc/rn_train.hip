@@ -20,7 +20,7 @@
 // The SGD step updates every packed copy of a weight in place.
 #include <type_traits>
 
-#include "rn_device.hpp"
+#include "rn_split.hpp"
 #include "rn_train.hpp"
 
 namespace rn {
@@ -134,380 +134,227 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
 
 // ------------------------------------------------------------------ dW
 
-// dW for layers 2..L (a_{l-1} a tiled cache), operands read 16 bytes at a
-// time.  The K index of the product is the tile's pixel: in 4 consecutive
-// k-steps lane group kq takes k = 4 kq + j, j = 0..3, pixel (row kq, column j),
-// so a lane's A values (dz at those pixels, output channel 16 mb + n) are
-// one 16-byte read of a transposed dz tile [channel][pixel], and its B values
-// (a_{l-1} at those pixels shifted by the column's kernel position (ky, kx),
-// channel ci) one 16-byte read of the halo copy for kx, [ci][halo row][4]
-// (halo columns kx .. kx + 3 of each row).  Wave u of a team owns all MBU
-// row blocks and QW column blocks (MBU x QW x 4 accumulators), so one staged
-// tile feeds MBU x QW x 4 matrix ops from MBU + QW reads.  Two staging
-// buffers of P tiles each alternate: the matrix ops read one while the next P
-// tiles are written to the other between their k-steps, one barrier per pass
-// (P = 2 where both buffers fit one CU's LDS, else 1).  Row strides (20
-// and 28 floats) put the 16 lanes of a read group in distinct bank groups.
-template <int CA, int CZ>
-struct Dw2 {
-    static constexpr int NQ = 9 * CA + 1;                 // columns: (kernel position, input channel), bias
-    static constexpr int NBQ = (NQ + 15) / 16;            // 16-column blocks
-    static constexpr int MB = CZ / 16;                    // 16-row blocks (output channels)
-    static constexpr int MBU = MB;                        // row blocks per wave
-    static constexpr int QW0 = 32 / MBU;                  // column blocks per wave, at most 32 blocks of accumulators
-    static constexpr int NCH = (NBQ + QW0 - 1) / QW0;     // column chunks (waves per team)
-    static constexpr int QW = (NBQ + NCH - 1) / NCH;
-    static constexpr int BPT = (NCH + 3) / 4;             // blocks per team
-    static constexpr int SZ = 20;                         // dz row stride (16 pixels + pad)
-    static constexpr int HS = 28;                         // halo copy channel stride (6 rows x 4 + pad)
-    static constexpr int DZT = CZ * SZ;                   // floats of one staged dz tile
-    static constexpr int HT = 3 * CA * HS;                // floats of one staged halo (three copies)
-    static constexpr int P = 16 * (DZT + HT) <= 160 * 1024 ? 2 : 1;  // tiles per buffer
-    static constexpr int DZV = (4 * CZ + 255) / 256;      // 16-byte dz chunks per thread and tile
-    static constexpr int HV = (9 * CA + 255) / 256;       // 16-byte halo chunks per thread and tile
-    static constexpr int BUF = P * (DZT + HT);            // floats of one staging buffer
-    static constexpr size_t lds_bytes = (size_t)2 * BUF * sizeof(float);   // two buffers
-    static_assert(lds_bytes <= 160 * 1024, "two buffers fit one CU");
-    static_assert(CZ % 16 == 0 && CA % 4 == 0, "whole row blocks and 16-byte channel chunks");
+// dW and db of layers 2..L on the bf16 matrix cores with operands split three
+// ways (rn_split.hpp): a GEMM with M = output channels, N = (kernel position,
+// input channel), K = pixels, on v_mfma_f32_16x16x32_bf16, two tiles (32
+// pixels) a step.
+//
+// Bound: matrix issue, 6 x 2 * 16 * CZ * 9 CA flops a tile; the float32
+// instruction needs 16/6 of that time.  A block of eight waves (two per SIMD)
+// sums CZB output channels x CAB input channels of a team's tiles: the waves
+// share out the 9 x CAB / 16 column blocks, each with all CZB / 16 row blocks
+// in registers (80 accumulator registers).  A team has CA / CAB x CZ / CZB
+// blocks, on one XCD where the teams allow it, since they read the same tiles.
+// The tiles' dz and a_{l-1} halos sit in LDS as bf16 planes, pixel by pixel as
+// in the caches (32 bytes of padding a pixel keep the banks apart); the matrix
+// operands want consecutive pixels of one channel, which ds_read_b64_tr_b16
+// gives: 16 lanes address 16 channels of four pixels and each receives its
+// channel's four.  So a value is split and written once, and a kernel position
+// is an address offset.  (The float32 kernels kept a transposed dz and three
+// column-shifted halo copies in LDS.)  Two buffers of two tiles: while the
+// matrix ops read one, the next step's tiles, loaded a step earlier, are split
+// into the other between them; one barrier a step.
+// A sum that is not finite is summed again in plain float32 by k_bwd_reduce.
+template <int CAB, int CZB>
+struct DwSplit {
+    static constexpr int MB = CZB / 16;                   // row blocks
+    static constexpr int NBC = (CAB + 15) / 16;           // column blocks per kernel position
+    static constexpr int NBT = 9 * NBC;
+    static constexpr int NW = NBT / 8, EXTRA = NBT % 8;   // column blocks per wave; the first EXTRA waves have one more
+    static constexpr int HS = CAB * 2 + 32, HP = 36 * HS; // bytes of a halo pixel, of a plane
+    static constexpr int DS = CZB * 2 + 32, DP = 16 * DS;
+    static constexpr int TILE = 3 * (HP + DP);
+    static constexpr int BUF = 2 * TILE;
+    static constexpr size_t lds_bytes = 2 * (size_t)BUF;
+    static constexpr int HU = 36 * CAB / 4, DU = 16 * CZB / 4;   // 16-byte units of a tile
+    static constexpr int UPT = (2 * (HU + DU) + 511) / 512;      // per thread
+    static_assert(CZB % 16 == 0 && CAB % 8 == 0 && lds_bytes <= 160 * 1024, "block shape");
+    static_assert(EXTRA < 8 && UPT <= NW, "a staging unit beside each column block");
 };
 
-// Staging of one fetched tile into an LDS buffer by 256 threads (tix the
-// thread's index among them): dz transposed to [channel][pixel] (PART 0), the
-// halo as three column-shifted copies [kx][channel][row-major 6 x 4 window]
-// (PART 1).
-template <int CA, int CZ, int PART>
-__device__ inline void dw2_stage(float *dz, float *h, const float4 *rdz, const float4 *rh, int tix) {
-    using D = Dw2<CA, CZ>;
-    if constexpr (PART == 0) {
+__device__ __align__(16) float g_zero_unit[4];
+
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef short shortx8 __attribute__((ext_vector_type(8)));
+
+// Two transposed reads: pixels of the halves' first and second row of four.
+__device__ inline dev::bf16x8 tr_frag(const unsigned char *p, int second) {
+    const shortx4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)p);
+    const shortx4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(p + second));
+    return __builtin_bit_cast(dev::bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int CAB, int CZB, int NW, bool BIAS, typename Fetch, typename Stage>
+__device__ inline void dw_split_wave(const BwdArgs &a, const unsigned char *lds, int q0, int steps, int team, int ci0, int co0,
+                                     Fetch fetch, Stage stage) {
+    using D = DwSplit<CAB, CZB>;
+    using dev::bf16x8;
+    const int lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15;
+    // Lane group kq takes tile kq / 2, pixel rows 2 (kq % 2) and the next; its
+    // lane i addresses pixel i / 4 of a row, channels 4 (i % 4) ..
+    const int tile = (kq >> 1) * D::TILE, row = 2 * (kq & 1), px = col >> 2, c4 = (col & 3) * 8;
+    const unsigned char *ab = lds + tile + 3 * D::HP + (row * 4 + px) * D::DS + c4;
+    const unsigned char *bb = lds + tile + (row * 6 + px) * D::HS + c4;
+    int boff[NW];
 #pragma unroll
-        for (int k = 0; k < D::DZV; ++k) {
-            const int e = tix + 256 * k;
-            if (e < 4 * CZ) {
-                const int m = e / (CZ / 4), c4 = e - m * (CZ / 4);   // pixel m, channels 4 c4 ..
-                const float4 v = rdz[k];
-                dz[(4 * c4 + 0) * D::SZ + m] = v.x;
-                dz[(4 * c4 + 1) * D::SZ + m] = v.y;
-                dz[(4 * c4 + 2) * D::SZ + m] = v.z;
-                dz[(4 * c4 + 3) * D::SZ + m] = v.w;
+    for (int k = 0; k < NW; ++k) {
+        const int pos = (q0 + k) / D::NBC, nb = (q0 + k) - pos * D::NBC;
+        boff[k] = (pos / 3 * 6 + pos % 3) * D::HS + nb * 32;
+    }
+    floatx4 acc[D::MB][NW], accb[BIAS ? D::MB : 1];
+#pragma unroll
+    for (int m = 0; m < D::MB; ++m) {
+        if constexpr (BIAS) accb[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < NW; ++k) acc[m][k] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+    int buf = 0;
+    for (int s = 0; s < steps; ++s) {
+        bf16x8 x[D::MB][3];
+#pragma unroll
+        for (int m = 0; m < D::MB; ++m)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) x[m][pl] = tr_frag(ab + buf * D::BUF + pl * D::DP + m * 32, 4 * D::DS);
+        bf16x8 y[3];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) y[pl] = tr_frag(bb + buf * D::BUF + boff[0] + pl * D::HP, 6 * D::HS);
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            bf16x8 yn[3];
+            if (k + 1 < NW) {
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) yn[pl] = tr_frag(bb + buf * D::BUF + boff[k + 1] + pl * D::HP, 6 * D::HS);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            // (dz plane, a plane), small terms first
+            constexpr int px_[6] = {2, 0, 1, 1, 0, 0}, py_[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+#pragma unroll
+                for (int m = 0; m < D::MB; ++m)
+                    acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[m][px_[p]], y[py_[p]], acc[m][k], 0, 0, 0);
+            if (k < D::UPT) stage(k, buf ^ 1);            // the next step's tiles
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) y[pl] = yn[pl];
         }
-    } else {
+        if constexpr (BIAS) {
 #pragma unroll
-        for (int k = 0; k < D::HV; ++k) {
-            const int e = tix + 256 * k;
-            if (e < 9 * CA) {
-                const int pos = e / (CA / 4), c4 = e - pos * (CA / 4);
-                const int hy = pos / 6, hx = pos - 6 * hy;
-                const float4 v = rh[k];
+            for (int pl = 2; pl >= 0; --pl)
 #pragma unroll
-                for (int kx = 0; kx < 3; ++kx) {
-                    const int j = hx - kx;
-                    if (j < 0 || j > 3) continue;
-                    float *d = h + (kx * CA + 4 * c4) * D::HS + hy * 4 + j;
-                    d[0] = v.x;
-                    d[D::HS] = v.y;
-                    d[2 * D::HS] = v.z;
-                    d[3 * D::HS] = v.w;
-                }
+                for (int m = 0; m < D::MB; ++m)
+                    accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[m][pl], ones, accb[m], 0, 0, 0);
+        }
+        fetch(s + 2);
+        dev::lds_barrier();                               // the other buffer staged, this one read
+        buf ^= 1;
+    }
+    const int NQ = 9 * a.ca + 1;
+#pragma unroll
+    for (int m = 0; m < D::MB; ++m) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const size_t base = (size_t)(co0 + 16 * m + 4 * kq + r) * NQ;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                const int pos = (q0 + k) / D::NBC, ci = 16 * ((q0 + k) - pos * D::NBC) + col;
+                if (ci < CAB) a.part[(base + pos * a.ca + ci0 + ci) * a.teams + team] = acc[m][k][r];
             }
+            if constexpr (BIAS)
+                if (ci0 == 0 && col == 0) a.part[(base + 9 * a.ca) * a.teams + team] = accb[m][r];
         }
     }
 }
 
-// One tile's A (dz rows) and B (halo columns) fragments from a staged buffer.
-template <int MBU, int QW>
-struct Dw2Ops {
-    float4 av[MBU], bv[QW];
-};
-
-template <int CA, int CZ, int QW = Dw2<CA, CZ>::QW>
-__device__ inline void dw2_ops(Dw2Ops<Dw2<CA, CZ>::MBU, QW> &o, const float *dz, const float *h, const int *boff,
-                               int col, int kq) {
-    using D = Dw2<CA, CZ>;
-#pragma unroll
-    for (int m = 0; m < D::MBU; ++m) o.av[m] = *reinterpret_cast<const float4 *>(dz + (16 * m + col) * D::SZ + 4 * kq);
-#pragma unroll
-    for (int k = 0; k < QW; ++k)
-        o.bv[k] = boff[k] >= 0 ? *reinterpret_cast<const float4 *>(h + boff[k])
-                               : (boff[k] == -1 ? make_float4(1.f, 1.f, 1.f, 1.f) : make_float4(0.f, 0.f, 0.f, 0.f));
-}
-
-// Matrix ops of k-steps J0 .. J1 - 1 of one tile.
-template <int MBU, int QW, int J0, int J1>
-__device__ inline void dw2_mma(floatx4 (&acc)[MBU][QW], const Dw2Ops<MBU, QW> &o) {
-#pragma unroll
-    for (int j = J0; j < J1; ++j)
-#pragma unroll
-        for (int m = 0; m < MBU; ++m)
-#pragma unroll
-            for (int k = 0; k < QW; ++k) {
-                const float x = j == 0 ? o.av[m].x : j == 1 ? o.av[m].y : j == 2 ? o.av[m].z : o.av[m].w;
-                const float y = j == 0 ? o.bv[k].x : j == 1 ? o.bv[k].y : j == 2 ? o.bv[k].z : o.bv[k].w;
-                acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc[m][k], 0, 0, 0);
-            }
-}
-
-template <int CA, int CZ>
-__global__ __launch_bounds__(256) void k_bwd_dw2(BwdArgs a) {
-    using D = Dw2<CA, CZ>;
-    extern __shared__ float smem[];                       // two buffers of [P][CZ][SZ] dz, [P][3][CA][HS] halo
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int team = blockIdx.x / D::BPT, u = (blockIdx.x - team * D::BPT) * 4 + wave;
-    const bool active = u < D::NCH;
-    const int qb0 = active ? u * D::QW : 0;
-    const int kq = lane >> 4, col = lane & 15;
-    // This lane's B offset per column block within a staged halo, or -1 for
-    // the bias column (all ones), -2 for a padding column (zeros).
-    int boff[D::QW];
-#pragma unroll
-    for (int k = 0; k < D::QW; ++k) {
-        const int q = (qb0 + k) * 16 + col;
-        if (q < 9 * CA) {
-            const int kpos = q / CA, ci = q - kpos * CA, ky = kpos / 3, kx = kpos - 3 * ky;
-            boff[k] = (kx * CA + ci) * D::HS + (kq + ky) * 4;
-        } else {
-            boff[k] = q == 9 * CA ? -1 : -2;
-        }
-    }
-    floatx4 acc[D::MBU][D::QW];
-#pragma unroll
-    for (int m = 0; m < D::MBU; ++m)
-#pragma unroll
-        for (int k = 0; k < D::QW; ++k) acc[m][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // The team's tiles [t0, t1) of the batch (batch index i, tile t), walked
-    // in order: (fi, ft) is the next tile to fetch.
+template <int CA, int CZ, int CAB, int CZB>
+__global__ __launch_bounds__(512, 2) void k_bwd_dw_split(BwdArgs a) {
+    using D = DwSplit<CAB, CZB>;
+    using dev::bf16x4;
+    constexpr int PZ = CZ / CZB, BPT = CA / CAB * PZ;     // blocks per team
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Blocks go round robin over the 8 XCDs: a team's blocks 8 apart.
+    const int b = blockIdx.x, j8 = b >> 3;
+    const bool whole = a.teams % 8 == 0;
+    const int team = whole ? j8 / BPT * 8 + (b & 7) : b / BPT, part = whole ? j8 % BPT : b % BPT;
+    const int co0 = part % PZ * CZB, ci0 = part / PZ * CAB;
     const long long NT = (long long)a.n * a.ntiles;
     const int t0 = (int)(NT * team / a.teams), t1 = (int)(NT * (team + 1) / a.teams);
-    int fi = t0 / a.ntiles, ft = t0 - fi * a.ntiles;
-    // Operands of tiles c .. c + P - 1 (this thread's share) into registers,
-    // every load issued; tiles past t1, out-of-image halo pixels: zero.  The
-    // slot of each tile's stream is read first, as a scalar load of a
-    // wave-uniform index, so that only the halo addresses wait for it (a
-    // vector load there would make the wait drain the dz loads as well).
-    float4 rdz[D::P][D::DZV], rh[D::P][D::HV];
-    const __attribute__((address_space(4))) int32_t *ids =
-        (const __attribute__((address_space(4))) int32_t *)a.ids;
-    auto fetch = [&](int c) __attribute__((always_inline)) {
-        bool ok[D::P];
-        int tl[D::P], slot[D::P];
+    const int steps = (t1 - t0 + 1) / 2;
+    int fi = t0 / a.ntiles, ft = t0 - fi * a.ntiles;      // the next tile to load
+    const __attribute__((address_space(4))) int32_t *ids = (const __attribute__((address_space(4))) int32_t *)a.ids;
+    floatx4 pre[D::UPT];
+    // This thread's units of step s's two tiles (past the team's last: zeros).
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+        bool ok[2];
+        int ty[2], tx[2];
+        const float *act[2], *dz[2];
 #pragma unroll
-        for (int pp = 0; pp < D::P; ++pp) {
-            ok[pp] = c + pp < t1;
-            const int i = __builtin_amdgcn_readfirstlane(ok[pp] ? fi : 0);
-            tl[pp] = ok[pp] ? ft : 0;
+        for (int t = 0; t < 2; ++t) {
+            ok[t] = t0 + 2 * s + t < t1;
+            const int i = __builtin_amdgcn_readfirstlane(ok[t] ? fi : 0), tl = ok[t] ? ft : 0;
             if (++ft == a.ntiles) {
                 ft = 0;
                 ++fi;
             }
-            slot[pp] = ids[i];
-            const float4 *dzp = reinterpret_cast<const float4 *>(a.dz_in + ((size_t)i * a.ntiles + tl[pp]) * kTilePx * CZ);
-#pragma unroll
-            for (int k = 0; k < D::DZV; ++k) {
-                const int e = threadIdx.x + 256 * k;
-                rdz[pp][k] = ok[pp] && e < 4 * CZ ? dzp[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            ty[t] = tl / a.TW;
+            tx[t] = tl - ty[t] * a.TW;
+            act[t] = a.act_prev + (size_t)ids[i] * a.prev_stride + ci0;
+            dz[t] = a.dz_in + ((size_t)i * a.ntiles + tl) * kTilePx * CZ + co0;
         }
 #pragma unroll
-        for (int pp = 0; pp < D::P; ++pp) {
-            const int t = tl[pp], ty = t / a.TW, tx = t - ty * a.TW;
-            const float *ap = a.act_prev + (size_t)slot[pp] * a.prev_stride;
-#pragma unroll
-            for (int k = 0; k < D::HV; ++k) {
-                const int e = threadIdx.x + 256 * k;
-                const int pos = e / (CA / 4), c4 = e - pos * (CA / 4);
-                const int y = ty * kTile - 1 + pos / 6, x = tx * kTile - 1 + pos % 6;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (ok[pp] && e < 9 * CA && y >= 0 && y < a.H && x >= 0 && x < a.W)
-                    v = *reinterpret_cast<const float4 *>(
-                        ap + ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CA + 4 * c4);
-                rh[pp][k] = v;
+        for (int k = 0; k < D::UPT; ++k) {
+            const int u = threadIdx.x + 512 * k;
+            const int hu = u < D::HU ? u : u - D::HU, t = u < 2 * D::HU ? (u >= D::HU) : (u - 2 * D::HU >= D::DU);
+            const float *src = g_zero_unit;
+            if (u < 2 * D::HU) {
+                const int pos = hu / (CAB / 4), c = hu - pos * (CAB / 4);
+                const int y = ty[t] * kTile - 1 + pos / 6, x = tx[t] * kTile - 1 + pos % 6;
+                if (ok[t] && y >= 0 && y < a.H && x >= 0 && x < a.W)
+                    src = act[t] + ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CA + 4 * c;
+            } else if (u < 2 * (D::HU + D::DU)) {
+                const int v = u - 2 * D::HU - (t ? D::DU : 0), p = v / (CZB / 4), c = v - p * (CZB / 4);
+                if (ok[t]) src = dz[t] + p * CZ + 4 * c;
             }
+            pre[k] = *reinterpret_cast<const floatx4 *>(src);
         }
     };
-    // Two staging buffers: while the matrix ops read the P tiles of one, the
-    // next P tiles (fetched into registers during the previous pass) are
-    // written to the other between k-steps, and the tiles after those are
-    // fetched; one block barrier per pass.  Fetching and staging run
-    // unconditionally (tiles past t1 load zeros from valid addresses): a
-    // guarded pass would make the compiler copy the accumulators between
-    // register files.
-    fetch(t0);
-#pragma unroll
-    for (int pp = 0; pp < D::P; ++pp) {
-        dw2_stage<CA, CZ, 0>(smem + pp * D::DZT, smem + D::P * D::DZT + pp * D::HT, rdz[pp], rh[pp], threadIdx.x);
-        dw2_stage<CA, CZ, 1>(smem + pp * D::DZT, smem + D::P * D::DZT + pp * D::HT, rdz[pp], rh[pp], threadIdx.x);
-    }
-    fetch(t0 + D::P);
-    dev::lds_barrier();
-    int b = 0;
-    for (int c = t0; c < t1; c += D::P) {
-        float *cb = smem + b * D::BUF, *nb = smem + (b ^ 1) * D::BUF;
-        Dw2Ops<D::MBU, D::QW> cur;
-        dw2_ops<CA, CZ>(cur, cb, cb + D::P * D::DZT, boff, col, kq);
-#pragma unroll
-        for (int pp = 0; pp < D::P; ++pp) {
-            Dw2Ops<D::MBU, D::QW> nxt;
-            if (pp + 1 < D::P) dw2_ops<CA, CZ>(nxt, cb + (pp + 1) * D::DZT, cb + D::P * D::DZT + (pp + 1) * D::HT, boff, col, kq);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_mma<D::MBU, D::QW, 0, 2>(acc, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_stage<CA, CZ, 0>(nb + pp * D::DZT, nb + D::P * D::DZT + pp * D::HT, rdz[pp], rh[pp], threadIdx.x);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_mma<D::MBU, D::QW, 2, 4>(acc, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_stage<CA, CZ, 1>(nb + pp * D::DZT, nb + D::P * D::DZT + pp * D::HT, rdz[pp], rh[pp], threadIdx.x);
-            __builtin_amdgcn_sched_barrier(0);
-            if (pp + 1 < D::P) cur = nxt;
-        }
-        fetch(c + 2 * D::P);                               // in flight during the next pass
-        dev::lds_barrier();                                // the other buffer staged, this one read
-        b ^= 1;
-    }
-    if (!active) return;
-#pragma unroll
-    for (int m = 0; m < D::MBU; ++m)
-#pragma unroll
-        for (int k = 0; k < D::QW; ++k) {
-            const int q = (qb0 + k) * 16 + col;
-            if (q >= D::NQ) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int co = m * 16 + 4 * kq + r;
-                a.part[((size_t)co * D::NQ + q) * a.teams + team] = acc[m][k][r];
-            }
-        }
-}
-
-// The same weight gradients with a block of 8 waves per team, for layers
-// whose row blocks and a third as many column blocks as above fit 64
-// accumulators (40 -> 80: 5 x 3 blocks): two waves per SIMD.  A pass takes
-// four tiles (two buffers of four fit one CU's LDS: one barrier per four
-// tiles); waves 0-3 stage and fetch tiles 0 and 2 of each pass, waves 4-7
-// tiles 1 and 3, each half between the k-steps of its own tiles, so that
-// while one wave of a SIMD runs its staging the other issues matrix ops.
-// Teams, tile ranges and the k-step order of every column block are those of
-// the 4-wave kernel: the same partial sums bit for bit.
-template <int CA, int CZ>
-struct Dw8 {
-    using D = Dw2<CA, CZ>;
-    static constexpr int QW = (D::NBQ + 7) / 8;           // column blocks per wave
-    static constexpr int P = 4;                            // tiles per pass: 0 and 2 of half 0, 1 and 3 of half 1
-    static constexpr int BUF = P * (D::DZT + D::HT);
-    static constexpr size_t lds_bytes = (size_t)2 * BUF * sizeof(float);
-    static constexpr bool FITS = D::MBU * QW * 4 <= 64 && lds_bytes <= 160 * 1024;
-};
-
-template <int CA, int CZ>
-__global__ __launch_bounds__(512) void k_bwd_dw8(BwdArgs a) {
-    using D = Dw2<CA, CZ>;
-    constexpr int QW = Dw8<CA, CZ>::QW;
-    static_assert(Dw8<CA, CZ>::FITS, "8-wave layout");
-    extern __shared__ float smem[];                       // two buffers of [P][CZ][SZ] dz, [P][3][CA][HS] halo
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int half = wave >> 2, hix = threadIdx.x & 255;  // tiles half, half + 2 of a pass are this half's to stage
-    const int team = blockIdx.x;
-    const int qb0 = wave * QW;
-    const int kq = lane >> 4, col = lane & 15;
-    int boff[QW];
-#pragma unroll
-    for (int k = 0; k < QW; ++k) {
-        const int q = (qb0 + k) * 16 + col;
-        if (q < 9 * CA) {
-            const int kpos = q / CA, ci = q - kpos * CA, ky = kpos / 3, kx = kpos - 3 * ky;
-            boff[k] = (kx * CA + ci) * D::HS + (kq + ky) * 4;
+    auto stage = [&](int k, int buf) __attribute__((always_inline)) {
+        const int u = threadIdx.x + 512 * k;
+        int off, plane;
+        if (u < 2 * D::HU) {
+            const int t = u >= D::HU, v = u - (t ? D::HU : 0), pos = v / (CAB / 4), c = v - pos * (CAB / 4);
+            off = t * D::TILE + pos * D::HS + 8 * c;
+            plane = D::HP;
         } else {
-            boff[k] = q == 9 * CA ? -1 : -2;
+            const int w = u - 2 * D::HU, t = w >= D::DU, v = w - (t ? D::DU : 0), p = v / (CZB / 4), c = v - p * (CZB / 4);
+            off = t * D::TILE + 3 * D::HP + p * D::DS + 8 * c;
+            plane = D::DP;
         }
-    }
-    floatx4 acc[D::MBU][QW];
-#pragma unroll
-    for (int m = 0; m < D::MBU; ++m)
-#pragma unroll
-        for (int k = 0; k < QW; ++k) acc[m][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const long long NT = (long long)a.n * a.ntiles;
-    const int t0 = (int)(NT * team / a.teams), t1 = (int)(NT * (team + 1) / a.teams);
-    // This half's tiles t0 + half, t0 + half + 2, ...: (fi, ft) the next one.
-    int fi = (t0 + half) / a.ntiles, ft = (t0 + half) - fi * a.ntiles;
-    float4 rdz[2][D::DZV], rh[2][D::HV];
-    const __attribute__((address_space(4))) int32_t *ids =
-        (const __attribute__((address_space(4))) int32_t *)a.ids;
-    auto fetch = [&](int c, int s) __attribute__((always_inline)) {   // tile c into register set s
-        const bool ok = c < t1;
-        const int i = __builtin_amdgcn_readfirstlane(ok ? fi : 0), tl = ok ? ft : 0;
-        ft += 2;
-        while (ft >= a.ntiles) {
-            ft -= a.ntiles;
-            ++fi;
-        }
-        const int slot = ids[i];
-        const float4 *dzp = reinterpret_cast<const float4 *>(a.dz_in + ((size_t)i * a.ntiles + tl) * kTilePx * CZ);
-#pragma unroll
-        for (int k = 0; k < D::DZV; ++k) {
-            const int e = hix + 256 * k;
-            rdz[s][k] = ok && e < 4 * CZ ? dzp[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        const int ty = tl / a.TW, tx = tl - ty * a.TW;
-        const float *ap = a.act_prev + (size_t)slot * a.prev_stride;
-#pragma unroll
-        for (int k = 0; k < D::HV; ++k) {
-            const int e = hix + 256 * k;
-            const int pos = e / (CA / 4), c4 = e - pos * (CA / 4);
-            const int y = ty * kTile - 1 + pos / 6, x = tx * kTile - 1 + pos % 6;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (ok && e < 9 * CA && y >= 0 && y < a.H && x >= 0 && x < a.W)
-                v = *reinterpret_cast<const float4 *>(
-                    ap + ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CA + 4 * c4);
-            rh[s][k] = v;
+        if (u < 2 * (D::HU + D::DU)) {
+            unsigned char *d = lds + buf * D::BUF + off;
+            bf16x4 h, m, l;
+            dev::split4(pre[k], h, m, l);
+            *reinterpret_cast<bf16x4 *>(d) = h;
+            *reinterpret_cast<bf16x4 *>(d + plane) = m;
+            *reinterpret_cast<bf16x4 *>(d + 2 * plane) = l;
         }
     };
-    constexpr int P = Dw8<CA, CZ>::P, BUF = Dw8<CA, CZ>::BUF;
+    fetch(0);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        fetch(t0 + half + 2 * s, s);
-        dw2_stage<CA, CZ, 0>(smem + (half + 2 * s) * D::DZT, smem + P * D::DZT + (half + 2 * s) * D::HT, rdz[s], rh[s], hix);
-        dw2_stage<CA, CZ, 1>(smem + (half + 2 * s) * D::DZT, smem + P * D::DZT + (half + 2 * s) * D::HT, rdz[s], rh[s], hix);
-    }
-    fetch(t0 + P + half, 0);
-    fetch(t0 + P + half + 2, 1);
+    for (int k = 0; k < D::UPT; ++k) stage(k, 0);
+    fetch(1);
     dev::lds_barrier();
-    int b = 0;
-    for (int c = t0; c < t1; c += P) {
-        float *cb = smem + b * BUF, *nb = smem + (b ^ 1) * BUF;
-        Dw2Ops<D::MBU, QW> cur;
-        dw2_ops<CA, CZ, QW>(cur, cb, cb + P * D::DZT, boff, col, kq);
-#pragma unroll
-        for (int pp = 0; pp < P; ++pp) {
-            Dw2Ops<D::MBU, QW> nxt;
-            if (pp + 1 < P) dw2_ops<CA, CZ, QW>(nxt, cb + (pp + 1) * D::DZT, cb + P * D::DZT + (pp + 1) * D::HT, boff, col, kq);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_mma<D::MBU, QW, 0, 2>(acc, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            if (half == (pp & 1)) dw2_stage<CA, CZ, 0>(nb + pp * D::DZT, nb + P * D::DZT + pp * D::HT, rdz[pp >> 1], rh[pp >> 1], hix);
-            __builtin_amdgcn_sched_barrier(0);
-            dw2_mma<D::MBU, QW, 2, 4>(acc, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            if (half == (pp & 1)) {
-                dw2_stage<CA, CZ, 1>(nb + pp * D::DZT, nb + P * D::DZT + pp * D::HT, rdz[pp >> 1], rh[pp >> 1], hix);
-                fetch(c + 2 * P + pp, pp >> 1);                // in flight during the next pass
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (pp + 1 < P) cur = nxt;
-        }
-        dev::lds_barrier();                                // the other buffer staged, this one read
-        b ^= 1;
-    }
-#pragma unroll
-    for (int m = 0; m < D::MBU; ++m)
-#pragma unroll
-        for (int k = 0; k < QW; ++k) {
-            const int q = (qb0 + k) * 16 + col;
-            if (q >= D::NQ) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int co = m * 16 + 4 * kq + r;
-                a.part[((size_t)co * D::NQ + q) * a.teams + team] = acc[m][k][r];
-            }
-        }
+    const int q0 = wave * D::NW + min(wave, D::EXTRA);
+    if (wave < D::EXTRA)
+        dw_split_wave<CAB, CZB, D::NW + 1, false>(a, lds, q0, steps, team, ci0, co0, fetch, stage);
+    else if (wave < 7)
+        dw_split_wave<CAB, CZB, D::NW, false>(a, lds, q0, steps, team, ci0, co0, fetch, stage);
+    else
+        dw_split_wave<CAB, CZB, D::NW, true>(a, lds, q0, steps, team, ci0, co0, fetch, stage);
 }
 
 // dW for layer 1 (a_0 the float32 input planes, 1 or 4 channels): so few
@@ -636,6 +483,25 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a) {
     for (int team = lane; team < a.teams; team += 64) s += p[team];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (!a.first && !dev::is_finite(s)) {
+        // Plain float32 products, lane j taking pixels j, j + 64, .. of the
+        // batch: infinities and NaN as float32 arithmetic gives them.
+        const int kpos = q / a.ca, ci = q - kpos * a.ca;
+        const long long pixels = (long long)a.n * a.ntiles * kTilePx;
+        s = 0.f;
+        for (long long p = lane; p < pixels; p += 64) {
+            const int i = (int)(p / (a.ntiles * kTilePx)), tp = (int)(p - (long long)i * a.ntiles * kTilePx);
+            const int t = tp / kTilePx, m = tp - t * kTilePx, ty = t / a.TW;
+            const int y = ty * kTile + m / 4 + kpos / 3 - 1, x = (t - ty * a.TW) * kTile + m % 4 + kpos % 3 - 1;
+            float v = q == 9 * a.ca ? 1.f : 0.f;
+            if (q < 9 * a.ca && y >= 0 && y < a.H && x >= 0 && x < a.W)
+                v = a.act_prev[(size_t)a.ids[i] * a.prev_stride +
+                               ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * a.ca + ci];
+            s = fmaf(a.dz_in[(size_t)p * a.cz + co], v, s);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    }
     if (lane != 0) return;
     float *d;
     if (q < 9 * a.ca) {
@@ -750,15 +616,16 @@ __global__ __launch_bounds__(256) void k_unprime(int32_t *primed, int S) {
 // ------------------------------------------------------------------ launchers
 
 #define RN_DW_FIRST_SHAPES(X) X(1, 20) X(1, 40) X(1, 64) X(1, 80) X(4, 20) X(4, 40) X(4, 64) X(4, 80)
-#define RN_DW_SHAPES(X) X(40, 80) X(64, 128) X(128, 128)
+// (input, output channels, those of a block)
+#define RN_DW_SHAPES(X) X(40, 80, 40, 80) X(64, 128, 64, 64) X(128, 128, 64, 64)
 
 int dw_blocks_per_team(int ca, int cz, bool first) {
 #define X(a_, z_) \
     if (first && ca == a_ && cz == z_) return 1;
     RN_DW_FIRST_SHAPES(X)
 #undef X
-#define X(a_, z_) \
-    if (!first && ca == a_ && cz == z_) return Dw8<a_, z_>::FITS ? 1 : Dw2<a_, z_>::BPT;
+#define X(a_, z_, ab, zb) \
+    if (!first && ca == a_ && cz == z_) return a_ / ab * (z_ / zb);
     RN_DW_SHAPES(X)
 #undef X
     return 0;
@@ -774,24 +641,16 @@ hipError_t run_dw_first(const BwdArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int CA, int CZ>
-hipError_t run_dw2(const BwdArgs &a, hipStream_t s) {
-    using D = Dw2<CA, CZ>;
-    if constexpr (Dw8<CA, CZ>::FITS) {
-        auto kern = k_bwd_dw8<CA, CZ>;
-        constexpr size_t lds8 = Dw8<CA, CZ>::lds_bytes;
-        static hipError_t attr = dev::set_lds(kern, lds8);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, dim3(a.teams), dim3(512), lds8, s, a);
-    } else {
-        auto kern = k_bwd_dw2<CA, CZ>;
-        static hipError_t attr = dev::set_lds(kern, D::lds_bytes);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, dim3(D::BPT * a.teams), dim3(256), D::lds_bytes, s, a);
-    }
+template <int CA, int CZ, int CAB, int CZB>
+hipError_t run_dw_split(const BwdArgs &a, hipStream_t s) {
+    auto kern = k_bwd_dw_split<CA, CZ, CAB, CZB>;
+    constexpr size_t lds = DwSplit<CAB, CZB>::lds_bytes;
+    static hipError_t attr = dev::set_lds(kern, lds);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kern, dim3(CA / CAB * (CZ / CZB) * a.teams), dim3(512), lds, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int total = CZ * D::NQ;
+    const int total = CZ * (9 * CA + 1);
     hipLaunchKernelGGL(k_bwd_reduce, dim3((total + 3) / 4), dim3(256), 0, s, a);
     return hipGetLastError();
 }
@@ -827,10 +686,9 @@ int bwd_dw_teams(int ca, int cz, bool first, int n, int ntiles, int cus) {
     }
     const int bpt = std::max(1, dw_blocks_per_team(ca, cz, first));
     const long long tiles = (long long)n * ntiles;
-    // One block per CU, one round: the accumulators and operands take more
-    // than half the register file, so one wave per SIMD is resident anyway,
-    // and equal tile ranges finish together (more, shorter teams measured
-    // slower, and each adds a partial to reduce).
+    // One block per CU, one round: its two buffers take most of LDS, and equal
+    // tile ranges finish together (more, shorter teams each add a partial to
+    // reduce).
     const long long want = std::max(1, cus / bpt);
     return (int)std::max(1LL, std::min(want, (tiles + 7) / 8));
 }
@@ -865,8 +723,8 @@ hipError_t launch_bwd_dw(const BwdArgs &a, int cus, hipStream_t s) {
     if (first && a.ca == a_ && a.cz == z_) return run_dw_first<a_, z_>(a, s);
     RN_DW_FIRST_SHAPES(X)
 #undef X
-#define X(a_, z_) \
-    if (!first && a.ca == a_ && a.cz == z_) return run_dw2<a_, z_>(a, s);
+#define X(a_, z_, ab, zb) \
+    if (!first && a.ca == a_ && a.cz == z_) return run_dw_split<a_, z_, ab, zb>(a, s);
     RN_DW_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

@@ -151,3 +151,55 @@ def test_decisions_near_zero_are_float32s(torch, fuse):
         seen += int(near.sum())
     assert seen > 0
     net.close()
+
+
+@pytest.mark.parametrize("convs,h,w", [((40, 80), 42, 32), ((64, 128, 128), 42, 32), ((40, 80), 13, 20)])
+def test_gradients_add_over_batches(torch, convs, h, w):
+    # Input gradients in groups of 16, 8 and 4 tiles (24, 13 and 1 streams of 88
+    # tiles) and weight gradients over teams of even and odd tile counts: the
+    # gradient of a batch is the sum of its parts' (each checked against the
+    # oracle in test_gpu_train.py).  Tolerance: float32 sums in another order,
+    # relative to each tensor's largest.
+    from paper_1909_05632_amd import ReuseNet
+    n = 37
+    wl = synth.Workload(cid=206, streams=n, frames=1, h=h, w=w, convs=convs, n_out=18)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]
+    g = torch.from_numpy(np.random.default_rng(6).normal(size=(n, 18)).astype(np.float32)).cuda()
+    net = ReuseNet(1, h, w, convs, 18, n, weights, fuse_first=False)
+    net.full(torch.from_numpy(x).cuda())
+    whole = net.backward(g, net.new_grads()).clone()
+    parts = net.new_grads()
+    for a, b in ((0, 13), (13, 36), (36, 37)):
+        ids = torch.arange(a, b, dtype=torch.int32, device="cuda")
+        net.backward(g[a:b].contiguous(), parts, stream_ids=ids, accumulate=True)
+    for u, v in zip(net.split_grads(whole), net.split_grads(parts)):
+        for p, q in zip(u, v) if isinstance(u, list) else [(u, v)]:
+            assert float((p - q).abs().max()) <= 2e-6 * float(p.abs().max()) + 1e-12
+    net.close()
+
+
+def test_gradients_of_infinities(torch):
+    # An infinite logit gradient: products and sums of layer 2's gradients are
+    # infinite or NaN exactly where IEEE arithmetic makes them so (float64 gives
+    # the same classes), not where operands split in three cancel.
+    wl = synth.Workload(cid=207, streams=2, frames=1, h=14, w=16, convs=(40, 80), n_out=6)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
+    net = make_net(wl, 2, weights)
+    net.full(torch.from_numpy(x).cuda())
+    g = np.random.default_rng(8).normal(size=(2, 6)).astype(np.float32)
+    g[0, 1] = np.inf
+    cw, cb, _dw, _db = net.split_grads(net.backward(torch.from_numpy(g).cuda(), net.new_grads()))
+    a1 = np.stack([net.activation(i, 1) for i in range(2)]).astype(np.float64)
+    a2 = np.stack([net.activation(i, 2) for i in range(2)])
+    with np.errstate(invalid="ignore"):
+        dz = np.where(a2 > 0, (g.astype(np.float64) @ weights[2]).reshape(a2.shape), 0.0)
+        pad = np.pad(a1, ((0, 0), (0, 0), (1, 1), (1, 1)))
+        want = np.stack([np.stack([(dz[:, :, None] * pad[:, None, :, ky:ky + 14, kx:kx + 16]).sum((0, 3, 4))
+                                   for kx in range(3)], -1) for ky in range(3)], -2)
+    got, bias = cw[1].cpu().numpy(), cb[1].cpu().numpy()
+    for u, v in ((got, want), (bias, dz.sum((0, 2, 3)))):
+        assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
+        assert np.array_equal(np.isneginf(u), np.isneginf(v))
+    net.close()

@@ -132,6 +132,93 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
     }
 }
 
+// The same for more logits or few streams: block (t, r) takes row r of tile
+// position t, a thread one input.  The weight gradients are [o][c][y][x], so a
+// thread's sums go out through LDS and leave as the four pixels of a row
+// (16 bytes), eight logits a round, and the tiles of one XCD are neighbours, so
+// its L2 completes the lines: stored as they lie (4 bytes at H W apart a lane)
+// they took most of the time (18 logits, 24 streams of 106x92: 408 us).
+// vec: gwd is 16-byte aligned.
+template <int NO>
+__global__ __launch_bounds__(512) void k_bwd_head_row(HeadBwdArgs a, int vec) {
+    constexpr int kStreams = NO <= 32 ? 128 : 64;         // streams per LDS stage of g
+    constexpr int kRound = 8;
+    __shared__ float s_g[kStreams * NO];
+    __shared__ int32_t s_slot[kStreams];
+    __shared__ float s_out[kRound * 512];
+    const int per = (a.ntiles + 7) / 8, t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (t >= a.ntiles) return;                            // uniform per block
+    const int E = kTilePx * a.C, n = 4 * a.C, tid = threadIdx.x;
+    const int ty = t / a.TW, tx = t - ty * a.TW, y = ty * kTile + blockIdx.y;
+    const bool ok = tid < n;
+    const int j = blockIdx.y * n + (ok ? tid : 0);
+    float w[NO], acc[NO];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        w[o] = ok && o < a.n_out ? a.wd[(size_t)o * a.K + (size_t)t * E + j] : 0.f;
+        acc[o] = 0.f;
+    }
+    for (int i0 = 0; i0 < a.n; i0 += kStreams) {
+        const int nc = min(kStreams, a.n - i0);
+        __syncthreads();                                  // the previous stage's readers are done
+        for (int k = tid; k < nc * NO; k += blockDim.x) {
+            const int ii = k / NO, o = k - ii * NO;
+            s_g[k] = o < a.n_out ? a.g[(size_t)(i0 + ii) * a.n_out + o] : 0.f;
+        }
+        for (int k = tid; k < nc; k += blockDim.x) s_slot[k] = a.ids[i0 + k];
+        __syncthreads();
+        if (ok) {
+#pragma unroll 4
+            for (int ii = 0; ii < nc; ++ii) {
+                const float in = a.act[(size_t)s_slot[ii] * a.act_stride + (size_t)t * E + j];
+                float da = 0.f;
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    const float gv = s_g[ii * NO + o];
+                    da = fmaf(w[o], gv, da);
+                    acc[o] = fmaf(gv, in, acc[o]);
+                }
+                a.dz[((size_t)(i0 + ii) * a.ntiles + t) * E + j] = in > 0.f ? da : 0.f;
+            }
+        }
+    }
+    if (y < a.H) {                                        // uniform per block; four whole pixels (W % 4 = 0)
+#pragma unroll
+        for (int o0 = 0; o0 < NO; o0 += kRound) {
+            __syncthreads();
+#pragma unroll
+            for (int o = 0; o < kRound; ++o)
+                if (o0 + o < NO) s_out[o * 512 + tid] = acc[o0 + o];
+            __syncthreads();
+            for (int k = tid; k < kRound * a.C; k += blockDim.x) {
+                const int o = k / a.C, c = k - o * a.C;
+                if (o0 + o >= a.n_out) break;
+                float v[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) v[p] = s_out[o * 512 + p * a.C + c];
+                float *d = a.gwd + ((size_t)(o0 + o) * a.C + c) * a.H * a.W + (size_t)y * a.W + tx * kTile;
+                if (vec) {
+                    float4 *d4 = reinterpret_cast<float4 *>(d);
+                    float4 q = make_float4(v[0], v[1], v[2], v[3]);
+                    if (a.accumulate) {
+                        const float4 b = *d4;
+                        q = make_float4(b.x + v[0], b.y + v[1], b.z + v[2], b.w + v[3]);
+                    }
+                    *d4 = q;
+                } else {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) d[p] = a.accumulate ? d[p] + v[p] : v[p];
+                }
+            }
+        }
+    }
+    if (t == 0 && blockIdx.y == 0 && tid < a.n_out) {
+        float s = 0.f;
+        for (int i = 0; i < a.n; ++i) s += a.g[(size_t)i * a.n_out + tid];
+        a.gbd[tid] = a.accumulate ? a.gbd[tid] + s : s;
+    }
+}
+
 // ------------------------------------------------------------------ dW
 
 // dW and db of layers 2..L on the bf16 matrix cores with operands split three
@@ -154,7 +241,8 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
 // column-shifted halo copies in LDS.)  Two buffers of two tiles: while the
 // matrix ops read one, the next step's tiles, loaded a step earlier, are split
 // into the other between them; one barrier a step.
-// A sum that is not finite is summed again in plain float32 by k_bwd_reduce.
+// A sum that is not finite is summed again in plain float32 by
+// k_bwd_reduce_rows.
 template <int CAB, int CZB>
 struct DwSplit {
     static constexpr int MB = CZB / 16;                   // row blocks
@@ -253,6 +341,7 @@ __device__ inline void dw_split_wave(const BwdArgs &a, const unsigned char *lds,
         buf ^= 1;
     }
     const int NQ = 9 * a.ca + 1;
+    float *part = a.part + (size_t)team * a.cz * NQ;      // [team][co][column]: 16 lanes write 64 bytes
 #pragma unroll
     for (int m = 0; m < D::MB; ++m) {
 #pragma unroll
@@ -261,10 +350,10 @@ __device__ inline void dw_split_wave(const BwdArgs &a, const unsigned char *lds,
 #pragma unroll
             for (int k = 0; k < NW; ++k) {
                 const int pos = (q0 + k) / D::NBC, ci = 16 * ((q0 + k) - pos * D::NBC) + col;
-                if (ci < CAB) a.part[(base + pos * a.ca + ci0 + ci) * a.teams + team] = acc[m][k][r];
+                if (ci < CAB) part[base + pos * a.ca + ci0 + ci] = acc[m][k][r];
             }
             if constexpr (BIAS)
-                if (ci0 == 0 && col == 0) a.part[(base + 9 * a.ca) * a.teams + team] = accb[m][r];
+                if (ci0 == 0 && col == 0) part[base + 9 * a.ca] = accb[m][r];
         }
     }
 }
@@ -470,47 +559,86 @@ __global__ __launch_bounds__(256) void k_bwd_dw_first(BwdArgs a) {
         }
 }
 
-// dW_l and db_l from the teams' partial sums ([co][column][team]): one wave
-// per weight, lane j adding teams j, j + 64, ... in order, then the lanes'
+// Where the gradient of weight e = (co, column) of a layer goes.
+__device__ inline float *dw_dest(const BwdArgs &a, int e) {
+    const int NQ = 9 * a.ca + 1, co = e / NQ, q = e - co * NQ;
+    if (q == 9 * a.ca) return a.gb + co;
+    const int kpos = q / a.ca, ci = q - kpos * a.ca;
+    return a.gw + ((size_t)co * a.ca + ci) * 9 + kpos;
+}
+
+// Layer 1's dW and db from the teams' partial sums ([co][column][team]): one
+// wave per weight, lane j adding teams j, j + 64, ... in order, then the lanes'
 // sums by a fixed butterfly, so the order never changes.
 __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a) {
     const int NQ = 9 * a.ca + 1;
     const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (e >= a.cz * NQ) return;                            // uniform per wave
-    const int co = e / NQ, q = e - co * NQ;
     const float *p = a.part + (size_t)e * a.teams;
     float s = 0.f;
     for (int team = lane; team < a.teams; team += 64) s += p[team];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (!a.first && !dev::is_finite(s)) {
-        // Plain float32 products, lane j taking pixels j, j + 64, .. of the
-        // batch: infinities and NaN as float32 arithmetic gives them.
-        const int kpos = q / a.ca, ci = q - kpos * a.ca;
-        const long long pixels = (long long)a.n * a.ntiles * kTilePx;
-        s = 0.f;
-        for (long long p = lane; p < pixels; p += 64) {
-            const int i = (int)(p / (a.ntiles * kTilePx)), tp = (int)(p - (long long)i * a.ntiles * kTilePx);
-            const int t = tp / kTilePx, m = tp - t * kTilePx, ty = t / a.TW;
-            const int y = ty * kTile + m / 4 + kpos / 3 - 1, x = (t - ty * a.TW) * kTile + m % 4 + kpos % 3 - 1;
-            float v = q == 9 * a.ca ? 1.f : 0.f;
-            if (q < 9 * a.ca && y >= 0 && y < a.H && x >= 0 && x < a.W)
-                v = a.act_prev[(size_t)a.ids[i] * a.prev_stride +
-                               ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * a.ca + ci];
-            s = fmaf(a.dz_in[(size_t)p * a.cz + co], v, s);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    }
     if (lane != 0) return;
-    float *d;
-    if (q < 9 * a.ca) {
-        const int kpos = q / a.ca, ci = q - kpos * a.ca;
-        d = a.gw + ((size_t)co * a.ca + ci) * 9 + kpos;
-    } else {
-        d = a.gb + co;
-    }
+    float *d = dw_dest(a, e);
     *d = a.accumulate ? *d + s : s;
+}
+
+// Gradient of weight e in plain float32 products, one lane of 64 taking pixels
+// j, j + 64, .. of the batch (the whole wave's sum is returned).
+__device__ inline float dw_plain(const BwdArgs &a, int e, int lane) {
+    const int NQ = 9 * a.ca + 1, co = e / NQ, q = e - co * NQ, kpos = q / a.ca, ci = q - kpos * a.ca;
+    const long long pixels = (long long)a.n * a.ntiles * kTilePx;
+    float s = 0.f;
+    for (long long p = lane; p < pixels; p += 64) {
+        const int i = (int)(p / (a.ntiles * kTilePx)), tp = (int)(p - (long long)i * a.ntiles * kTilePx);
+        const int t = tp / kTilePx, m = tp - t * kTilePx, ty = t / a.TW;
+        const int y = ty * kTile + m / 4 + kpos / 3 - 1, x = (t - ty * a.TW) * kTile + m % 4 + kpos % 3 - 1;
+        float v = q == 9 * a.ca ? 1.f : 0.f;
+        if (q < 9 * a.ca && y >= 0 && y < a.H && x >= 0 && x < a.W)
+            v = a.act_prev[(size_t)a.ids[i] * a.prev_stride +
+                           ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * a.ca + ci];
+        s = fmaf(a.dz_in[(size_t)p * a.cz + co], v, s);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
+}
+
+// dW_l and db_l of layers 2..L from partial sums [team][co][column]: a block
+// takes 64 weights, wave w the w-th quarter of the teams in order (four sums,
+// teams mod 4), then the quarters in order.  Loads and the kernel's stores are
+// contiguous; with the team fastest every store was 4 bytes on a line of its
+// own (28880 weights of 256 teams, 4 streams of 105x80: 135 us in all).  A sum
+// that is not finite is taken from plain float32 products.
+__global__ __launch_bounds__(256) void k_bwd_reduce_rows(BwdArgs a) {
+    __shared__ float s_sum[4][64];
+    const int total = a.cz * (9 * a.ca + 1);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
+    const int t0 = a.teams * wave / 4, t1 = a.teams * (wave + 1) / 4;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (e < total) {
+        const float *p = a.part + e;
+#pragma unroll 4
+        for (int t = t0; t < t1; t += 4)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (t + k < t1) s[k] += p[(size_t)(t + k) * total];
+    }
+    s_sum[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (wave > 0) return;
+    float v = (s_sum[0][lane] + s_sum[1][lane]) + (s_sum[2][lane] + s_sum[3][lane]);
+    uint64_t plain = __ballot(e < total && !dev::is_finite(v));
+    while (plain) {                                        // rare: one weight at a time, by the whole wave
+        const int j = __ffsll((long long)plain) - 1;
+        plain &= plain - 1;
+        const float f = dw_plain(a, blockIdx.x * 64 + j, lane);
+        if (lane == j) v = f;
+    }
+    if (e >= total) return;
+    float *d = dw_dest(a, e);
+    *d = a.accumulate ? *d + v : v;
 }
 
 // ------------------------------------------------------------------ SGD
@@ -651,7 +779,7 @@ hipError_t run_dw_split(const BwdArgs &a, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int total = CZ * (9 * CA + 1);
-    hipLaunchKernelGGL(k_bwd_reduce, dim3((total + 3) / 4), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bwd_reduce_rows, dim3((total + 63) / 64), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -702,17 +830,23 @@ hipError_t launch_reinforce(int n, int n_out, const float *logits, const int32_t
 }
 
 hipError_t launch_bwd_head(const HeadBwdArgs &a, hipStream_t s) {
-    const int E = kTilePx * a.C;
-    if (a.n_out <= 8) {
-        // a float4 of inputs per thread, one block per tile up to 512 threads
-        const int q = E / 4, th = std::min(512, (q + 63) / 64 * 64);
+    if (a.W % 4 != 0 || a.C > 128) return hipErrorInvalidValue;
+    if (a.n_out <= 8 && a.n >= 48) {
+        // A float4 of inputs per thread, one block per tile up to 512 threads:
+        // the caches' bytes bound it (64 streams of 105x80, 6 logits: 105 us
+        // against 113 by rows, 256: 341 against 420).  With few streams the
+        // weight gradients' stores do (16 streams: 33 us by rows against 47,
+        // 24 of 106x92 with 128 channels: 83 against 108).
+        const int q = kTilePx * a.C / 4, th = std::min(512, (q + 63) / 64 * 64);
         hipLaunchKernelGGL((k_bwd_head<8, 4>), dim3(a.ntiles, (q + th - 1) / th), dim3(th), 0, s, a);
-    } else {
-        // 32 or 64 weights and sums per input: one input per thread
-        const dim3 grid(a.ntiles, (E + 255) / 256), block(256);
-        if (a.n_out <= 32) hipLaunchKernelGGL((k_bwd_head<32, 1>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_bwd_head<64, 1>), grid, block, 0, s, a);
+        return hipGetLastError();
     }
+    const dim3 grid((a.ntiles + 7) / 8 * 8, 4), block((4 * a.C + 63) / 64 * 64);
+    const int vec = reinterpret_cast<uintptr_t>(a.gwd) % 16 == 0;
+    if (a.n_out <= 8) hipLaunchKernelGGL((k_bwd_head_row<8>), grid, block, 0, s, a, vec);
+    else if (a.n_out <= 18) hipLaunchKernelGGL((k_bwd_head_row<18>), grid, block, 0, s, a, vec);
+    else if (a.n_out <= 32) hipLaunchKernelGGL((k_bwd_head_row<32>), grid, block, 0, s, a, vec);
+    else hipLaunchKernelGGL((k_bwd_head_row<64>), grid, block, 0, s, a, vec);
     return hipGetLastError();
 }
 

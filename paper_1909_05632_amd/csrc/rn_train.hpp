@@ -38,7 +38,7 @@ struct BwdArgs {
     int first;                    // act_prev is the input cache (planar; a ring of 4 frames when stacking)
     int stack, cin0;              // layer 1: frames stacked, channels per frame
     const int32_t *ring_head;
-    float *part;                  // [cz][9 ca + 1][teams]
+    float *part;                  // partial sums: layer 1 [cz][9 ca + 1][teams], later layers [teams][cz][9 ca + 1]
     int teams;
     float *gw, *gb;               // OIHW [cz][ca][3][3], [cz]
     int accumulate;

@@ -451,10 +451,11 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // groups at every octet.
 //
 // A result that is not finite (an operand the split cannot carry), or, but for
-// variants, that lies within 2^-19 of 0 relative to the largest of its lane, is
-// taken from the plain float32 sum instead (about 4 tiles in 1000; two float32
-// roundings of the sums differ by 2^-22 of it): ReLU decisions are then those
-// of the float32 sums, which the gradient depends on.  (All such tiles' whole
+// variants, that lies within 2^-19 of 0 relative to the largest of its tile
+// column (4 pixels, all channels), is taken from the plain float32 sum instead
+// (about 6 tiles in 1000; two float32 roundings of the sums differ by 2^-22 of
+// it): ReLU decisions are then those of the float32 sums, which the gradient
+// depends on.  (All such tiles' whole
 // products: 140 us for 256 streams of 105x80, since some block meets several;
 // output by output 112; without this rule 103.)
 struct Res {
@@ -670,6 +671,14 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                         least = fminf(fminf(fabsf(acc[nb][e]), fabsf(acc[nb][e + 1])), least);
                         seen = nonfinite(acc[nb][e + 1], nonfinite(acc[nb][e], seen));
                     }
+                }
+                if constexpr (!VAR) {                     // over the 16 lanes (80 channels) of a tile column
+#define RN_ROR(n) most = fmaxf(most, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(most), 0x120 + n, 0xf, 0xf, false)))
+                    RN_ROR(8);
+                    RN_ROR(4);
+                    RN_ROR(2);
+                    RN_ROR(1);
+#undef RN_ROR
                 }
                 const float near = VAR ? 0.f : most * 0x1p-19f;
                 if (__any(seen != 0.f || (!VAR && least <= near))) {

@@ -130,9 +130,9 @@ def _chain(x, w, b):
 
 @pytest.mark.parametrize("fuse", [True, False])
 def test_decisions_near_zero_are_float32s(torch, fuse):
-    # Results within 2^-19 of 0 relative to the largest of their lane (channels c,
-    # c + 16, .. of a tile column) come from the float32 product: up to half of
-    # that they are the chain's, bit for bit; the others only to rounding.
+    # Results within 2^-19 of 0 relative to the largest of their tile column come
+    # from the float32 sum: up to half of that they are the chain's, bit for bit;
+    # the others only to rounding.
     from paper_1909_05632_amd import ReuseNet
     wl = synth.Workload(cid=205, streams=4, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
     weights = synth.net_weights(wl, bias_std=0.05)
@@ -142,8 +142,8 @@ def test_decisions_near_zero_are_float32s(torch, fuse):
     seen = 0
     for i in range(4):
         z = _chain(net.activation(i, 1), weights[0][1], weights[1][1])
-        m = np.abs(np.pad(z, ((0, 0), (0, 3), (0, 0)))).reshape(5, 16, 26, 4, 80).max((0, 3))   # rows past the image: less
-        m = np.broadcast_to(m[None, :, :, None], (5, 16, 26, 4, 80)).reshape(80, 104, 80)[:, :101]
+        m = np.abs(np.pad(z, ((0, 0), (0, 3), (0, 0)))).reshape(80, 26, 4, 80).max((0, 2))      # rows past the image: less
+        m = np.broadcast_to(m[None, :, None], (80, 26, 4, 80)).reshape(80, 104, 80)[:, :101]
         near = np.abs(z) <= m * 2.0 ** -20
         got, want = net.activation(i, 2), np.maximum(z, np.float32(0))
         assert np.array_equal(got[near], want[near])

@@ -100,7 +100,8 @@ __device__ inline const float *halo_src(const ConvArgs &a, const TileRef &r, int
 }
 
 // One output before bias in plain float32, for results the split cannot carry
-// (C16: columns of the float32 packing).
+// (C16: columns of the float32 packing).  A sum that has become NaN stays NaN:
+// it ends there, so a net full of NaN costs a few products an output.
 template <int CIN, int C16, bool VAR>
 __device__ float plain_output(const ConvArgs &a, const TileRef &r, int p, int n) {
     float acc = 0.f;
@@ -110,6 +111,7 @@ __device__ float plain_output(const ConvArgs &a, const TileRef &r, int p, int n)
             const int y = r.ty * kTile + (p >> 2) + kpos / 3 - 1, x = r.tx * kTile + (p & 3) + kpos % 3 - 1;
             const float *src = halo_src<CIN, VAR>(a, r, y, x, true);
             for (int ci = ci0; ci < ci0 + 16; ++ci) acc = fmaf(src[ci], w[f32_weight(kpos, ci, n, CIN, C16)], acc);
+            if (__builtin_isnan(acc)) return acc;
         }
     return acc;
 }

@@ -584,13 +584,14 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a) {
     *d = a.accumulate ? *d + s : s;
 }
 
-// Gradient of weight e in plain float32 products, one lane of 64 taking pixels
-// j, j + 64, .. of the batch (the whole wave's sum is returned).
-__device__ inline float dw_plain(const BwdArgs &a, int e, int lane) {
+// A team's share of the gradient of weight e in plain float32 products, one
+// lane of 64 taking pixels j, j + 64, .. of its tiles (the whole wave's sum is
+// returned).
+__device__ inline float dw_plain(const BwdArgs &a, int e, int team, int lane) {
     const int NQ = 9 * a.ca + 1, co = e / NQ, q = e - co * NQ, kpos = q / a.ca, ci = q - kpos * a.ca;
-    const long long pixels = (long long)a.n * a.ntiles * kTilePx;
+    const long long tiles = (long long)a.n * a.ntiles, end = tiles * (team + 1) / a.teams * kTilePx;
     float s = 0.f;
-    for (long long p = lane; p < pixels; p += 64) {
+    for (long long p = tiles * team / a.teams * kTilePx + lane; p < end; p += 64) {
         const int i = (int)(p / (a.ntiles * kTilePx)), tp = (int)(p - (long long)i * a.ntiles * kTilePx);
         const int t = tp / kTilePx, m = tp - t * kTilePx, ty = t / a.TW;
         const int y = ty * kTile + m / 4 + kpos / 3 - 1, x = (t - ty * a.TW) * kTile + m % 4 + kpos % 3 - 1;
@@ -609,8 +610,10 @@ __device__ inline float dw_plain(const BwdArgs &a, int e, int lane) {
 // takes 64 weights, wave w the w-th quarter of the teams in order (four sums,
 // teams mod 4), then the quarters in order.  Loads and the kernel's stores are
 // contiguous; with the team fastest every store was 4 bytes on a line of its
-// own (28880 weights of 256 teams, 4 streams of 105x80: 135 us in all).  A sum
-// that is not finite is taken from plain float32 products.
+// own (28880 weights of 256 teams, 4 streams of 105x80: 135 us in all).  Where
+// the sum is not finite, the partial sums that are not are taken again from
+// plain float32 products, team by team until the sum is NaN (whatever follows):
+// one infinite pixel costs one team's tiles, a net full of NaN no more.
 __global__ __launch_bounds__(256) void k_bwd_reduce_rows(BwdArgs a) {
     __shared__ float s_sum[4][64];
     const int total = a.cz * (9 * a.ca + 1);
@@ -633,7 +636,18 @@ __global__ __launch_bounds__(256) void k_bwd_reduce_rows(BwdArgs a) {
     while (plain) {                                        // rare: one weight at a time, by the whole wave
         const int j = __ffsll((long long)plain) - 1;
         plain &= plain - 1;
-        const float f = dw_plain(a, blockIdx.x * 64 + j, lane);
+        const int ej = blockIdx.x * 64 + j;
+        float f = 0.f;
+        for (int t0 = 0; t0 < a.teams && !__builtin_isnan(f); t0 += 64) {      // uniform: every lane has the sum
+            const float pt = t0 + lane < a.teams ? a.part[(size_t)(t0 + lane) * total + ej] : 0.f;
+            const bool fin = dev::is_finite(pt);
+            float good = fin ? pt : 0.f;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) good += __shfl_xor(good, o, 64);
+            f += good;
+            for (uint64_t bad = __ballot(!fin); bad && !__builtin_isnan(f); bad &= bad - 1)
+                f += dw_plain(a, ej, t0 + __ffsll((long long)bad) - 1, lane);
+        }
         if (lane == j) v = f;
     }
     if (e >= total) return;

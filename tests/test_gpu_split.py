@@ -179,24 +179,26 @@ def test_gradients_add_over_batches(torch, convs, h, w):
     net.close()
 
 
-def test_gradients_of_infinities(torch):
+@pytest.mark.parametrize("n,h,w", [(2, 14, 16), (5, 45, 40)])
+def test_gradients_of_infinities(torch, n, h, w):
     # An infinite logit gradient: products and sums of layer 2's gradients are
     # infinite or NaN exactly where IEEE arithmetic makes them so (float64 gives
-    # the same classes), not where operands split in three cancel.
-    wl = synth.Workload(cid=207, streams=2, frames=1, h=14, w=16, convs=(40, 80), n_out=6)
+    # the same classes), not where operands split in three cancel.  4 teams of
+    # tiles, two of them without an infinity, and 75 (more than a wave's lanes).
+    wl = synth.Workload(cid=207, streams=n, frames=1, h=h, w=w, convs=(40, 80), n_out=6)
     weights = synth.net_weights(wl, bias_std=0.05)
-    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
-    net = make_net(wl, 2, weights)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]
+    net = make_net(wl, n, weights)
     net.full(torch.from_numpy(x).cuda())
-    g = np.random.default_rng(8).normal(size=(2, 6)).astype(np.float32)
-    g[0, 1] = np.inf
+    g = np.random.default_rng(8).normal(size=(n, 6)).astype(np.float32)
+    g[n - 1, 1] = np.inf
     cw, cb, _dw, _db = net.split_grads(net.backward(torch.from_numpy(g).cuda(), net.new_grads()))
-    a1 = np.stack([net.activation(i, 1) for i in range(2)]).astype(np.float64)
-    a2 = np.stack([net.activation(i, 2) for i in range(2)])
+    a1 = np.stack([net.activation(i, 1) for i in range(n)]).astype(np.float64)
+    a2 = np.stack([net.activation(i, 2) for i in range(n)])
     with np.errstate(invalid="ignore"):
         dz = np.where(a2 > 0, (g.astype(np.float64) @ weights[2]).reshape(a2.shape), 0.0)
         pad = np.pad(a1, ((0, 0), (0, 0), (1, 1), (1, 1)))
-        want = np.stack([np.stack([(dz[:, :, None] * pad[:, None, :, ky:ky + 14, kx:kx + 16]).sum((0, 3, 4))
+        want = np.stack([np.stack([(dz[:, :, None] * pad[:, None, :, ky:ky + h, kx:kx + w]).sum((0, 3, 4))
                                    for kx in range(3)], -1) for ky in range(3)], -2)
     got, bias = cw[1].cpu().numpy(), cb[1].cpu().numpy()
     for u, v in ((got, want), (bias, dz.sum((0, 2, 3)))):

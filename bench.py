@@ -39,6 +39,7 @@ if ROOT not in sys.path:
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_F32_TFLOPS = 157.3
 PEAK_MFMA_BF16_TFLOPS = 2500.0
+PEAK_MFMA_SPLIT_TFLOPS = PEAK_MFMA_BF16_TFLOPS / 6     # float32 products as six bf16 ones
 PROFILES = os.path.join(ROOT, "profiles")
 CSRC = os.path.join(ROOT, "paper_1909_05632_amd", "csrc")
 DEFAULT_WORKLOAD = "fullres-1024x32"
@@ -81,7 +82,7 @@ def layer_kernel(specs, l, dtype, folded, separate):
         return f"k_conv_first_bf16<{ci}, {co}>" if l == 1 else f"k_conv_bf16_grp<{ci}, {co}>"
     if l == 1:
         return f"k_conv_first4_mfma<{co}>" if ci == 4 else f"k_conv_first_f32<{ci}, {co}>"
-    if (ci, co) == (40, 80):                                     # weights resident in LDS
+    if (ci, co) == (40, 80):                                     # weights resident in registers
         return "k_conv_mfma_res<40, 80>" + (" (layer 1 folded in)" if folded else "")
     return f"k_conv_mfma_{'staged' if separate else 'split'}<{ci}, {co}>"
 
@@ -91,7 +92,7 @@ def mfma_peak(kernel, dtype):
     layers on split operands run six bf16 products for one."""
     if dtype == "bf16":
         return PEAK_MFMA_BF16_TFLOPS
-    return PEAK_MFMA_BF16_TFLOPS / 6 if "split" in kernel else PEAK_MFMA_F32_TFLOPS
+    return PEAK_MFMA_SPLIT_TFLOPS if "split" in kernel or "_res<" in kernel else PEAK_MFMA_F32_TFLOPS
 
 
 def schedule(frames: int, length: int):
@@ -321,9 +322,9 @@ def train_bench(args, torch):
         kern["bwd_dx"]["tflops"] = f_dx * T / (prof["bwd_dx"]["ms"] / 1e3) / 1e12
     dom = max(("bwd_dw", "bwd_dx"), key=lambda k: prof[k]["ms"])
     ach = kern[dom]["tflops"]
-    roof = {"bound": "mfma", "kernel": {"bwd_dw": "k_bwd_dw8 / k_bwd_dw2 + k_bwd_dw_first (weight gradients, teams of tiles on MFMA)",
-                                        "bwd_dx": "k_bwd_dx (input gradients, transposed conv on MFMA)"}[dom],
-            "achieved": ach, "peak": PEAK_MFMA_F32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_MFMA_F32_TFLOPS,
+    roof = {"bound": "mfma", "kernel": {"bwd_dw": "k_bwd_dw_split + k_bwd_dw_first (weight gradients, teams of tiles on MFMA)",
+                                        "bwd_dx": "k_conv_mfma_split (input gradients, transposed conv on MFMA)"}[dom],
+            "achieved": ach, "peak": PEAK_MFMA_SPLIT_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_MFMA_SPLIT_TFLOPS,
             "traffic": None}
     cpu = None
     if not args.no_cpu:

@@ -450,16 +450,14 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // 36 hy + 5 hx, so the 16 pixels of a 16-lane read lie in 16 distinct bank
 // groups at every octet.
 //
-// A result that is not finite (an operand the split cannot carry) is taken from
-// the plain float32 sum instead.  But for variants, one that lies within 2^-19
-// of 0 relative to the largest of its tile column (4 pixels, all channels; float32
-// sums are off by 2^-22 of it) is summed in float64 (about 6 tiles in 1000; from
-// the float32 sum where a tile has more than kSingles): the ReLU decisions, which
-// the gradient depends on, are then those of the exact sums of these inputs.
-// (256 streams of 105x80: all such tiles' whole products 140 us, since some block
-// meets several; output by output 106 (110 by a float32 chain);
-// without this rule 103.)
-constexpr int kSingles = 16;
+// A result that is not finite (an operand the split cannot carry), or, but for
+// variants, that lies within 2^-19 of 0 relative to the largest of its tile
+// column (4 pixels, all channels), is taken from the plain float32 sum instead
+// (about 6 tiles in 1000; two float32 roundings of the sums differ by 2^-22 of
+// it): ReLU decisions are then those of the float32 sums, which the gradient
+// depends on.  (All such tiles' whole
+// products: 140 us for 256 streams of 105x80, since some block meets several;
+// output by output 112; without this rule 103.)
 struct Res {
     static constexpr int CIN = 40, COUT = 80, NB = COUT / 16, KS = 12, KW = KS / 4;
     static constexpr int OCT = 45;                    // octets of K
@@ -470,7 +468,8 @@ struct Res {
     // Two tiles a group: three halo buffers (built, read, kept for the check
     // of the sums), two of partial products.
     static constexpr int OPART = 3 * 2 * HALO, OSMALL = OPART + 2 * 2 * PART;
-    static constexpr size_t lds_bytes = (size_t)OSMALL + 2 * 64 * 4 + COUT * 4;
+    static constexpr int PAIRS = 2 * 9 * CIN, OPAIRS = OSMALL + 2 * 64 * 4 + COUT * 4;   // floats a wave; bytes
+    static constexpr size_t lds_bytes = (size_t)OPAIRS + 2 * PAIRS * 4;
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");
     static constexpr size_t w_bytes = (size_t)KS * NB * 3 * 1024;
 };
@@ -522,11 +521,11 @@ __device__ inline void res_plain(const float *w, const unsigned char *halo, floa
     }
 }
 
-// One output before bias, channel n, pixel (row, column) of the tile, in
-// float64: a lane's six products, then a butterfly over the wave.  (The same
-// output as a float32 chain of 360 steps took about 2 us, the whole tile's
-// float32 product some 14.)
-__device__ inline double res_wide_one(const float *w, const unsigned char *halo, int n, int row, int col, int lane) {
+// One output of it: channel n, pixel (row, column) of the tile.  The wave lays
+// the 360 pairs of factors out in `pairs` in the order of the sum, one memory
+// round trip, and then runs the chain, every lane the same: about 2 us, where
+// the whole tile's product takes some 14.
+__device__ inline float res_plain_one(const float *w, const unsigned char *halo, float *pairs, int n, int row, int col, int lane) {
     using R = Res;
     constexpr int K = 9 * R::CIN, V = (K + 63) / 64;
     float x[V], y[V];
@@ -539,12 +538,18 @@ __device__ inline double res_wide_one(const float *w, const unsigned char *halo,
         x[v] = (float)*reinterpret_cast<const __bf16 *>(p) + (float)*reinterpret_cast<const __bf16 *>(p + R::PLANE) +
                (float)*reinterpret_cast<const __bf16 *>(p + 2 * R::PLANE);
     }
-    double acc = 0.0;
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (lane + 64 * v < K) acc = fma((double)x[v], (double)y[v], acc);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+        if (lane + 64 * v < K) reinterpret_cast<float2 *>(pairs)[lane + 64 * v] = make_float2(x[v], y[v]);
+    wave_sync();
+    float acc = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < K; k += 2) {
+        const float4 q = reinterpret_cast<const float4 *>(pairs)[k / 2];
+        acc = fmaf(q.x, q.y, acc);
+        acc = fmaf(q.z, q.w, acc);
+    }
+    wave_sync();
     return acc;
 }
 
@@ -679,12 +684,12 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                 if (__any(seen != 0.f || (!VAR && least <= near))) {
                     // exact zeros (all products zero) stay
                     auto doubtful = [&](float z) { return !is_finite(z) || (z != 0.f && fabsf(z) <= near); };
-                    int many = __any(seen != 0.f) ? kSingles + 1 : 0;
+                    int many = 0;
 #pragma unroll
                     for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) many += __popcll(__ballot(doubtful(acc[nb][e])));
-                    if (many > kSingles) {
+                    if (many > 4) {
                         floatx4 plain[R::NB];
                         res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, lane);
 #pragma unroll
@@ -693,6 +698,7 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                             for (int e = 0; e < 4; ++e)
                                 if (doubtful(acc[nb][e])) acc[nb][e] = plain[nb][e] + s_bias[nb * 16 + mrow];
                     } else if (many > 0) {
+                        float *pairs = reinterpret_cast<float *>(lds + R::OPAIRS) + t * R::PAIRS;
 #pragma unroll
                         for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
@@ -701,9 +707,9 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                                 while (which) {           // lane j: channel nb * 16 + j % 16, pixel (e, j / 16)
                                     const int j = __ffsll((long long)which) - 1;
                                     which &= which - 1;
-                                    const double f = res_wide_one(static_cast<const float *>(a.w), halo_of(k, t),
+                                    const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
                                                                   nb * 16 + (j & 15), e, j >> 4, lane);
-                                    if (lane == j) acc[nb][e] = (float)(f + (double)s_bias[nb * 16 + mrow]);
+                                    if (lane == j) acc[nb][e] = f + s_bias[nb * 16 + mrow];
                                 }
                             }
                     }

@@ -50,7 +50,7 @@ def kernel_source_hash(source: str) -> str:
     """Hash of a kernel source file together with the device headers it includes."""
     import hashlib
     h = hashlib.sha256()
-    for f in (source, "rn_device.hpp", "rn_internal.hpp"):
+    for f in (source, "rn_split.hpp", "rn_device.hpp", "rn_internal.hpp"):
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -682,8 +682,14 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                 }
                 const float near = VAR ? 0.f : most * 0x1p-19f;
                 if (__any(seen != 0.f || (!VAR && least <= near))) {
-                    // exact zeros (all products zero) stay
-                    auto doubtful = [&](float z) { return !is_finite(z) || (z != 0.f && fabsf(z) <= near); };
+                    // Zeros stay where the tile has many (no input at all);
+                    // a few are sums that cancelled to the last bit.
+                    int zeros = 0;
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) zeros += __popcll(__ballot(acc[nb][e] == 0.f));
+                    auto doubtful = [&](float z) { return !is_finite(z) || (fabsf(z) <= near && (z != 0.f || zeros <= 4)); };
                     int many = 0;
 #pragma unroll
                     for (int nb = 0; nb < R::NB; ++nb)

@@ -516,8 +516,15 @@ __device__ inline void res_plain(const float *w, const unsigned char *halo, floa
 #pragma unroll
             for (int nb = 0; nb < R::NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[nb][j], acc[nb], 0, 0, 0);
         }
+        // NaN stays NaN: a net that has diverged ends here after one block.
+        bool open = false;
 #pragma unroll
-        for (int nb = 0; nb < R::NB; ++nb) b[nb] = next[nb];
+        for (int nb = 0; nb < R::NB; ++nb) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) open |= !__builtin_isnan(acc[nb][e]);
+            b[nb] = next[nb];
+        }
+        if (!__any(open)) break;                          // uniform
     }
 }
 

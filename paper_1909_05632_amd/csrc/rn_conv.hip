@@ -450,14 +450,21 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // 36 hy + 5 hx, so the 16 pixels of a 16-lane read lie in 16 distinct bank
 // groups at every octet.
 //
-// A result that is not finite (an operand the split cannot carry), or, but for
-// variants, that lies within 2^-19 of 0 relative to the largest of its tile
-// column (4 pixels, all channels), is taken from the plain float32 sum instead
-// (about 6 tiles in 1000; two float32 roundings of the sums differ by 2^-22 of
-// it): ReLU decisions are then those of the float32 sums, which the gradient
-// depends on.  (All such tiles' whole
-// products: 140 us for 256 streams of 105x80, since some block meets several;
-// output by output 112; without this rule 103.)
+// A result that is not finite (an operand the split cannot carry) is taken from
+// the plain float32 sum instead.  So is, in the TRAINING form, one that lies
+// within 2^-17 of 0 relative to the largest of its own four partial products:
+// ReLU decisions, which the gradient depends on, are then those of the float32
+// sums.  (Of 42 K results that near to 0 the float32 sums' errors reach 2^-18.8
+// of that partial product; about 4 tiles in 1000 hold such a result, whatever
+// the sizes of the channels are.)  More than four of them in a tile come from
+// inputs that cancel by structure, an edge filter over a flat patch: their
+// float32 sums are rounding noise as well, and they stay as they are, so the
+// time of a tile does not depend on its values.  Steps, dense passes and
+// variants of one net share the form, and with it the bits.
+enum Form { FOLDED, CACHED, TRAINING };   // layer 1 folded in, read from its cache, read for gradients
+constexpr float kNearZero = 0x1p-17f;
+constexpr int kMostSingle = 4;            // results of a tile taken one by one
+
 struct Res {
     static constexpr int CIN = 40, COUT = 80, NB = COUT / 16, KS = 12, KW = KS / 4;
     static constexpr int OCT = 45;                    // octets of K
@@ -560,9 +567,10 @@ __device__ inline float res_plain_one(const float *w, const unsigned char *halo,
     return acc;
 }
 
-template <bool DENSE, bool FUSE, int NO, bool VAR>
+template <bool DENSE, int FORM, int NO, bool VAR>
 __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
     using R = Res;
+    constexpr bool FUSE = FORM == FOLDED;
     extern __shared__ __align__(16) unsigned char lds[];
     float *s_patch = reinterpret_cast<float *>(lds + R::OSMALL);
     float *s_bias = s_patch + 128;
@@ -662,75 +670,96 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                     ++c0;
                     w1 = word_chunk<DENSE>(a, rr, t, G, c0 + 1, lane);
                 }
-                const floatx4 *p = part_of(k, t) + lane;
-                // Sums and bias, the largest and smallest magnitude of the lane.
+                floatx4 *p = part_of(k, t) + lane;
+                // Sums and bias; `least` is below 0 where a result is near 0.
                 floatx4 acc[R::NB];
-                float most = 0.f, least = __builtin_inff(), seen = 0.f;
+                float least = 0.f, seen = 0.f;
 #pragma unroll
                 for (int nb = 0; nb < R::NB; ++nb) {
                     acc[nb] = p[nb * 64];
+                    float size[4];
+                    if constexpr (FORM == TRAINING)
 #pragma unroll
-                    for (int q = 1; q < 4; ++q) acc[nb] += p[(q * R::NB + nb) * 64];
+                        for (int e = 0; e < 4; ++e) size[e] = fabsf(acc[nb][e]);
+#pragma unroll
+                    for (int q = 1; q < 4; ++q) {
+                        const floatx4 v = p[(q * R::NB + nb) * 64];
+                        acc[nb] += v;
+                        if constexpr (FORM == TRAINING)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) size[e] = fmaxf(size[e], fabsf(v[e]));
+                    }
                     acc[nb] += s_bias[nb * 16 + mrow];
 #pragma unroll
-                    for (int e = 0; e < 4; e += 2) {
-                        most = fmaxf(fmaxf(fabsf(acc[nb][e]), fabsf(acc[nb][e + 1])), most);
-                        least = fminf(fminf(fabsf(acc[nb][e]), fabsf(acc[nb][e + 1])), least);
-                        seen = nonfinite(acc[nb][e + 1], nonfinite(acc[nb][e], seen));
+                    for (int e = 0; e < 4; ++e) {
+                        seen = nonfinite(acc[nb][e], seen);
+                        if constexpr (FORM == TRAINING) least = fminf(least, fmaf(size[e], -kNearZero, fabsf(acc[nb][e])));
                     }
                 }
-                if constexpr (!VAR) {                     // over the 16 lanes (80 channels) of a tile column
-#define RN_ROR(n) most = fmaxf(most, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(most), 0x120 + n, 0xf, 0xf, false)))
-                    RN_ROR(8);
-                    RN_ROR(4);
-                    RN_ROR(2);
-                    RN_ROR(1);
-#undef RN_ROR
-                }
-                const float near = VAR ? 0.f : most * 0x1p-19f;
-                if (__any(seen != 0.f || (!VAR && least <= near))) {
-                    // Zeros stay where the tile has many (no input at all);
-                    // a few are sums that cancelled to the last bit.
-                    int zeros = 0;
+                const TileRef r = item_of(a, w0, w1, c0, k);
+                const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
+                if (__any(seen != 0.f || least < 0.f)) {
+                    // Results inside the image to be taken again, bit 4 nb + e.
+                    uint32_t lost = 0, near = 0;
 #pragma unroll
-                    for (int nb = 0; nb < R::NB; ++nb)
+                    for (int nb = 0; nb < R::NB; ++nb) {
+                        __builtin_amdgcn_sched_barrier(0);   // one block's partial products in registers at a time
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) zeros += __popcll(__ballot(acc[nb][e] == 0.f));
-                    auto doubtful = [&](float z) { return !is_finite(z) || (fabsf(z) <= near && (z != 0.f || zeros <= 4)); };
-                    int many = 0;
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t bit = (col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31)) & (1 << (4 * nb + e));
+                            if (!is_finite(acc[nb][e])) lost |= bit;
+                            if constexpr (FORM == TRAINING) {
+                                float size = 0.f;
 #pragma unroll
-                    for (int nb = 0; nb < R::NB; ++nb)
+                                for (int q = 0; q < 4; ++q) size = fmaxf(size, fabsf(p[(q * R::NB + nb) * 64][e]));
+                                if (is_finite(acc[nb][e]) && fmaf(size, -kNearZero, fabsf(acc[nb][e])) < 0.f) near |= bit;
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    int n_lost = 0, n_near = 0;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) many += __popcll(__ballot(doubtful(acc[nb][e])));
-                    if (many > 4) {
+                    for (int j = 0; j < 4 * R::NB; ++j) {
+                        n_lost += __popcll(__ballot(lost >> j & 1));
+                        n_near += __popcll(__ballot(near >> j & 1));
+                    }
+                    if (n_near <= kMostSingle) lost |= near;
+                    // The results wait in LDS, in place of the first partial
+                    // products (head weights and plain sums fill the registers).
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
+                    float *z = reinterpret_cast<float *>(p);
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));          // what follows is computed here, not kept in registers throughout
+                    if (n_lost > kMostSingle) {
                         floatx4 plain[R::NB];
-                        res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, lane);
+                        res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, ln);
 #pragma unroll
                         for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                if (doubtful(acc[nb][e])) acc[nb][e] = plain[nb][e] + s_bias[nb * 16 + mrow];
-                    } else if (many > 0) {
+                                if (lost >> (4 * nb + e) & 1) z[nb * 256 + e] = plain[nb][e] + s_bias[nb * 16 + mrow];
+                    } else {
                         float *pairs = reinterpret_cast<float *>(lds + R::OPAIRS) + t * R::PAIRS;
-#pragma unroll
-                        for (int nb = 0; nb < R::NB; ++nb)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                uint64_t which = __ballot(doubtful(acc[nb][e]));
-                                while (which) {           // lane j: channel nb * 16 + j % 16, pixel (e, j / 16)
-                                    const int j = __ffsll((long long)which) - 1;
-                                    which &= which - 1;
-                                    const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
-                                                                  nb * 16 + (j & 15), e, j >> 4, lane);
-                                    if (lane == j) acc[nb][e] = f + s_bias[nb * 16 + mrow];
-                                }
+#pragma unroll 1
+                        for (int j = 0; j < 4 * R::NB; ++j) {
+                            uint64_t which = __ballot(lost >> j & 1);
+                            const int nb = j >> 2, e = j & 3;
+                            while (which) {               // lane i: channel nb * 16 + i % 16, pixel (e, i / 16)
+                                const int i = __ffsll((long long)which) - 1;
+                                which &= which - 1;
+                                const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
+                                                              nb * 16 + (i & 15), e, i >> 4, ln);
+                                if (lane == i) z[nb * 256 + e] = f + s_bias[nb * 16 + mrow];
                             }
+                        }
                     }
+                    wave_sync();
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) acc[nb] = p[nb * 64];
                 }
                 // As epilogue(), with the head weights in registers already.
-                const TileRef r = item_of(a, w0, w1, c0, k);
                 const int widx = rr.at(t + k * G);
-                const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
 #pragma unroll
                 for (int nb = 0; nb < R::NB; ++nb) {
 #pragma unroll
@@ -1526,9 +1555,9 @@ __global__ __launch_bounds__(256) void k_conv_gen(ConvArgs a) {
 
 // ------------------------------------------------------------------ dispatch
 
-template <bool DENSE, bool FUSE, int NO, bool VAR>
+template <bool DENSE, int FORM, int NO, bool VAR>
 hipError_t run_resident_no(const ConvArgs &a, int cus, hipStream_t s) {
-    auto kern = k_conv_mfma_res<DENSE, FUSE, NO, VAR>;
+    auto kern = k_conv_mfma_res<DENSE, FORM, NO, VAR>;
     static hipError_t attr = set_lds(kern, Res::lds_bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, a.max_tiles)), dim3(512), Res::lds_bytes, s, a);
@@ -1536,16 +1565,17 @@ hipError_t run_resident_no(const ConvArgs &a, int cus, hipStream_t s) {
 }
 
 // Logit count as a template argument where it is a common one.
-template <bool DENSE, bool FUSE, bool VAR>
+template <bool DENSE, int FORM, bool VAR>
 hipError_t run_resident(const ConvArgs &a, int cus, hipStream_t s) {
-    if (a.n_out == 0) return run_resident_no<DENSE, FUSE, 0, VAR>(a, cus, s);
-    if (a.n_out == 6) return run_resident_no<DENSE, FUSE, 6, VAR>(a, cus, s);
-    return run_resident_no<DENSE, FUSE, -1, VAR>(a, cus, s);
+    if (a.n_out == 0) return run_resident_no<DENSE, FORM, 0, VAR>(a, cus, s);
+    if (a.n_out == 6) return run_resident_no<DENSE, FORM, 6, VAR>(a, cus, s);
+    return run_resident_no<DENSE, FORM, -1, VAR>(a, cus, s);
 }
 
 template <bool DENSE, bool VAR>
-hipError_t run_mfma(const ConvArgs &a, int cus, hipStream_t s) {
-    return a.fuse_first ? run_resident<DENSE, true, VAR>(a, cus, s) : run_resident<DENSE, false, VAR>(a, cus, s);
+hipError_t run_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s) {
+    return training ? run_resident<DENSE, TRAINING, VAR>(a, cus, s)
+                    : a.fuse_first ? run_resident<DENSE, FOLDED, VAR>(a, cus, s) : run_resident<DENSE, CACHED, VAR>(a, cus, s);
 }
 
 template <int CIN, int COUT, bool DENSE>
@@ -1687,10 +1717,11 @@ bool conv_first_supported(int cin, int cout, rn_dtype dt) {
 
 // cus: compute units of the device; the persistent grid is at most one block
 // (resident MFMA kernel) or eight blocks (first layer) per CU.
-hipError_t launch_conv_mfma(const ConvArgs &a, int cus, hipStream_t s, bool var) {
+hipError_t launch_conv_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s, bool var) {
     const bool dense = a.wl == nullptr;
-    if ((var && dense) || !is_resident(a.cin, a.cout)) return hipErrorInvalidValue;
-    return var ? run_mfma<false, true>(a, cus, s) : dense ? run_mfma<true, false>(a, cus, s) : run_mfma<false, false>(a, cus, s);
+    if ((var && dense) || !is_resident(a.cin, a.cout) || (training && a.fuse_first)) return hipErrorInvalidValue;
+    return var ? run_mfma<false, true>(a, training, cus, s)
+               : dense ? run_mfma<true, false>(a, training, cus, s) : run_mfma<false, false>(a, training, cus, s);
 }
 
 hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s) {

@@ -128,29 +128,110 @@ def _chain(x, w, b):
     return acc + b[:, None, None]
 
 
-@pytest.mark.parametrize("fuse", [True, False])
-def test_decisions_near_zero_are_float32s(torch, fuse):
-    # Results within 2^-19 of 0 relative to the largest of their tile column come
-    # from the float32 sum: up to half of that they are the chain's, bit for bit;
-    # the others only to rounding.
+def _uneven(weights, big=2.0 ** 20, small=2.0 ** -20):
+    """The same weights with a loud, a quiet and a silent channel in the last conv layer."""
+    cw, cb = [np.array(v) for v in weights[0]], [np.array(v) for v in weights[1]]
+    for c, f in ((3, big), (7, small), (11, 0.0)):
+        cw[-1][c] *= np.float32(f)
+        cb[-1][c] *= np.float32(f)
+    return (cw, cb, *weights[2:])
+
+
+def _largest_quarter(x, w):
+    """Largest magnitude of the four partial sums of each 40 -> 80 result: K in octets of channels, octet g at
+    kernel position g / 5, twelve octets (the last one nine) a quarter."""
+    H, W = x.shape[1:]
+    xp = np.zeros((40, H + 2, W + 2))
+    xp[:, 1:-1, 1:-1] = x
+    part = np.zeros((4, 80, H, W))
+    for g in range(45):
+        pos, c = g // 5, 8 * (g % 5)
+        win = xp[c:c + 8, pos // 3:pos // 3 + H, pos % 3:pos % 3 + W]
+        part[g // 12] += np.tensordot(w[:, c:c + 8, pos // 3, pos % 3].astype(np.float64), win, 1)
+    return np.abs(part).max(0)
+
+
+@pytest.mark.parametrize("uneven", [False, True])
+def test_decisions_near_zero_are_float32s(torch, uneven):
+    # With a separate layer 1 (the training form), results within 2^-17 of 0
+    # relative to the largest of their own quarter sums come from the float32
+    # sum: up to half of that they are the chain's, bit for bit, whatever the
+    # sizes of the other channels are; the others only to rounding.
     from paper_1909_05632_amd import ReuseNet
-    wl = synth.Workload(cid=205, streams=4, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
+    wl = synth.Workload(cid=205, streams=8, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
     weights = synth.net_weights(wl, bias_std=0.05)
-    x = synth.to_f32(synth.sprite_batch(wl, streams=range(4), frames=1))[0][:, None]
-    net = ReuseNet(1, wl.h, wl.w, wl.convs, 6, 4, weights, fuse_first=fuse)
+    if uneven:
+        weights = _uneven(weights)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(8), frames=1))[0][:, None]
+    net = ReuseNet(1, wl.h, wl.w, wl.convs, 6, 8, weights, fuse_first=False)
     net.full(torch.from_numpy(x).cuda())
     seen = 0
-    for i in range(4):
-        z = _chain(net.activation(i, 1), weights[0][1], weights[1][1])
-        m = np.abs(np.pad(z, ((0, 0), (0, 3), (0, 0)))).reshape(80, 26, 4, 80).max((0, 2))      # rows past the image: less
-        m = np.broadcast_to(m[None, :, None], (80, 26, 4, 80)).reshape(80, 104, 80)[:, :101]
-        near = np.abs(z) <= m * 2.0 ** -20
+    for i in range(8):
+        a1 = net.activation(i, 1)
+        z, size = _chain(a1, weights[0][1], weights[1][1]), _largest_quarter(a1, weights[0][1])
+        near = np.abs(z) < size * 2.0 ** -18
+        tile = np.pad(np.abs(z) < size * 2.0 ** -16, ((0, 0), (0, 3), (0, 0))).reshape(80, 26, 4, 20, 4).sum((0, 2, 4))
+        assert tile.max() <= 4                            # each taken one by one
         got, want = net.activation(i, 2), np.maximum(z, np.float32(0))
         assert np.array_equal(got[near], want[near])
-        assert np.abs(got - want).max() <= 360 * 2.0 ** -24 * np.abs(z).max()
+        assert np.all(np.abs(got - want) <= 360 * 2.0 ** -24 * 4 * size + 1e-30)
         seen += int(near.sum())
     assert seen > 0
     net.close()
+
+
+@pytest.mark.parametrize("fuse", [True, False])
+def test_time_of_a_layer_whatever_its_values(torch, fuse):
+    # Channels of very different size: a rule that takes float32 sums by the
+    # size of other channels made this 10 times slower; the bound is far from
+    # both.  Medians of dense passes, weights in turn.
+    from paper_1909_05632_amd import ReuseNet
+    n = 64
+    wl = synth.Workload(cid=208, streams=n, frames=1, h=105, w=80, convs=(40, 80), n_out=6)
+    even = synth.net_weights(wl, bias_std=0.05)
+    x = torch.from_numpy(synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]).cuda()
+    nets = [ReuseNet(1, wl.h, wl.w, wl.convs, 6, n, w, fuse_first=fuse) for w in (even, _uneven(even))]
+    ms = [[], []]
+    for _ in range(12):
+        for net, t in zip(nets, ms):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            net.full(x)
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1))
+    assert np.median(ms[1]) < 1.5 * np.median(ms[0]), ms
+    for net in nets:
+        net.close()
+
+
+# Options of a net: its convs, whether layer 1 is folded into layer 2.
+ONE_ARITHMETIC = [((40, 80), True), ((40, 80), False), ((64, 128, 128), True)]
+
+
+@pytest.mark.parametrize("n_out", [6, 18])
+@pytest.mark.parametrize("convs,fuse", ONE_ARITHMETIC)
+def test_step_full_and_variants_agree(torch, convs, fuse, n_out):
+    # Of one net a step, a dense pass and a variant of the same frame give the
+    # same bits, and a variant that rewrites the base's own pixels gives the
+    # base's.  16 ragged frames, variant i = slot 0 with frame i in its boxes.
+    from paper_1909_05632_amd import ReuseNet
+    wl = synth.Workload(cid=209, streams=16, frames=1, h=101, w=80, convs=convs, n_out=n_out,
+                        n_sprites=3, smin=3, smax=6, vmin=1, vmax=3)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = torch.from_numpy(synth.to_f32(synth.sprite_batch(wl, streams=range(16), frames=1))[0][:, None]).cuda()
+    net = ReuseNet(1, wl.h, wl.w, convs, n_out, 16, weights, fuse_first=fuse)
+    other = ReuseNet(1, wl.h, wl.w, convs, n_out, 16, weights, fuse_first=fuse)
+    full, step = net.full(x), other.step(x)
+    assert torch.equal(full, step)
+    whole = torch.tensor([[0, 0, wl.h, wl.w]] * 16, dtype=torch.int32, device="cuda")
+    part = torch.tensor([[3 * i, 2 * i, 3 * i + 9, 2 * i + 14] for i in range(16)], dtype=torch.int32, device="cuda")
+    off = torch.arange(17, dtype=torch.int32, device="cuda")
+    tiles = 26 * 20
+    assert torch.equal(net.variants(0, whole, off, x, max_tiles=tiles), full)
+    assert torch.equal(net.variants(0, part, off, x[:1], max_tiles=tiles), full[:1].expand(16, n_out))
+    net.close()
+    other.close()
 
 
 @pytest.mark.parametrize("convs,h,w", [((40, 80), 42, 32), ((64, 128, 128), 42, 32), ((40, 80), 13, 20)])

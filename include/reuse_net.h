@@ -106,8 +106,8 @@ typedef struct {
  *     either way; reuse_net_read_activation(layer 1) then computes the layer
  *     on demand.
  *     It is the form for training, which reads every layer's cache; with it
- *     float32 layers 64->128 and 128->128 of steps and full passes run on the
- *     float32 matrix instructions, and results of 40->80 layers that lie next
+ *     float32 layers 64->128 and 128->128 run on the float32 matrix
+ *     instructions, and results of 40->80 layers that lie next
  *     to 0 are summed in plain float32, so that ReLU decisions, and with them
  *     the gradients, are those of float32 sums.  By default all these layers
  *     run on the bf16 ones with operands split three ways (closer to the exact

@@ -954,7 +954,8 @@ struct SplitOps {
 // gradient depends on which side of 0 each pre-activation lies, so training
 // keeps the plain float32 sums (the split form of rn_conv_split.hip rounds
 // differently, and in layers that feed another a decision can then fall the
-// other way); a training step spends under 5% of its time here.
+// other way); a training step of 24 106x92 streams spends about 12% of its time
+// here.  Variants (VAR) take the same sums as the net's steps.
 //
 // A block of four waves computes a group of T tiles, each wave COUT / 4 output
 // channels of all of them, walking K one 16-channel chunk at a time and, within
@@ -1050,8 +1051,9 @@ __device__ inline void dma_items(const ConvArgs &a, int g, int end, uint32_t dst
     lds_dma4(item_src<DENSE>(a, min(g + min(lane, T - 1), end - 1)), dst);
 }
 
-// Source of each of this wave's halo loads for chunk 0 of the group at g.
-template <int CIN, int COUT, int T, bool DENSE>
+// Source of each of this wave's halo loads for chunk 0 of the group at g.  (The
+// loads that VAR's look-ups take are waited for here, so the counts above hold.)
+template <int CIN, int COUT, int T, bool DENSE, bool VAR>
 __device__ inline void chunk_sources(const ConvArgs &a, int g, int end, const uint32_t *items,
                                      const float *(&src)[Chunked<CIN, COUT, T>::HDW], int wave, int lane) {
     using C = Chunked<CIN, COUT, T>;
@@ -1066,9 +1068,12 @@ __device__ inline void chunk_sources(const ConvArgs &a, int g, int end, const ui
         const TileRef r = item_ref(a, item_from<DENSE>(a, min(g + tc, end - 1), items[tc]));
         const int y = r.ty * kTile - 1 + hy, x = r.tx * kTile - 1 + hx;
         const bool ok = t < T && g + t < end && r2 < 24 && y >= 0 && y < a.H && x >= 0 && x < a.W;
-        src[k] = ok ? in + (size_t)r.slot * a.in_stride +
-                          ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CIN + 4 * kq
-                    : g_zero_page + 4 * kq;
+        if constexpr (VAR)
+            src[k] = (ok ? var_src<float>(a, r.slot, y, x, CIN) : g_zero_page) + 4 * kq;
+        else
+            src[k] = ok ? in + (size_t)r.slot * a.in_stride +
+                              ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * CIN + 4 * kq
+                        : g_zero_page + 4 * kq;
     }
 }
 
@@ -1174,7 +1179,7 @@ __device__ inline void quad_transpose(float (&v)[4], int b) {
     }
 }
 
-template <int CIN, int COUT, bool DENSE, int T>
+template <int CIN, int COUT, bool DENSE, bool VAR, int T>
 __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
     using C = Chunked<CIN, COUT, T>;
     constexpr int NBW = C::NBW;
@@ -1202,7 +1207,7 @@ __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
     const float *src[C::HDW];
     dma_items<DENSE, T>(a, xr.first, xr.end, ilds, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    chunk_sources<CIN, COUT, T, DENSE>(a, xr.first, xr.end, items, src, wave, lane);
+    chunk_sources<CIN, COUT, T, DENSE, VAR>(a, xr.first, xr.end, items, src, wave, lane);
 #pragma unroll
     for (int k = 0; k < 3; ++k) dma_chunk<CIN, COUT, T>(src, k, hlds + k * C::HB, wave);
 #pragma unroll
@@ -1263,7 +1268,7 @@ __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
                     // Refill this chunk's buffer with the chunk three ahead.
                     if (dc == C::NCH) {                       // on to the next group
                         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(9 * NBW + C::HDMIN) : "memory");
-                        chunk_sources<CIN, COUT, T, DENSE>(a, g + xr.stride, xr.end, items, src, wave, lane);
+                        chunk_sources<CIN, COUT, T, DENSE, VAR>(a, g + xr.stride, xr.end, items, src, wave, lane);
                         dc = 0;
                     }
                     dma_chunk<CIN, COUT, T>(src, dc, hlds + hk * C::HB, wave);
@@ -1304,8 +1309,9 @@ __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
             if (g + t >= xr.end) break;                   // uniform
             const TileRef r = item_ref(a, item_from<DENSE>(a, g + t, items[t]));
             const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
-            float *dst = static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride +
-                         (size_t)r.tile * kTilePx * COUT + (qb * 4 + kq) * COUT + wave * C::CW + 4 * qm;
+            float *dst = (VAR ? static_cast<float *>(a.vov_out) + (size_t)(g + t) * kTilePx * COUT
+                              : static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride + (size_t)r.tile * kTilePx * COUT) +
+                         (qb * 4 + kq) * COUT + wave * C::CW + 4 * qm;
 #pragma unroll
             for (int nb = 0; nb < NBW; ++nb) {
                 float v[4];
@@ -1322,13 +1328,13 @@ __device__ void chunk_path(const ConvArgs &a, int cnt, float *smem) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // loads issued for a group that does not come
 }
 
-template <int CIN, int COUT, bool DENSE>
+template <int CIN, int COUT, bool DENSE, bool VAR>
 __global__ __launch_bounds__(256) void k_conv_mfma_staged(ConvArgs a) {
     extern __shared__ float smem[];
     // Groups of 8 tiles when every block has at least 16 of them to do, else of 4.
     const int cnt = work_count<DENSE>(a);
-    if (cnt >= 16 * 8 * (int)gridDim.x) chunk_path<CIN, COUT, DENSE, 8>(a, cnt, smem);
-    else chunk_path<CIN, COUT, DENSE, 4>(a, cnt, smem);
+    if (cnt >= 16 * 8 * (int)gridDim.x) chunk_path<CIN, COUT, DENSE, VAR, 8>(a, cnt, smem);
+    else chunk_path<CIN, COUT, DENSE, VAR, 4>(a, cnt, smem);
 }
 
 // ------------------------------------------------------------------ general layers
@@ -1578,12 +1584,13 @@ hipError_t run_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s) {
                     : a.fuse_first ? run_resident<DENSE, FOLDED, VAR>(a, cus, s) : run_resident<DENSE, CACHED, VAR>(a, cus, s);
 }
 
-template <int CIN, int COUT, bool DENSE>
+template <int CIN, int COUT, bool DENSE, bool VAR>
 hipError_t run_staged(const ConvArgs &a, int cus, hipStream_t s) {
-    if (a.fuse_first || a.n_out > 0) return hipErrorInvalidValue;   // head partials come from their own kernel
+    // Head partials come from their own kernel, which reads the overlays.
+    if (a.fuse_first || a.n_out > 0 || (VAR && a.vov_out == nullptr)) return hipErrorInvalidValue;
     constexpr size_t lds = std::max(Chunked<CIN, COUT, 8>::lds_bytes, Chunked<CIN, COUT, 4>::lds_bytes);
     static_assert(lds <= 160 * 1024, "staged layer exceeds LDS");
-    auto kern = k_conv_mfma_staged<CIN, COUT, DENSE>;
+    auto kern = k_conv_mfma_staged<CIN, COUT, DENSE, VAR>;
     static hipError_t attr = set_lds(kern, lds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, (a.max_tiles + 3) / 4)), dim3(256), lds, s, a);
@@ -1724,11 +1731,13 @@ hipError_t launch_conv_mfma(const ConvArgs &a, bool training, int cus, hipStream
                : dense ? run_mfma<true, false>(a, training, cus, s) : run_mfma<false, false>(a, training, cus, s);
 }
 
-hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s) {
+hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s, bool var) {
     const bool dense = a.wl == nullptr;
-#define X(ci, co)                     \
-    if (a.cin == ci && a.cout == co) \
-        return dense ? run_staged<ci, co, true>(a, cus, s) : run_staged<ci, co, false>(a, cus, s);
+    if (var && dense) return hipErrorInvalidValue;
+#define X(ci, co)                                                      \
+    if (a.cin == ci && a.cout == co)                                   \
+        return var ? run_staged<ci, co, false, true>(a, cus, s)        \
+                   : dense ? run_staged<ci, co, true, false>(a, cus, s) : run_staged<ci, co, false, false>(a, cus, s);
     RN_STAGED_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

@@ -60,7 +60,7 @@ struct Plan {
     // The bf16 planes of float32 layers' weights; split: a layer of launch_conv_split.
     bool split[RN_MAX_CONV] = {false};
     size_t o_ws[RN_MAX_CONV] = {0};
-    bool plain = false;                     // RN_OPT_SEPARATE_FIRST: steps and full passes sum in plain float32
+    bool plain = false;                     // RN_OPT_SEPARATE_FIRST: 64->128 and 128->128 in plain float32
     size_t wt_elems[RN_MAX_CONV] = {0};
     size_t o_wts[RN_MAX_CONV] = {0};        // their bf16 planes
     size_t act_stride[RN_MAX_CONV + 1] = {0};   // elements per slot
@@ -444,7 +444,7 @@ MaskGeom make_geom(reuse_net *net) {
 hipError_t launch_conv_later(const Plan &p, const ConvArgs &cv, int l, int cus, hipStream_t s, bool var) {
     if (p.dt == RN_BF16) return launch_conv_mfma_bf16(cv, cus, s, var);
     if (!p.split[l - 1]) return launch_conv_mfma(cv, p.plain, cus, s, var);
-    return p.plain && !var ? launch_conv_staged(cv, cus, s) : launch_conv_split(cv, cus, s, var);
+    return p.plain ? launch_conv_staged(cv, cus, s, var) : launch_conv_split(cv, cus, s, var);
 }
 
 // The split planes of the weights, from their float32 packing.

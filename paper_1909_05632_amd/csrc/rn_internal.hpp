@@ -231,8 +231,8 @@ hipError_t launch_conv_split(const ConvArgs &a, int cus, hipStream_t s, bool var
 bool train_dx_supported(int cz, int ca);
 hipError_t launch_bwd_dx(const ConvArgs &a, int cus, hipStream_t s);
 // The same layers on the float32 matrix instructions (nets with
-// RN_OPT_SEPARATE_FIRST), not for variants.
-hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s);
+// RN_OPT_SEPARATE_FIRST).
+hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
 bool conv_first_supported(int cin, int cout, rn_dtype dt);
 // General layers (any k <= 8, stride 1, 2 or 4, pad <= (k - 1) / 2; float32):
 // first = the layer reads the input frames.

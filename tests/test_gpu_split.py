@@ -206,7 +206,7 @@ def test_time_of_a_layer_whatever_its_values(torch, fuse):
 
 
 # Options of a net: its convs, whether layer 1 is folded into layer 2.
-ONE_ARITHMETIC = [((40, 80), True), ((40, 80), False), ((64, 128, 128), True)]
+ONE_ARITHMETIC = [((40, 80), True), ((40, 80), False), ((64, 128, 128), True), ((64, 128, 128), False)]
 
 
 @pytest.mark.parametrize("n_out", [6, 18])
@@ -229,6 +229,10 @@ def test_step_full_and_variants_agree(torch, convs, fuse, n_out):
     off = torch.arange(17, dtype=torch.int32, device="cuda")
     tiles = 26 * 20
     assert torch.equal(net.variants(0, whole, off, x, max_tiles=tiles), full)
+    # 64 variants: 33280 tiles a layer, the staged kernel's groups of 8
+    many = net.variants(0, whole.repeat(4, 1), torch.arange(65, dtype=torch.int32, device="cuda"), x.repeat(4, 1, 1, 1),
+                        max_tiles=tiles)
+    assert torch.equal(many, full.repeat(4, 1))
     assert torch.equal(net.variants(0, part, off, x[:1], max_tiles=tiles), full[:1].expand(16, n_out))
     net.close()
     other.close()

@@ -585,21 +585,33 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(BwdArgs a) {
 }
 
 // A team's share of the gradient of weight e in plain float32 products, one
-// lane of 64 taking pixels j, j + 64, .. of its tiles (the whole wave's sum is
-// returned).
+// lane of 64 taking every 64th pixel of its tiles (the whole wave's sum is
+// returned, NaN as soon as it must be).
 __device__ inline float dw_plain(const BwdArgs &a, int e, int team, int lane) {
+    constexpr int U = 4;                                   // tiles a lane loads at once
     const int NQ = 9 * a.ca + 1, co = e / NQ, q = e - co * NQ, kpos = q / a.ca, ci = q - kpos * a.ca;
-    const long long tiles = (long long)a.n * a.ntiles, end = tiles * (team + 1) / a.teams * kTilePx;
+    const bool bias = q == 9 * a.ca;
+    const int dy = bias ? 0 : kpos / 3 - 1, dx = bias ? 0 : kpos % 3 - 1;
+    const long long NT = (long long)a.n * a.ntiles;
+    const int t0 = (int)(NT * team / a.teams), t1 = (int)(NT * (team + 1) / a.teams), m = lane & 15;
     float s = 0.f;
-    for (long long p = tiles * team / a.teams * kTilePx + lane; p < end; p += 64) {
-        const int i = (int)(p / (a.ntiles * kTilePx)), tp = (int)(p - (long long)i * a.ntiles * kTilePx);
-        const int t = tp / kTilePx, m = tp - t * kTilePx, ty = t / a.TW;
-        const int y = ty * kTile + m / 4 + kpos / 3 - 1, x = (t - ty * a.TW) * kTile + m % 4 + kpos % 3 - 1;
-        float v = q == 9 * a.ca ? 1.f : 0.f;
-        if (q < 9 * a.ca && y >= 0 && y < a.H && x >= 0 && x < a.W)
-            v = a.act_prev[(size_t)a.ids[i] * a.prev_stride +
-                           ((size_t)((y >> 2) * a.TW + (x >> 2)) * kTilePx + (y & 3) * 4 + (x & 3)) * a.ca + ci];
-        s = fmaf(a.dz_in[(size_t)p * a.cz + co], v, s);
+    for (int b = t0; b < t1; b += 4 * U) {                 // four tiles of 16 pixels a wave, U times
+        float d[U], v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int T = b + 4 * u + (lane >> 4), Tc = min(T, t1 - 1), i = Tc / a.ntiles, t = Tc - i * a.ntiles, ty = t / a.TW;
+            const int y = ty * kTile + (m >> 2) + dy, x = (t - ty * a.TW) * kTile + (m & 3) + dx;
+            const int yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
+            const float act = bias ? 1.f : a.act_prev[(size_t)a.ids[i] * a.prev_stride +
+                                                      ((size_t)((yc >> 2) * a.TW + (xc >> 2)) * kTilePx + (yc & 3) * 4 + (xc & 3)) * a.ca + ci];
+            const float dz = a.dz_in[((size_t)Tc * kTilePx + m) * a.cz + co];
+            d[u] = T < t1 ? dz : 0.f;
+            v[u] = T < t1 && (bias || (y == yc && x == xc)) ? act : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) s = fmaf(d[u], v[u], s);
+        if (__any(__builtin_isnan(s)) || (__any(s == __builtin_inff()) && __any(s == -__builtin_inff())))
+            return __uint_as_float(0x7fc00000u);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
@@ -612,8 +624,8 @@ __device__ inline float dw_plain(const BwdArgs &a, int e, int team, int lane) {
 // contiguous; with the team fastest every store was 4 bytes on a line of its
 // own (28880 weights of 256 teams, 4 streams of 105x80: 135 us in all).  Where
 // the sum is not finite, the partial sums that are not are taken again from
-// plain float32 products, team by team until the sum is NaN (whatever follows):
-// one infinite pixel costs one team's tiles, a net full of NaN no more.
+// plain float32 products, the block's waves taking such weights in turn, team
+// by team until the sum is NaN (whatever follows); a team ends there too.
 __global__ __launch_bounds__(256) void k_bwd_reduce_rows(BwdArgs a) {
     __shared__ float s_sum[4][64];
     const int total = a.cz * (9 * a.ca + 1);
@@ -630,26 +642,31 @@ __global__ __launch_bounds__(256) void k_bwd_reduce_rows(BwdArgs a) {
     }
     s_sum[wave][lane] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    if (wave > 0) return;
     float v = (s_sum[0][lane] + s_sum[1][lane]) + (s_sum[2][lane] + s_sum[3][lane]);
-    uint64_t plain = __ballot(e < total && !dev::is_finite(v));
-    while (plain) {                                        // rare: one weight at a time, by the whole wave
-        const int j = __ffsll((long long)plain) - 1;
-        plain &= plain - 1;
-        const int ej = blockIdx.x * 64 + j;
-        float f = 0.f;
-        for (int t0 = 0; t0 < a.teams && !__builtin_isnan(f); t0 += 64) {      // uniform: every lane has the sum
-            const float pt = t0 + lane < a.teams ? a.part[(size_t)(t0 + lane) * total + ej] : 0.f;
-            const bool fin = dev::is_finite(pt);
-            float good = fin ? pt : 0.f;
+    const uint64_t plain = __ballot(e < total && !dev::is_finite(v));      // the same in every wave
+    if (plain) {                                           // rare: one weight at a time, by a whole wave
+        __syncthreads();                                   // every wave has read the sums
+        int turn = 0;
+        for (uint64_t left = plain; left; left &= left - 1, ++turn) {
+            if ((turn & 3) != wave) continue;              // uniform per wave
+            const int j = __ffsll((long long)left) - 1, ej = blockIdx.x * 64 + j;
+            float f = 0.f;
+            for (int b = 0; b < a.teams && !__builtin_isnan(f); b += 64) {     // uniform: every lane has the sum
+                const float pt = b + lane < a.teams ? a.part[(size_t)(b + lane) * total + ej] : 0.f;
+                const bool fin = dev::is_finite(pt);
+                float good = fin ? pt : 0.f;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) good += __shfl_xor(good, o, 64);
-            f += good;
-            for (uint64_t bad = __ballot(!fin); bad && !__builtin_isnan(f); bad &= bad - 1)
-                f += dw_plain(a, ej, t0 + __ffsll((long long)bad) - 1, lane);
+                for (int o = 32; o > 0; o >>= 1) good += __shfl_xor(good, o, 64);
+                f += good;
+                for (uint64_t bad = __ballot(!fin); bad && !__builtin_isnan(f); bad &= bad - 1)
+                    f += dw_plain(a, ej, b + __ffsll((long long)bad) - 1, lane);
+            }
+            if (lane == 0) s_sum[0][j] = f;
         }
-        if (lane == j) v = f;
+        __syncthreads();
+        if (plain >> lane & 1) v = s_sum[0][lane];
     }
+    if (wave > 0) return;
     if (e >= total) return;
     float *d = dw_dest(a, e);
     *d = a.accumulate ? *d + v : v;

@@ -905,7 +905,7 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
 #pragma unroll
                     for (int hx = 0; hx < 6; ++hx) {
                         bf16x4 q[3];
-                        if (wide) split4_wide(v[hx], q[0], q[1], q[2]);
+                        if (wide) split4_any(v[hx], q[0], q[1], q[2]);
                         else split4(v[hx], q[0], q[1], q[2]);
 #pragma unroll
                         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<bf16x4 *>(h + pl * R::PLANE + hx * 80) = q[pl];

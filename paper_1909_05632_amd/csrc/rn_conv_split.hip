@@ -32,6 +32,13 @@
 // The sums over K of an output run in one order whatever T is, so a tile's
 // outputs do not depend on the group size a launch picks, and a dense pass, a
 // reuse step and a variant give the same bits.
+//   A result that is not finite: an infinity or a NaN among its operands makes
+// the sum of the small terms NaN, and the leading sum alone has the class that
+// float32 arithmetic gives.  Where the sum of the small terms is finite, finite
+// operands overflowed, and where a halo holds a value that rounds up to
+// infinity in bf16 (watched while staging; clamping each of them instead cost
+// 1.2% of the step) the leading sum says nothing: such results are summed again
+// in plain float32.  The weights' leading planes are clamped when packed.
 #include "rn_split.hpp"
 
 namespace rn {
@@ -66,7 +73,7 @@ struct SplitConv {
     static constexpr int JY = 6 / RY, JX = 6 / RX;
     static constexpr int UPT = JY * JX;
     static constexpr size_t WSTAGE = (size_t)3 * NN * 512;   // bf16 weights per stage
-    static constexpr size_t lds_bytes = 2 * (size_t)BUF + COUT * sizeof(float);
+    static constexpr size_t lds_bytes = 2 * (size_t)BUF + COUT * sizeof(float) + T * sizeof(int);
     static_assert(CIN % 16 == 0 && NCH >= 3 && COUT % 4 == 0 && NN * WM == 4 && T % 4 == 0, "chunks in flight, waves");
     static_assert(UPT <= 9 && RY * RX * 4 <= TPT, "at most one unit per stage, all of them covered");
     static_assert(CIN <= 128, "zero source");
@@ -99,22 +106,30 @@ __device__ inline const float *halo_src(const ConvArgs &a, const TileRef &r, int
     return in ? src + ((y & 3) * 4 + (x & 3)) * CIN : g_zero_halo;
 }
 
-// One output before bias in plain float32, for results the split cannot carry
-// (C16: columns of the float32 packing).  A sum that has become NaN stays NaN:
-// it ends there, so a net full of NaN costs a few products an output.
+// Outputs n, n + 8, n + 16 and n + 24 of pixel p before bias in plain float32
+// (C16: columns of the float32 packing), those with a bit in `want`.  A sum
+// that has become NaN stays NaN: it ends there.
 template <int CIN, int C16, bool VAR>
-__device__ float plain_output(const ConvArgs &a, const TileRef &r, int p, int n) {
-    float acc = 0.f;
+__device__ __attribute__((always_inline)) inline void plain_outputs(const ConvArgs &a, const TileRef &r, int p, int n, int want, float (&acc)[4]) {
     const float *w = static_cast<const float *>(a.w);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = 0.f;
     for (int ci0 = 0; ci0 < CIN; ci0 += 16)
         for (int kpos = 0; kpos < 9; ++kpos) {
             const int y = r.ty * kTile + (p >> 2) + kpos / 3 - 1, x = r.tx * kTile + (p & 3) + kpos % 3 - 1;
             const float *src = halo_src<CIN, VAR>(a, r, y, x, true);
-            for (int ci = ci0; ci < ci0 + 16; ++ci) acc = fmaf(src[ci], w[f32_weight(kpos, ci, n, CIN, C16)], acc);
-            if (__builtin_isnan(acc)) return acc;
+#pragma unroll 4
+            for (int ci = ci0; ci < ci0 + 16; ++ci)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[j] = fmaf(src[ci], w[f32_weight(kpos, ci, min(n + 8 * j, C16 - 1), CIN, C16)], acc[j]);
+            bool open = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) open |= (want >> j & 1) && !__builtin_isnan(acc[j]);
+            if (!open) return;
         }
-    return acc;
 }
+constexpr uint32_t kNan = 0x7fc00000u, kAgain = 0x7fc00001u;   // a NaN result; one to be summed again
 
 // Row of the output a tile is written to.
 template <int COUT, bool VAR>
@@ -124,7 +139,7 @@ __device__ inline float *out_tile(const ConvArgs &a, const TileRef &r, int t) {
 }
 
 template <int CIN, int COUT, int MODE, int T>
-__device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
+__device__ __attribute__((always_inline)) inline void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     using C = SplitConv<CIN, COUT, T>;
     constexpr bool DENSE = MODE == DENSE_PASS || MODE == INPUT_GRAD, VAR = MODE == VARIANTS, GRAD = MODE == INPUT_GRAD;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -135,6 +150,10 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
     float *s_bias = reinterpret_cast<float *>(lds + 2 * C::BUF);
     if constexpr (!GRAD)
         for (int j = tid; j < COUT; j += 256) s_bias[j] = a.bias[j];
+    // The last group whose halo of tile t holds an infinity or what rounds to one.
+    int *s_wide = reinterpret_cast<int *>(s_bias + COUT);
+    if (tid < T) s_wide[tid] = -1;
+    float most = 0.f;                                     // of this thread's values of the group being staged
 
     // Item word of tile lane % T of a group (past the end: the last item).
     auto items = [&](int g) __attribute__((always_inline)) {
@@ -163,6 +182,8 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
         unsigned char *d = ulds + buf * C::BUF + (j / C::JX * 12 + j % C::JX) * 16;
         bf16x4 h, m, l;
         split4(pre[j], h, m, l);
+        most = fmaxf(fmaxf(fabsf(pre[j][0]), fabsf(pre[j][1])), most);
+        most = fmaxf(fmaxf(fabsf(pre[j][2]), fabsf(pre[j][3])), most);
         if (unit) {
             *reinterpret_cast<bf16x4 *>(d) = h;
             *reinterpret_cast<bf16x4 *>(d + C::PLANE) = m;
@@ -214,6 +235,10 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
             // From here on the loads are the next group's (chunk c + 2).
             if (c == C::NCH - 2) sources(g + xr.stride, it_next);
             const int cl = c + 2 < C::NCH ? c + 2 : c + 2 - C::NCH;
+            if (c == C::NCH - 1) {                        // staged in full; what follows is the next group's
+                if (most >= kWide) s_wide[utile] = g;
+                most = 0.f;
+            }
             bf16x8 x[3];
             load_x(x, buf, 0, 0);
 #pragma unroll
@@ -257,8 +282,7 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
         }
         // Epilogue: bias, ReLU and the zero outside the image on the bit
         // patterns (a float above zero has a positive int pattern), 16 bytes
-        // a lane.  A result that is not finite is stored as NaN and recomputed
-        // in plain float32 below.
+        // a lane.  A result to be summed again is marked, and taken below.
         bool bad = false;
 #pragma unroll
         for (int m = 0; m < C::MB; ++m) asm volatile("" : "+a"(hi[m]), "+a"(lo[m]));
@@ -291,10 +315,21 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
                 }
             }
             if (__any(seen != 0.f)) {                     // NaN: some result is not finite
-                bad = true;
+                const bool wide = s_wide[t] == g;
+                bool again = false;
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (!is_finite(v[e])) v[e] = __uint_as_float(0x7fc00000u);
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int i = 4 * q + e;
+                        const float bias = GRAD ? 0.f : s_bias[ch + 8 * q + e];
+                        const bool lost = !is_finite(v[i]), plain = wide || (is_finite(lo[m][i]) && is_finite(bias));
+                        float lead = hi[m][i] + bias;
+                        lead = plain ? __uint_as_float(kAgain) : __builtin_isnan(lead) ? __uint_as_float(kNan) : lead;
+                        v[i] = lost ? lead : v[i];
+                        again |= lost && plain && (GRAD ? mask[q][e] > 0.f : keep != 0);
+                    }
+                bad |= __any(again);
             }
             if (g + t < xr.end && (!VAR || a.vov_out != nullptr)) {
 #pragma unroll
@@ -316,11 +351,18 @@ __device__ void split_path(const ConvArgs &a, int cnt, unsigned char *lds) {
                 if (g + t >= xr.end || (VAR && a.vov_out == nullptr)) continue;
                 const TileRef r = item_ref(a, (uint32_t)__shfl((int)it, t));
                 float *dst = out_tile<COUT, VAR>(a, r, g + t) + p * COUT;
-                for (int n = wn * 32 + (lane & 7); n < min(wn * 32 + 32, COUT); n += 8)
-                    if (__builtin_isnan(dst[n])) {
-                        const float f = plain_output<CIN, C::C16, VAR>(a, r, p, n);
-                        dst[n] = GRAD ? f : __int_as_float(max(__float_as_int(f + s_bias[n]), 0));
-                    }
+                const int n = wn * 32 + (lane & 7);
+                int want = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    want |= n + 8 * j < COUT && __float_as_uint(dst[min(n + 8 * j, COUT - 1)]) == kAgain ? 1 << j : 0;
+                if (want == 0) continue;
+                float f[4];
+                plain_outputs<CIN, C::C16, VAR>(a, r, p, n, want, f);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (want >> j & 1)
+                        dst[n + 8 * j] = GRAD ? f[j] : __int_as_float(max(__float_as_int(f[j] + s_bias[n + 8 * j]), 0));
             }
         }
         it = it_next;
@@ -355,7 +397,7 @@ __global__ void k_pack_split(const float *w, int cin, int c16, int NN, __bf16 *d
         floatx4 v{0.f, 0.f, 0.f, 0.f};
         if (n < c16) v = *reinterpret_cast<const floatx4 *>(w + f32_weight(kpos, ci + 4 * q, n, cin, c16));
         bf16x4 p[3];
-        split4(v, p[0], p[1], p[2]);
+        split4_any(v, p[0], p[1], p[2]);
         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<bf16x4 *>(d + (size_t)pl * NN * 512 + 4 * q) = p[pl];
     }
 }

@@ -52,29 +52,35 @@ __device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) 
     l = __builtin_bit_cast(bf16x4, u32x2{p[2][0], p[2][1]});
 }
 
-// The same where some value is infinite or rounds up to infinity in bf16: the
-// planes of a finite value then still add up to it (leading plane clamped), an
-// infinity is its leading plane alone.
-__device__ inline void split4_wide(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
+// The same for every float32: the leading plane of a finite value is finite
+// (clamped to the largest bf16), so its planes add up to it; an infinity is
+// infinite in its leading plane and NaN in the others, NaN is NaN in all.
+__device__ inline bool is_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
+
+__device__ inline void split4_any(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
     constexpr float kMost = 0x1.fep127f;              // largest finite bf16
-    floatx4 lead, rest;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    uint32_t p[3][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const bool inf = fabsf(v[i]) == __builtin_inff();
-        lead[i] = inf || __builtin_isnan(v[i]) ? v[i] : fminf(fmaxf(v[i], -kMost), kMost);
+    for (int i = 0; i < 2; ++i) {
+        float x = v[2 * i], y = v[2 * i + 1];
+        p[0][i] = round_pair(is_finite(x) ? __builtin_amdgcn_fmed3f(x, -kMost, kMost) : x,
+                             is_finite(y) ? __builtin_amdgcn_fmed3f(y, -kMost, kMost) : y);
+#pragma unroll
+        for (int pl = 1; pl < 3; ++pl) {
+            x -= pair_lo(p[pl - 1][i]);
+            y -= pair_hi(p[pl - 1][i]);
+            p[pl][i] = round_pair(x, y);
+        }
     }
-    h = __builtin_convertvector(lead, bf16x4);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rest[i] = fabsf(v[i]) <= 0x1.fffffep127f ? v[i] - (float)h[i] : 0.f;
-    m = __builtin_convertvector(rest, bf16x4);
-    l = __builtin_convertvector(rest - __builtin_convertvector(m, floatx4), bf16x4);
+    h = __builtin_bit_cast(bf16x4, u32x2{p[0][0], p[0][1]});
+    m = __builtin_bit_cast(bf16x4, u32x2{p[1][0], p[1][1]});
+    l = __builtin_bit_cast(bf16x4, u32x2{p[2][0], p[2][1]});
 }
 constexpr float kWide = 0x1.ffp127f;                  // the smallest float32 that rounds to infinity
 
 // 0 while every value seen was finite, NaN after one that was not.
 __device__ inline float nonfinite(float v, float seen) { return fmaf(v, 0.0f, seen); }
-
-__device__ inline bool is_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
 
 }  // namespace dev
 }  // namespace rn

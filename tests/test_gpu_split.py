@@ -55,26 +55,18 @@ def _weights(wl, rng, scale):
     return (cw, *w[1:])
 
 
-@pytest.mark.parametrize("convs", [(64, 128, 128), (40, 80)])
-@pytest.mark.parametrize("value", [3.4e38, -3.4e38, np.inf, -np.inf])
-def test_values_beyond_the_split(torch, value, convs):
-    # One pixel of the frame holds `value`.  Plain float32 arithmetic (torch on
-    # the CPU, sums in another order) gives the expected result wherever it is
-    # not NaN; where it is, the GPU's ReLU may give NaN or 0 (the sign of a NaN).
-    # 3.4e38 is finite in float32 and infinite in bf16; the layer weights keep
-    # its products and their sums finite.  Tolerance: 1152 float32 roundings.
+def _check_layers(torch, wl, weights, x, fuse=True):
+    """Every layer of a dense pass of two frames against torch's float32 convolution of the layer's own input."""
+    from paper_1909_05632_amd import ReuseNet
     import torch.nn.functional as F
-    wl = synth.Workload(cid=202, streams=2, frames=1, h=20, w=24, convs=convs, n_out=18)
-    weights = _weights(wl, np.random.default_rng(5), 1e-4)
-    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
-    x[0, 0, 9, 10] = value
-    net = make_net(wl, 2, weights)
+    net = ReuseNet(1, wl.h, wl.w, wl.convs, wl.n_out, 2, weights, fuse_first=fuse)
     net.full(torch.from_numpy(x).cuda())
     cur = torch.from_numpy(x)
-    for l in range(1, len(convs) + 1):
-        z = F.conv2d(cur, torch.from_numpy(weights[0][l - 1]), torch.from_numpy(weights[1][l - 1]), padding=1)
-        size = F.conv2d(cur.abs(), torch.from_numpy(np.abs(weights[0][l - 1])), torch.from_numpy(np.abs(weights[1][l - 1])),
-                        padding=1).numpy()               # sum of the terms' magnitudes
+    for l in range(1, len(wl.convs) + 1):
+        w, b = torch.from_numpy(weights[0][l - 1]), torch.from_numpy(weights[1][l - 1])
+        pad = F.pad(cur, (1, 1, 1, 1))                    # zeros that are multiplied, as the kernels do
+        z = F.conv2d(pad, w, b)
+        size = F.conv2d(pad.abs(), w.abs(), b.abs()).numpy()   # sum of the terms' magnitudes
         want = torch.clamp_min(z, 0.0).numpy()
         got = np.stack([net.activation(i, l) for i in range(2)])
         known = ~np.isnan(z.numpy())
@@ -85,6 +77,36 @@ def test_values_beyond_the_split(torch, value, convs):
             assert np.all(np.abs(got[fin] - want[fin]) <= 1152 * 2.0 ** -24 * size[fin] + 1e-30), l
         cur = torch.from_numpy(got)                       # the next layer's input as the GPU has it
     net.close()
+
+
+@pytest.mark.parametrize("convs", [(64, 128, 128), (40, 80)])
+@pytest.mark.parametrize("value", [3.4e38, -3.4e38, np.inf, -np.inf])
+def test_values_beyond_the_split(torch, value, convs):
+    # One pixel of the frame holds `value`.  Plain float32 arithmetic (torch on
+    # the CPU, sums in another order) gives the expected result wherever it is
+    # not NaN; where it is, the GPU's ReLU may give NaN or 0 (the sign of a NaN).
+    # 3.4e38 is finite in float32 and infinite in bf16; the layer weights keep
+    # its products and their sums finite.  Tolerance: 1152 float32 roundings.
+    wl = synth.Workload(cid=202, streams=2, frames=1, h=20, w=24, convs=convs, n_out=18)
+    weights = _weights(wl, np.random.default_rng(5), 1e-4)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None]
+    x[0, 0, 9, 10] = value
+    _check_layers(torch, wl, weights, x)
+
+
+# A weight, or a bias, of each later layer that no bf16 holds: 3.4e38 is finite
+# in float32 (the frame's values keep its products finite).
+@pytest.mark.parametrize("fuse", [True, False])
+@pytest.mark.parametrize("convs", [(64, 128, 128), (40, 80)])
+@pytest.mark.parametrize("value", [3.4e38, -3.4e38, np.inf, -np.inf, np.nan])
+def test_weights_beyond_the_split(torch, value, convs, fuse):
+    wl = synth.Workload(cid=211, streams=2, frames=1, h=20, w=24, convs=convs, n_out=18)
+    weights = _weights(wl, np.random.default_rng(12), 1e-4)
+    for l in range(1, len(convs)):
+        weights[0][l][5, 3, 1, 1] = weights[0][l][70, 9, 0, 2] = value
+        weights[1][l][11] = value
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(2), frames=1))[0][:, None] * np.float32(0.01)
+    _check_layers(torch, wl, weights, x, fuse)
 
 
 # Head partials by position: groups of 1 item (88 tiles), 5 (2112) and 18 (8800)
@@ -264,13 +286,16 @@ def test_gradients_add_over_batches(torch, convs, h, w):
     net.close()
 
 
+@pytest.mark.parametrize("convs", [(40, 80), (64, 128, 128)])
 @pytest.mark.parametrize("n,h,w", [(2, 14, 16), (5, 45, 40)])
-def test_gradients_of_infinities(torch, n, h, w):
-    # An infinite logit gradient: products and sums of layer 2's gradients are
-    # infinite or NaN exactly where IEEE arithmetic makes them so (float64 gives
-    # the same classes), not where operands split in three cancel.  4 teams of
-    # tiles, two of them without an infinity, and 75 (more than a wave's lanes).
-    wl = synth.Workload(cid=207, streams=n, frames=1, h=h, w=w, convs=(40, 80), n_out=6)
+def test_gradients_of_infinities(torch, n, h, w, convs):
+    # An infinite logit gradient: products and sums of every layer's gradients
+    # are infinite or NaN exactly where IEEE arithmetic makes them so (float64
+    # gives the same classes), not where operands split in three cancel.  4
+    # teams of tiles, two of them without an infinity, and 75 (more than a
+    # wave's lanes); weight gradients of one block and of several a team, input
+    # gradients to 40, 64 and 128 channels.
+    wl = synth.Workload(cid=207, streams=n, frames=1, h=h, w=w, convs=convs, n_out=6)
     weights = synth.net_weights(wl, bias_std=0.05)
     x = synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]
     net = make_net(wl, n, weights)
@@ -278,17 +303,30 @@ def test_gradients_of_infinities(torch, n, h, w):
     g = np.random.default_rng(8).normal(size=(n, 6)).astype(np.float32)
     g[n - 1, 1] = np.inf
     cw, cb, _dw, _db = net.split_grads(net.backward(torch.from_numpy(g).cuda(), net.new_grads()))
-    a1 = np.stack([net.activation(i, 1) for i in range(n)]).astype(np.float64)
-    a2 = np.stack([net.activation(i, 2) for i in range(n)])
+    acts = [x] + [np.stack([net.activation(i, l) for i in range(n)]) for l in range(1, len(convs) + 1)]
+
+    def shifted(v):                                       # [3][3] views of v shifted by the kernel positions
+        p = np.pad(v, ((0, 0), (0, 0), (1, 1), (1, 1)))
+        return [[p[:, :, ky:ky + h, kx:kx + w] for kx in range(3)] for ky in range(3)]
+
     with np.errstate(invalid="ignore"):
-        dz = np.where(a2 > 0, (g.astype(np.float64) @ weights[2]).reshape(a2.shape), 0.0)
-        pad = np.pad(a1, ((0, 0), (0, 0), (1, 1), (1, 1)))
-        want = np.stack([np.stack([(dz[:, :, None] * pad[:, None, :, ky:ky + h, kx:kx + w]).sum((0, 3, 4))
-                                   for kx in range(3)], -1) for ky in range(3)], -2)
-    got, bias = cw[1].cpu().numpy(), cb[1].cpu().numpy()
-    for u, v in ((got, want), (bias, dz.sum((0, 2, 3)))):
-        assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
-        assert np.array_equal(np.isneginf(u), np.isneginf(v))
+        da = (g.astype(np.float64) @ weights[2]).reshape(acts[-1].shape)
+        for l in range(len(convs), 0, -1):
+            dz = np.where(acts[l] > 0, da, 0.0)
+            prev = shifted(acts[l - 1].astype(np.float64))
+            # (summed channel by channel: matrix products of infinities are left to numpy's plain loops)
+            want = np.stack([np.stack([np.stack([(dz * v[:, None, c]).sum((0, 2, 3)) for c in range(v.shape[1])], 1)
+                                       for v in row], -1) for row in prev], -2)
+            for u, v in ((cw[l - 1].cpu().numpy(), want), (cb[l - 1].cpu().numpy(), dz.sum((0, 2, 3)))):
+                assert np.array_equal(np.isnan(u), np.isnan(v)), l
+                assert np.array_equal(np.isposinf(u), np.isposinf(v)) and np.array_equal(np.isneginf(u), np.isneginf(v)), l
+            if l > 1:
+                wt, back = weights[0][l - 1].astype(np.float64), shifted(dz)
+                da = np.zeros(acts[l - 1].shape)
+                for ky in range(3):
+                    for kx in range(3):
+                        for c in range(wt.shape[0]):
+                            da += wt[None, c, :, 2 - ky, 2 - kx, None, None] * back[ky][kx][:, c, None]
     net.close()
 
 
@@ -321,3 +359,31 @@ def test_time_of_non_finite_weight_gradients(torch, convs, n, h, w):
                        for v in (g, one, torch.full_like(g, np.inf), torch.full_like(g, np.nan)))
     assert max(others) < 10 * finite, (finite, others)
     net.close()
+
+
+# Layers and calls with infinities or NaN in weights or logit gradients, times
+# relative to the finite ones: up to 2 (input gradients) and 10 (forward) with
+# every such result summed again one by one; 1, and 1.6 where a layer's input is
+# infinite.
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_time_of_non_finite_split_layers(torch, value):
+    from paper_1909_05632_amd import ReuseNet
+    n, h, w = 16, 106, 92
+    wl = synth.Workload(cid=212, streams=n, frames=1, h=h, w=w, convs=(64, 128, 128), n_out=6)
+    weights = synth.net_weights(wl, bias_std=0.05)
+    x = torch.from_numpy(synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0][:, None]).cuda()
+    g = torch.from_numpy(np.random.default_rng(9).normal(size=(n, 6)).astype(np.float32)).cuda()
+    odd = ([np.array(v) for v in weights[0]], *weights[1:])
+    odd[0][1][:, 0, 0, 0] = value
+    ms = {}
+    for name, wts in (("finite", weights), ("odd", odd)):
+        net = ReuseNet(1, h, w, wl.convs, 6, n, wts)
+        grads = net.new_grads()
+        ms[name, "forward"] = _phase_ms(torch, net, "convN", lambda: net.full(x))
+        ms[name, "weights"] = _phase_ms(torch, net, "bwd_dx", lambda: net.backward(g, grads))
+        if name == "finite":
+            ms[name, "gradients"] = ms[name, "weights"]
+            ms["odd", "gradients"] = _phase_ms(torch, net, "bwd_dx", lambda: net.backward(torch.full_like(g, value), grads))
+        net.close()
+    for what in ("forward", "weights", "gradients"):
+        assert ms["odd", what] < 2 * ms["finite", what], ms

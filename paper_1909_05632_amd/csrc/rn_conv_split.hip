@@ -35,7 +35,7 @@
 //   A result that is not finite: an infinity or a NaN among its operands makes
 // the sum of the small terms NaN, and the leading sum alone has the class that
 // float32 arithmetic gives.  Where the sum of the small terms is finite, finite
-// operands overflowed, and where a halo holds a value that rounds up to
+// operands overflowed, and where a halo holds a finite value that rounds up to
 // infinity in bf16 (watched while staging; clamping each of them instead cost
 // 1.2% of the step) the leading sum says nothing: such results are summed again
 // in plain float32.  The weights' leading planes are clamped when packed.
@@ -150,10 +150,10 @@ __device__ __attribute__((always_inline)) inline void split_path(const ConvArgs 
     float *s_bias = reinterpret_cast<float *>(lds + 2 * C::BUF);
     if constexpr (!GRAD)
         for (int j = tid; j < COUT; j += 256) s_bias[j] = a.bias[j];
-    // The last group whose halo of tile t holds an infinity or what rounds to one.
+    // The last group whose halo of tile t holds a finite value that rounds to infinity.
     int *s_wide = reinterpret_cast<int *>(s_bias + COUT);
     if (tid < T) s_wide[tid] = -1;
-    float most = 0.f;                                     // of this thread's values of the group being staged
+    float rest = 0.f;                                     // split4, over this thread's values of the group being staged
 
     // Item word of tile lane % T of a group (past the end: the last item).
     auto items = [&](int g) __attribute__((always_inline)) {
@@ -181,9 +181,7 @@ __device__ __attribute__((always_inline)) inline void split_path(const ConvArgs 
     auto store_unit = [&](int j, int buf) __attribute__((always_inline)) {
         unsigned char *d = ulds + buf * C::BUF + (j / C::JX * 12 + j % C::JX) * 16;
         bf16x4 h, m, l;
-        split4(pre[j], h, m, l);
-        most = fmaxf(fmaxf(fabsf(pre[j][0]), fabsf(pre[j][1])), most);
-        most = fmaxf(fmaxf(fabsf(pre[j][2]), fabsf(pre[j][3])), most);
+        split4(pre[j], h, m, l, rest);
         if (unit) {
             *reinterpret_cast<bf16x4 *>(d) = h;
             *reinterpret_cast<bf16x4 *>(d + C::PLANE) = m;
@@ -236,8 +234,8 @@ __device__ __attribute__((always_inline)) inline void split_path(const ConvArgs 
             if (c == C::NCH - 2) sources(g + xr.stride, it_next);
             const int cl = c + 2 < C::NCH ? c + 2 : c + 2 - C::NCH;
             if (c == C::NCH - 1) {                        // staged in full; what follows is the next group's
-                if (most >= kWide) s_wide[utile] = g;
-                most = 0.f;
+                if (rest == __builtin_inff()) s_wide[utile] = g;
+                rest = 0.f;
             }
             bf16x8 x[3];
             load_x(x, buf, 0, 0);

@@ -33,8 +33,10 @@ __device__ inline uint32_t round_pair(float x, float y) {
 __device__ inline float pair_lo(uint32_t p) { return __uint_as_float(p << 16); }
 __device__ inline float pair_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
 
-// The three bf16 planes of four values.
-__device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
+// The three bf16 planes of four values.  `rest`: the largest magnitude of what
+// the leading planes leave; infinite once a finite value's rounded up to
+// infinity (an infinity leaves NaN, which the maximum passes over).
+__device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l, float &rest) {
     uint32_t p[3][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -44,12 +46,18 @@ __device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) 
             p[pl][i] = round_pair(x, y);
             x -= pair_lo(p[pl][i]);
             y -= pair_hi(p[pl][i]);
+            if (pl == 0) rest = fmaxf(fmaxf(fabsf(x), fabsf(y)), rest);
         }
     }
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     h = __builtin_bit_cast(bf16x4, u32x2{p[0][0], p[0][1]});
     m = __builtin_bit_cast(bf16x4, u32x2{p[1][0], p[1][1]});
     l = __builtin_bit_cast(bf16x4, u32x2{p[2][0], p[2][1]});
+}
+
+__device__ inline void split4(const floatx4 v, bf16x4 &h, bf16x4 &m, bf16x4 &l) {
+    float rest = 0.f;
+    split4(v, h, m, l, rest);
 }
 
 // The same for every float32: the leading plane of a finite value is finite

@@ -450,9 +450,12 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // 36 hy + 5 hx, so the 16 pixels of a 16-lane read lie in 16 distinct bank
 // groups at every octet.
 //
-// A result that is not finite (an operand the split cannot carry) is taken from
-// the plain float32 sum instead.  So is, in the TRAINING form, one that lies
-// within 2^-17 of 0 relative to the largest of its own four partial products:
+// A result that is not finite: an infinity or a NaN among its operands makes it
+// NaN (split4_any), and the sum of its leading terms alone, formed then, has the
+// class of the float32 sum; a NaN weight makes its channel's results NaN by the
+// bias (flagged when packed), so that a net full of NaN takes no second look.
+// What overflows from finite operands is taken from the plain float32 sum.  So
+// is, in the TRAINING form, one that lies within 2^-17 of 0 relative to the largest of its own four partial products:
 // ReLU decisions, which the gradient depends on, are then those of the float32
 // sums.  (Of 42 K results that near to 0 the float32 sums' errors reach 2^-18.8
 // of that partial product; about 4 tiles in 1000 hold such a result, whatever
@@ -478,7 +481,7 @@ struct Res {
     static constexpr int PAIRS = 2 * 9 * CIN, OPAIRS = OSMALL + 2 * 64 * 4 + COUT * 4;   // floats a wave; bytes
     static constexpr size_t lds_bytes = (size_t)OPAIRS + 2 * PAIRS * 4;
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");
-    static constexpr size_t w_bytes = (size_t)KS * NB * 3 * 1024;
+    static constexpr size_t w_bytes = (size_t)KS * NB * 3 * 1024;   // then [COUT] floats: NaN where a weight of the channel is
 };
 
 // The plain float32 product of a tile from its halo planes (their sum is the
@@ -495,8 +498,7 @@ __device__ inline void res_plain(const float *w, const unsigned char *halo, floa
     };
 #pragma unroll
     for (int nb = 0; nb < R::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // Blocks u = 3 kpos + blk of 16, 16 and 8 channels; a block's weights are
-    // loaded while the previous one's products run.
+    // Blocks u = 3 kpos + blk of 16, 16 and 8 channels.
     auto load = [&](floatx4 (&b)[R::NB], int u) __attribute__((always_inline)) {
         const int kpos = u / 3, blk = u - 3 * kpos;
         const float *p = w + kpos * R::CIN * R::COUT + blk * 16 * R::COUT;
@@ -510,11 +512,10 @@ __device__ inline void res_plain(const float *w, const unsigned char *halo, floa
             }
         }
     };
-    floatx4 b[R::NB], next[R::NB];
-    load(b, 0);
 #pragma unroll 1
     for (int u = 0; u < 27; ++u) {
-        load(next, min(u + 1, 26));
+        floatx4 b[R::NB];
+        load(b, u);
         const int kpos = u / 3, blk = u - 3 * kpos, steps = blk < 2 ? 4 : 2;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -526,12 +527,28 @@ __device__ inline void res_plain(const float *w, const unsigned char *halo, floa
         // NaN stays NaN: a net that has diverged ends here after one block.
         bool open = false;
 #pragma unroll
-        for (int nb = 0; nb < R::NB; ++nb) {
+        for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) open |= !__builtin_isnan(acc[nb][e]);
-            b[nb] = next[nb];
-        }
         if (!__any(open)) break;                          // uniform
+    }
+}
+
+// The sum of the leading terms, hh, of a tile.
+__device__ inline void res_lead(const bf16x8 *w, const unsigned char *halo, floatx4 (&acc)[Res::NB], int lane) {
+    using R = Res;
+    const int m = lane & 15, kq = lane >> 4;
+#pragma unroll
+    for (int nb = 0; nb < R::NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 3
+    for (int s = 0; s < R::KS; ++s) {
+        const int g = 4 * s + kq, pos = g / 5;
+        bf16x8 x{};                                       // octets past the last: 0, where 0 times an infinity would be NaN
+        if (g < R::OCT)
+            x = *reinterpret_cast<const bf16x8 *>(halo + ((m & 3) + pos / 3) * R::ROW + ((m >> 2) + pos % 3) * 80 + (g - 5 * pos) * 16);
+#pragma unroll
+        for (int nb = 0; nb < R::NB; ++nb)
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w[(s * R::NB + nb) * 3 * 64 + lane], acc[nb], 0, 0, 0);
     }
 }
 
@@ -583,7 +600,9 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
     const int groups = (rr.count + G - 1) / G;
     auto halo_of = [&](int i, int t) { return lds + (2 * (i % 3) + t) * R::HALO; };
     auto part_of = [&](int i, int t) { return reinterpret_cast<floatx4 *>(lds + R::OPART + (2 * (i & 1) + t) * R::PART); };
-    if (tid < R::COUT) s_bias[tid] = a.bias[tid];
+    if (tid < R::COUT)
+        s_bias[tid] = a.bias[tid] +
+                      reinterpret_cast<const float *>(static_cast<const unsigned char *>(a.w_split) + R::w_bytes)[tid];
 
     if (wave < 4) {
         bf16x8 w[R::KW][R::NB][3];
@@ -701,6 +720,9 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                 if (__any(seen != 0.f || least < 0.f)) {
                     // Results inside the image to be taken again, bit 4 nb + e.
                     uint32_t lost = 0, near = 0;
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));          // what follows is computed here, not kept in registers throughout
+                    const float *bias = s_bias + (ln & 15);
 #pragma unroll
                     for (int nb = 0; nb < R::NB; ++nb) {
                         __builtin_amdgcn_sched_barrier(0);   // one block's partial products in registers at a time
@@ -717,6 +739,28 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
+                    // The results wait in LDS, in place of the first partial
+                    // products (head weights and plain sums fill the registers).
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
+                    float *z = reinterpret_cast<float *>(p);
+                    asm volatile("" : "+v"(lost), "+v"(near));
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb) lost &= __builtin_isnan(bias[nb * 16]) ? ~(15u << (4 * nb)) : ~0u;
+                    if (__any(lost != 0)) {
+                        floatx4 lead[R::NB];
+                        res_lead(static_cast<const bf16x8 *>(a.w_split), halo_of(k, t), lead, ln);
+#pragma unroll
+                        for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float b = bias[nb * 16], v = lead[nb][e] + b;
+                                if ((lost >> (4 * nb + e) & 1) && !(is_finite(lead[nb][e]) && is_finite(b))) {
+                                    z[nb * 256 + e] = __builtin_isnan(v) ? __uint_as_float(0x7fc00000u) : v;
+                                    lost &= ~(1u << (4 * nb + e));
+                                }
+                            }
+                    }
                     int n_lost = 0, n_near = 0;
 #pragma unroll
                     for (int j = 0; j < 4 * R::NB; ++j) {
@@ -724,13 +768,6 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                         n_near += __popcll(__ballot(near >> j & 1));
                     }
                     if (n_near <= kMostSingle) lost |= near;
-                    // The results wait in LDS, in place of the first partial
-                    // products (head weights and plain sums fill the registers).
-#pragma unroll
-                    for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
-                    float *z = reinterpret_cast<float *>(p);
-                    int ln = lane;
-                    asm volatile("" : "+v"(ln));          // what follows is computed here, not kept in registers throughout
                     if (n_lost > kMostSingle) {
                         floatx4 plain[R::NB];
                         res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, ln);
@@ -738,7 +775,7 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                         for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                if (lost >> (4 * nb + e) & 1) z[nb * 256 + e] = plain[nb][e] + s_bias[nb * 16 + mrow];
+                                if (lost >> (4 * nb + e) & 1) z[nb * 256 + e] = plain[nb][e] + bias[nb * 16];
                     } else {
                         float *pairs = reinterpret_cast<float *>(lds + R::OPAIRS) + t * R::PAIRS;
 #pragma unroll 1
@@ -750,7 +787,7 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                                 which &= which - 1;
                                 const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
                                                               nb * 16 + (i & 15), e, i >> 4, ln);
-                                if (lane == i) z[nb * 256 + e] = f + s_bias[nb * 16 + mrow];
+                                if (lane == i) z[nb * 256 + e] = f + bias[nb * 16];
                             }
                         }
                     }
@@ -919,10 +956,24 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
 
 // The split weights in the order the waves hold them, [k-step][16-channel
 // block][plane][lane][8], from the float32 packing.
+// The waves past those take a channel each: NaN if one of its weights is, else 0.
 __global__ void k_pack_res(const float *w, __bf16 *dst) {
     using R = Res;
     const int u = blockIdx.x * blockDim.x + threadIdx.x;  // (k-step, block, lane)
-    if (u >= R::KS * R::NB * 64) return;
+    const int n = (u - R::KS * R::NB * 64) / 64, ln = u & 63;
+    if (n >= R::COUT) return;
+    if (u >= R::KS * R::NB * 64) {                        // uniform per wave
+        float nan = 0.f;
+        for (int kpos = 0; kpos < 9; ++kpos)
+            if (ln < R::CIN) {
+                const int blk = ln / 16, steps = blk < 2 ? 4 : 2, c = ln - 16 * blk;
+                const float v = w[kpos * R::CIN * R::COUT + blk * 16 * R::COUT + (n / 16 * 64 + c / steps * 16 + n % 16) * steps + c % steps];
+                nan = __builtin_isnan(v) ? v : nan;
+            }
+        const bool any = __any(__builtin_isnan(nan));
+        if (ln == 0) reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(dst) + R::w_bytes)[n] = any ? __uint_as_float(0x7fc00000u) : 0.f;
+        return;
+    }
     const int l = u & 63, nb = u / 64 % R::NB, s = u / 64 / R::NB;
     const int g = 4 * s + (l >> 4), kpos = g / 5;
     for (int q = 0; q < 2; ++q) {
@@ -934,7 +985,7 @@ __global__ void k_pack_res(const float *w, __bf16 *dst) {
                 v[e] = w[kpos * R::CIN * R::COUT + blk * 16 * R::COUT + (nb * 64 + lw) * steps + c % steps];
         }
         bf16x4 p[3];
-        split4(v, p[0], p[1], p[2]);
+        split4_any(v, p[0], p[1], p[2]);
         for (int pl = 0; pl < 3; ++pl)
             *reinterpret_cast<bf16x4 *>(dst + ((size_t)((s * R::NB + nb) * 3 + pl) * 64 + l) * 8 + 4 * q) = p[pl];
     }
@@ -1706,10 +1757,10 @@ bool conv_mfma_supported(int cin, int cout, rn_dtype dt) {
 
 bool conv_fused_first_supported(int c1, int c2, rn_dtype dt) { return dt == RN_F32 && is_resident(c1, c2); }
 
-size_t conv_res_bytes(int cin, int cout) { return is_resident(cin, cout) ? Res::w_bytes : 0; }
+size_t conv_res_bytes(int cin, int cout) { return is_resident(cin, cout) ? Res::w_bytes + Res::COUT * sizeof(float) : 0; }
 
 hipError_t launch_pack_res(const float *w, void *dst, hipStream_t s) {
-    const int units = Res::KS * Res::NB * 64;
+    const int units = (Res::KS * Res::NB + Res::COUT) * 64;
     hipLaunchKernelGGL(k_pack_res, dim3((units + 255) / 256), dim3(256), 0, s, w, static_cast<__bf16 *>(dst));
     return hipGetLastError();
 }

@@ -107,11 +107,10 @@ typedef struct {
  *     on demand.
  *     It is the form for training, which reads every layer's cache; with it
  *     float32 layers 64->128 and 128->128 run on the float32 matrix
- *     instructions, and results of 40->80 layers that lie next
- *     to 0 are summed in plain float32, so that ReLU decisions, and with them
- *     the gradients, are those of float32 sums.  By default all these layers
- *     run on the bf16 ones with operands split three ways (closer to the exact
- *     sums, other roundings). */
+ *     instructions, so that ReLU decisions, and with them the gradients, are
+ *     those of float32 sums.  By default these run on the bf16 ones with
+ *     operands split three ways (closer to the exact sums, other roundings).
+ *     Steps, full passes and variants of one net give the same bits. */
 #define RN_OPT_SEPARATE_FIRST 1
 
 typedef struct {                  /* HOST pointers, float32, read during create only */

@@ -454,18 +454,19 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // NaN (split4_any), and the sum of its leading terms alone, formed then, has the
 // class of the float32 sum; a NaN weight makes its channel's results NaN by the
 // bias (flagged when packed), so that a net full of NaN takes no second look.
-// What overflows from finite operands is taken from the plain float32 sum.  So
-// is, in the TRAINING form, one that lies within 2^-17 of 0 relative to the largest of its own four partial products:
-// ReLU decisions, which the gradient depends on, are then those of the float32
-// sums.  (Of 42 K results that near to 0 the float32 sums' errors reach 2^-18.8
-// of that partial product; about 4 tiles in 1000 hold such a result, whatever
-// the sizes of the channels are.)  More than four of them in a tile come from
-// inputs that cancel by structure, an edge filter over a flat patch: their
-// float32 sums are rounding noise as well, and they stay as they are, so the
-// time of a tile does not depend on its values.  Steps, dense passes and
-// variants of one net share the form, and with it the bits.
-enum Form { FOLDED, CACHED, TRAINING };   // layer 1 folded in, read from its cache, read for gradients
-constexpr float kNearZero = 0x1p-17f;
+// What overflows from finite operands is taken from the plain float32 sum.
+//
+// So is a result next to 0: within 2^-19 of the largest of its channel's first
+// and last partial products over the 4 pixels of its tile column.  ReLU
+// decisions, which the gradient depends on, are then those of the float32 sums.
+// (Of 168 K results next to 0, the float32 sums' errors relative to that scale
+// are below 2^-19.2 but for 1 in 10 K; 1 or 2 tiles in 1000 hold such a result,
+// whatever the sizes of the channels.  A scale taken over all 80 channels made
+// every tile of an uneven net sum again, 10 times the time.)  More than four of
+// them in a tile come from inputs that cancel by structure, an edge filter over
+// a flat patch: their float32 sums are rounding noise as well, and they stay as
+// they are, so that a tile's time is bounded whatever its values.
+constexpr float kNearZero = 0x1p-19f;
 constexpr int kMostSingle = 4;            // results of a tile taken one by one
 
 struct Res {
@@ -573,21 +574,44 @@ __device__ inline float res_plain_one(const float *w, const unsigned char *halo,
     for (int v = 0; v < V; ++v)
         if (lane + 64 * v < K) reinterpret_cast<float2 *>(pairs)[lane + 64 * v] = make_float2(x[v], y[v]);
     wave_sync();
+    // Two pairs a read, B reads in flight while the chain takes the B before.
+    constexpr int B = 5, N = K / 2 / B;
+    static_assert(N * B * 2 == K, "whole batches");
+    const floatx4 *src = reinterpret_cast<const floatx4 *>(pairs);
+    floatx4 cur[B], next[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) cur[i] = src[i];
     float acc = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < K; k += 2) {
-        const float4 q = reinterpret_cast<const float4 *>(pairs)[k / 2];
-        acc = fmaf(q.x, q.y, acc);
-        acc = fmaf(q.z, q.w, acc);
+#pragma unroll 2
+    for (int n = 0; n < N; ++n) {
+        const floatx4 *s = src + min(n + 1, N - 1) * B;
+#pragma unroll
+        for (int i = 0; i < B; ++i) next[i] = s[i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            acc = fmaf(cur[i][0], cur[i][1], acc);
+            acc = fmaf(cur[i][2], cur[i][3], acc);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < B; ++i) cur[i] = next[i];
     }
     wave_sync();
     return acc;
 }
 
-template <bool DENSE, int FORM, int NO, bool VAR>
+// Largest magnitude of a channel's first and last partial products over a tile column.
+__device__ inline float column_size(const floatx4 q0, const floatx4 q3) {
+    float m = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = fmaxf(fmaxf(fabsf(q0[e]), fabsf(q3[e])), m);
+    return m;
+}
+
+template <bool DENSE, bool FUSE, int NO, bool VAR>
 __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
     using R = Res;
-    constexpr bool FUSE = FORM == FOLDED;
     extern __shared__ __align__(16) unsigned char lds[];
     float *s_patch = reinterpret_cast<float *>(lds + R::OSMALL);
     float *s_bias = s_patch + 128;
@@ -690,34 +714,25 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                     w1 = word_chunk<DENSE>(a, rr, t, G, c0 + 1, lane);
                 }
                 floatx4 *p = part_of(k, t) + lane;
-                // Sums and bias; `least` is below 0 where a result is near 0.
+                // Sums and bias; `least` is below 0 where a result is near 0,
+                // `most` is not finite where one is not.
                 floatx4 acc[R::NB];
-                float least = 0.f, seen = 0.f;
+                float least = 0.f, most = 0.f;
 #pragma unroll
                 for (int nb = 0; nb < R::NB; ++nb) {
-                    acc[nb] = p[nb * 64];
-                    float size[4];
-                    if constexpr (FORM == TRAINING)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) size[e] = fabsf(acc[nb][e]);
-#pragma unroll
-                    for (int q = 1; q < 4; ++q) {
-                        const floatx4 v = p[(q * R::NB + nb) * 64];
-                        acc[nb] += v;
-                        if constexpr (FORM == TRAINING)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) size[e] = fmaxf(size[e], fabsf(v[e]));
-                    }
+                    const floatx4 q0 = p[nb * 64], q3 = p[(3 * R::NB + nb) * 64];
+                    acc[nb] = q0 + p[(R::NB + nb) * 64] + p[(2 * R::NB + nb) * 64] + q3;
                     acc[nb] += s_bias[nb * 16 + mrow];
+                    float small = fabsf(acc[nb][0]);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        seen = nonfinite(acc[nb][e], seen);
-                        if constexpr (FORM == TRAINING) least = fminf(least, fmaf(size[e], -kNearZero, fabsf(acc[nb][e])));
-                    }
+                    for (int e = 1; e < 4; ++e) small = fminf(small, fabsf(acc[nb][e]));
+                    least = fminf(least, fmaf(column_size(q0, q3), -kNearZero, small));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) most = __builtin_elementwise_maximum(most, fabsf(acc[nb][e]));
                 }
                 const TileRef r = item_of(a, w0, w1, c0, k);
                 const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
-                if (__any(seen != 0.f || least < 0.f)) {
+                if (__any(!is_finite(most) || least < 0.f)) {
                     // Results inside the image to be taken again, bit 4 nb + e.
                     uint32_t lost = 0, near = 0;
                     int ln = lane;
@@ -726,16 +741,12 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
 #pragma unroll
                     for (int nb = 0; nb < R::NB; ++nb) {
                         __builtin_amdgcn_sched_barrier(0);   // one block's partial products in registers at a time
+                        const float size = column_size(p[nb * 64], p[(3 * R::NB + nb) * 64]);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const uint32_t bit = (col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31)) & (1 << (4 * nb + e));
                             if (!is_finite(acc[nb][e])) lost |= bit;
-                            if constexpr (FORM == TRAINING) {
-                                float size = 0.f;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) size = fmaxf(size, fabsf(p[(q * R::NB + nb) * 64][e]));
-                                if (is_finite(acc[nb][e]) && fmaf(size, -kNearZero, fabsf(acc[nb][e])) < 0.f) near |= bit;
-                            }
+                            if (is_finite(acc[nb][e]) && fmaf(size, -kNearZero, fabsf(acc[nb][e])) < 0.f) near |= bit;
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -798,12 +809,17 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                 // As epilogue(), with the head weights in registers already.
                 const int widx = rr.at(t + k * G);
 #pragma unroll
-                for (int nb = 0; nb < R::NB; ++nb) {
+                for (int nb = 0; nb < R::NB; ++nb)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int keep = col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31);
-                        acc[nb][e] = __int_as_float(max(__float_as_int(acc[nb][e]), 0) & keep);
-                    }
+                    for (int e = 0; e < 4; ++e) acc[nb][e] = __int_as_float(max(__float_as_int(acc[nb][e]), 0));
+                if ((r.ty + 1) * kTile > a.H || (r.tx + 1) * kTile > a.W) {   // uniform: pixels outside the image
+#pragma unroll
+                    for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int keep = col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31);
+                            acc[nb][e] = __int_as_float(__float_as_int(acc[nb][e]) & keep);
+                        }
                 }
                 if constexpr (NO != 0) {
                     for (int o0 = 0; o0 < n_out; o0 += NQ) {
@@ -1612,9 +1628,9 @@ __global__ __launch_bounds__(256) void k_conv_gen(ConvArgs a) {
 
 // ------------------------------------------------------------------ dispatch
 
-template <bool DENSE, int FORM, int NO, bool VAR>
+template <bool DENSE, bool FUSE, int NO, bool VAR>
 hipError_t run_resident_no(const ConvArgs &a, int cus, hipStream_t s) {
-    auto kern = k_conv_mfma_res<DENSE, FORM, NO, VAR>;
+    auto kern = k_conv_mfma_res<DENSE, FUSE, NO, VAR>;
     static hipError_t attr = set_lds(kern, Res::lds_bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3(persistent_grid(cus, a.max_tiles)), dim3(512), Res::lds_bytes, s, a);
@@ -1622,17 +1638,16 @@ hipError_t run_resident_no(const ConvArgs &a, int cus, hipStream_t s) {
 }
 
 // Logit count as a template argument where it is a common one.
-template <bool DENSE, int FORM, bool VAR>
+template <bool DENSE, bool FUSE, bool VAR>
 hipError_t run_resident(const ConvArgs &a, int cus, hipStream_t s) {
-    if (a.n_out == 0) return run_resident_no<DENSE, FORM, 0, VAR>(a, cus, s);
-    if (a.n_out == 6) return run_resident_no<DENSE, FORM, 6, VAR>(a, cus, s);
-    return run_resident_no<DENSE, FORM, -1, VAR>(a, cus, s);
+    if (a.n_out == 0) return run_resident_no<DENSE, FUSE, 0, VAR>(a, cus, s);
+    if (a.n_out == 6) return run_resident_no<DENSE, FUSE, 6, VAR>(a, cus, s);
+    return run_resident_no<DENSE, FUSE, -1, VAR>(a, cus, s);
 }
 
 template <bool DENSE, bool VAR>
-hipError_t run_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s) {
-    return training ? run_resident<DENSE, TRAINING, VAR>(a, cus, s)
-                    : a.fuse_first ? run_resident<DENSE, FOLDED, VAR>(a, cus, s) : run_resident<DENSE, CACHED, VAR>(a, cus, s);
+hipError_t run_mfma(const ConvArgs &a, int cus, hipStream_t s) {
+    return a.fuse_first ? run_resident<DENSE, true, VAR>(a, cus, s) : run_resident<DENSE, false, VAR>(a, cus, s);
 }
 
 template <int CIN, int COUT, bool DENSE, bool VAR>
@@ -1775,11 +1790,10 @@ bool conv_first_supported(int cin, int cout, rn_dtype dt) {
 
 // cus: compute units of the device; the persistent grid is at most one block
 // (resident MFMA kernel) or eight blocks (first layer) per CU.
-hipError_t launch_conv_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s, bool var) {
+hipError_t launch_conv_mfma(const ConvArgs &a, int cus, hipStream_t s, bool var) {
     const bool dense = a.wl == nullptr;
-    if ((var && dense) || !is_resident(a.cin, a.cout) || (training && a.fuse_first)) return hipErrorInvalidValue;
-    return var ? run_mfma<false, true>(a, training, cus, s)
-               : dense ? run_mfma<true, false>(a, training, cus, s) : run_mfma<false, false>(a, training, cus, s);
+    if ((var && dense) || !is_resident(a.cin, a.cout)) return hipErrorInvalidValue;
+    return var ? run_mfma<false, true>(a, cus, s) : dense ? run_mfma<true, false>(a, cus, s) : run_mfma<false, false>(a, cus, s);
 }
 
 hipError_t launch_conv_staged(const ConvArgs &a, int cus, hipStream_t s, bool var) {

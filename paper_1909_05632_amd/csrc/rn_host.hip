@@ -443,7 +443,7 @@ MaskGeom make_geom(reuse_net *net) {
 // Layers 2..L other than the general ones.
 hipError_t launch_conv_later(const Plan &p, const ConvArgs &cv, int l, int cus, hipStream_t s, bool var) {
     if (p.dt == RN_BF16) return launch_conv_mfma_bf16(cv, cus, s, var);
-    if (!p.split[l - 1]) return launch_conv_mfma(cv, p.plain, cus, s, var);
+    if (!p.split[l - 1]) return launch_conv_mfma(cv, cus, s, var);
     return p.plain ? launch_conv_staged(cv, cus, s, var) : launch_conv_split(cv, cus, s, var);
 }
 

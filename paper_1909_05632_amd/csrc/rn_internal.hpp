@@ -214,8 +214,7 @@ hipError_t launch_var_lists(const VarMaskArgs &a, hipStream_t s);
 // Conv launchers: list mode (a.wl set), dense mode (a.wl NULL), or variant
 // mode (var = true, a.wl set).
 hipError_t launch_conv_first(const ConvArgs &a, rn_dtype dt, int grid, hipStream_t s, bool var = false);
-// training: ReLU decisions are those of the plain float32 sums (nets with RN_OPT_SEPARATE_FIRST).
-hipError_t launch_conv_mfma(const ConvArgs &a, bool training, int cus, hipStream_t s, bool var = false);
+hipError_t launch_conv_mfma(const ConvArgs &a, int cus, hipStream_t s, bool var = false);
 size_t conv_res_bytes(int cin, int cout);   // its split weights (0: another kernel's layer)
 hipError_t launch_pack_res(const float *w, void *dst, hipStream_t s);
 bool conv_mfma_supported(int cin, int cout, rn_dtype dt);

@@ -159,44 +159,47 @@ def _uneven(weights, big=2.0 ** 20, small=2.0 ** -20):
     return (cw, cb, *weights[2:])
 
 
-def _largest_quarter(x, w):
-    """Largest magnitude of the four partial sums of each 40 -> 80 result: K in octets of channels, octet g at
-    kernel position g / 5, twelve octets (the last one nine) a quarter."""
+def _column_size(x, w):
+    """Largest magnitude of a channel's first and last partial sums over the 4 pixels of a tile column: K in octets
+    of channels, octet g at kernel position g / 5, twelve octets (the last one nine) a partial sum."""
     H, W = x.shape[1:]
-    xp = np.zeros((40, H + 2, W + 2))
-    xp[:, 1:-1, 1:-1] = x
-    part = np.zeros((4, 80, H, W))
-    for g in range(45):
+    xp = np.zeros((40, -(-H // 4) * 4 + 2, W + 2))
+    xp[:, 1:H + 1, 1:-1] = x
+    part = np.zeros((2, 80, xp.shape[1] - 2, W))
+    for g in (*range(12), *range(36, 45)):
         pos, c = g // 5, 8 * (g % 5)
-        win = xp[c:c + 8, pos // 3:pos // 3 + H, pos % 3:pos % 3 + W]
-        part[g // 12] += np.tensordot(w[:, c:c + 8, pos // 3, pos % 3].astype(np.float64), win, 1)
-    return np.abs(part).max(0)
+        win = xp[c:c + 8, pos // 3:pos // 3 + part.shape[2], pos % 3:pos % 3 + W]
+        part[g // 36] += np.tensordot(w[:, c:c + 8, pos // 3, pos % 3].astype(np.float64), win, 1)
+    size = np.abs(part).max(0).reshape(80, -1, 4, W).max(2)
+    return np.repeat(size, 4, 1)[:, :H]
 
 
+@pytest.mark.parametrize("fuse", [True, False])
 @pytest.mark.parametrize("uneven", [False, True])
-def test_decisions_near_zero_are_float32s(torch, uneven):
-    # With a separate layer 1 (the training form), results within 2^-17 of 0
-    # relative to the largest of their own quarter sums come from the float32
-    # sum: up to half of that they are the chain's, bit for bit, whatever the
-    # sizes of the other channels are; the others only to rounding.
+def test_decisions_near_zero_are_float32s(torch, fuse, uneven):
+    # Results within 2^-19 of 0 relative to the largest of their channel's first
+    # and last partial sums in their tile column come from the float32 sum: up
+    # to half of that they are the chain's, bit for bit, whatever the sizes of
+    # the other channels are; the others only to rounding.
     from paper_1909_05632_amd import ReuseNet
-    wl = synth.Workload(cid=205, streams=8, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
+    wl = synth.Workload(cid=205, streams=12, frames=1, h=101, w=80, convs=(40, 80), n_out=6)
     weights = synth.net_weights(wl, bias_std=0.05)
     if uneven:
         weights = _uneven(weights)
-    x = synth.to_f32(synth.sprite_batch(wl, streams=range(8), frames=1))[0][:, None]
-    net = ReuseNet(1, wl.h, wl.w, wl.convs, 6, 8, weights, fuse_first=False)
+    x = synth.to_f32(synth.sprite_batch(wl, streams=range(12), frames=1))[0][:, None]
+    net = ReuseNet(1, wl.h, wl.w, wl.convs, 6, 12, weights, fuse_first=fuse)
     net.full(torch.from_numpy(x).cuda())
     seen = 0
-    for i in range(8):
+    for i in range(12):
         a1 = net.activation(i, 1)
-        z, size = _chain(a1, weights[0][1], weights[1][1]), _largest_quarter(a1, weights[0][1])
-        near = np.abs(z) < size * 2.0 ** -18
-        tile = np.pad(np.abs(z) < size * 2.0 ** -16, ((0, 0), (0, 3), (0, 0))).reshape(80, 26, 4, 20, 4).sum((0, 2, 4))
+        z, size = _chain(a1, weights[0][1], weights[1][1]), _column_size(a1, weights[0][1])
+        near = np.abs(z) < size * 2.0 ** -20
+        tile = np.pad(np.abs(z) < size * 2.0 ** -18, ((0, 0), (0, 3), (0, 0))).reshape(80, 26, 4, 20, 4).sum((0, 2, 4))
         assert tile.max() <= 4                            # each taken one by one
         got, want = net.activation(i, 2), np.maximum(z, np.float32(0))
         assert np.array_equal(got[near], want[near])
-        assert np.all(np.abs(got - want) <= 360 * 2.0 ** -24 * 4 * size + 1e-30)
+        bound = 360 * 2.0 ** -24 * np.abs(weights[0][1]).sum((1, 2, 3)) * np.abs(a1).max()
+        assert np.all(np.abs(got - want) <= bound[:, None, None])
         seen += int(near.sum())
     assert seen > 0
     net.close()

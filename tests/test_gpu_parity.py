@@ -26,10 +26,10 @@ BF16_REL = 1e-2          # bf16: max |gpu - oracle| <= 1e-2 * max |oracle| per t
 
 
 def _run_sequence(torch, wl, streams, frames, weights, slots=None, max_streams=None, u8=False,
-                  sample=None, mask_every=1, value_every=1, label="", head="tiles", act_dtype="f32"):
+                  sample=None, mask_every=1, value_every=1, label="", head="tiles", act_dtype="f32", fuse_first=True):
     u8x, x = sprite_inputs(wl, range(streams), frames)
     S = max_streams or streams
-    net = make_net(wl, S, weights, head=head, act_dtype=act_dtype)
+    net = make_net(wl, S, weights, head=head, act_dtype=act_dtype, fuse_first=fuse_first)
     bf = act_dtype == "bf16"
     onet = oracle_net(wl, bf16=bf)
     ids = None
@@ -302,14 +302,16 @@ def test_stacked_frames_ring(torch):
     net.close()
 
 
-def test_three_layer_64_128_128_small_frames(torch):
+@pytest.mark.parametrize("fuse", [True, False])
+def test_three_layer_64_128_128_small_frames(torch, fuse):
     # The full-resolution net's channels (1->64->128->128, 18 logits) on small
-    # ragged frames: weight-staged MFMA kernels for 64->128 and 128->128.
+    # ragged frames: split kernels for 64->128 and 128->128, and, in nets with a
+    # separate layer 1, the float32 staged kernel's work-list mode.
     wl = synth.Workload(cid=77, streams=5, frames=6, h=42, w=32, convs=(64, 128, 128), n_out=18,
                         n_sprites=3, smin=3, smax=6, vmin=1, vmax=3)
     weights = synth.net_weights(wl, bias_std=0.05)
     for head in ("tiles", "full"):
-        _run_sequence(torch, wl, 5, 6, weights, label=f"3-layer head={head}", head=head).close()
+        _run_sequence(torch, wl, 5, 6, weights, label=f"3-layer head={head}", head=head, fuse_first=fuse).close()
 
 
 def test_fullres_210x160_three_layers(torch):
@@ -417,11 +419,13 @@ def test_large_frame_masks_beyond_64k_lds(torch):
     b.close()
 
 
-def test_staged_group_size_does_not_change_results(torch):
-    # The staged layers (64->128, 128->128) run groups of 8 tiles when every
-    # block has at least 16 groups to do and groups of 4 otherwise; both sum
-    # over K in one order, so a tile's outputs are the same bits either way.
-    # A full pass over 400 streams (35200 tiles per layer: groups of 8) against
+@pytest.mark.parametrize("fuse", [False, True])
+def test_staged_group_size_does_not_change_results(torch, fuse):
+    # The staged layers (64->128, 128->128 of nets with a separate layer 1) run
+    # groups of 8 tiles when every block has at least 16 groups to do and groups
+    # of 4 otherwise; both sum over K in one order, so a tile's outputs are the
+    # same bits either way.  (Other nets run the split kernel, groups of 16 and
+    # of 4.)  A full pass over 400 streams (35200 tiles per layer: groups of 8) against
     # the same frames in batches of 8 streams (704 tiles: groups of 4): logits
     # of every stream and the staged layers' caches of sampled streams, bit
     # for bit, and the logits against the oracle.
@@ -431,8 +435,10 @@ def test_staged_group_size_does_not_change_results(torch):
     weights = synth.net_weights(wl, bias_std=0.05)
     x = synth.to_f32(synth.sprite_batch(wl, streams=range(n), frames=1))[0]      # [n][H][W]
     dev = torch.from_numpy(x[:, None]).cuda()
-    a, b = make_net(wl, n, weights), make_net(wl, n, weights)
+    a, b = (make_net(wl, n, weights, fuse_first=fuse) for _ in range(2))
     la = a.full(dev).cpu().numpy()
+    # an all-dirty step: the same tiles by list, groups of 8
+    assert np.array_equal(la.view(np.uint32), b.step(dev).cpu().numpy().view(np.uint32))
     lb = np.concatenate([b.full(dev[i:i + 8].contiguous(),
                                 stream_ids=torch.arange(i, i + 8, dtype=torch.int32).cuda()).cpu().numpy()
                          for i in range(0, n, 8)])

@@ -110,7 +110,7 @@ typedef struct {
  *     instructions, so that ReLU decisions, and with them the gradients, are
  *     those of float32 sums.  By default these run on the bf16 ones with
  *     operands split three ways (closer to the exact sums, other roundings).
- *     Steps, full passes and variants of one net give the same bits. */
+ *     Steps, full passes and variants of one float32 net give the same bits. */
 #define RN_OPT_SEPARATE_FIRST 1
 
 typedef struct {                  /* HOST pointers, float32, read during create only */

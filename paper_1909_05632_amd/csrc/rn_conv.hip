@@ -304,22 +304,15 @@ __device__ inline float fetch_patch(const ConvArgs &a, const TileRef &r, int lan
 
 // Bias, ReLU, zero outside the image, coalesced store of the 16 x COUT tile
 // through LDS (the halo area is free by now), and the tile's head partials.
-// NO is the number of logits when known at compile time (0: this layer feeds
-// no head partials), else -1 (a.n_out at run time).  A fixed count keeps the
-// number of memory operations per tile fixed, so the next tile's waits can
-// name exactly the loads they need instead of draining this tile's stores.
-// VAR: work item widx of a variant list; the outputs go to overlay row widx
-// (none for a last layer, which only feeds the head), the partials to row
-// widx of the variant partials.
 template <int COUT>
 struct Epi {
     static constexpr int NB = COUT / 16;      // 16-column blocks of the 16x16x4 product
     static constexpr int SR = COUT + 4;       // row stride of the output staging area
 };
 
-template <int COUT, int NO, bool VAR>
+template <int COUT>
 __device__ inline void epilogue(const ConvArgs &a, const TileRef &r, floatx4 *acc, const float *s_bias,
-                                float *stage, int lane, int widx) {
+                                float *stage, int lane) {
     using M = Epi<COUT>;
     const int mrow = lane & 15, kq = lane >> 4;       // D holds pixels (py = i, px = kq)
     // Bias, then ReLU and the zero outside the image on the bit patterns, with
@@ -341,8 +334,8 @@ __device__ inline void epilogue(const ConvArgs &a, const TileRef &r, floatx4 *ac
         }
     }
     wave_sync();
-    const int n_out = NO >= 0 ? NO : a.n_out;
-    if (NO != 0 && n_out > 0) {
+    const int n_out = a.n_out;
+    if (n_out > 0) {
         // Tile contribution to each logit: per-lane partial dot products, then
         // the lane sums, 8 logits at a time (lane_sums8).
         const int ntiles = a.TH * a.TW;
@@ -385,24 +378,18 @@ __device__ inline void epilogue(const ConvArgs &a, const TileRef &r, floatx4 *ac
             const float v = lane_sums8(p, lane);
             const int q = (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
             if ((lane & 7) == 0 && o0 + q < n_out) {
-                float *hp = VAR ? a.vhpart + (size_t)widx * n_out
-                                : a.hpart + ((size_t)r.slot * ntiles + r.tile) * n_out;
-                hp[o0 + q] = v;
+                a.hpart[((size_t)r.slot * ntiles + r.tile) * n_out + o0 + q] = v;
             }
         }
     }
     // The tile's stores go last: the next tile's waits on its own loads then
     // never have to drain them.
-    if (!VAR || n_out == 0) {
-        float4 *d4 = reinterpret_cast<float4 *>(
-            VAR ? static_cast<float *>(a.vov_out) + (size_t)widx * kTilePx * COUT
-                : static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride + (size_t)r.tile * kTilePx * COUT);
+    float4 *d4 = reinterpret_cast<float4 *>(static_cast<float *>(a.out) + (size_t)r.slot * a.out_stride + (size_t)r.tile * kTilePx * COUT);
 #pragma unroll
-        for (int j = 0; j < M::NB; ++j) {              // 16 * COUT / 4 float4 = 64 * NB
-            const int o4 = lane + 64 * j;
-            const int e = 4 * o4, m = e / COUT, n = e - m * COUT;
-            d4[o4] = *reinterpret_cast<const float4 *>(stage + m * M::SR + n);
-        }
+    for (int j = 0; j < M::NB; ++j) {                  // 16 * COUT / 4 float4 = 64 * NB
+        const int o4 = lane + 64 * j;
+        const int e = 4 * o4, m = e / COUT, n = e - m * COUT;
+        d4[o4] = *reinterpret_cast<const float4 *>(stage + m * M::SR + n);
     }
     wave_sync();
 }
@@ -428,7 +415,9 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // Bound: matrix issue.  A tile is 2 * 16 * 80 * 360 flops six times over on
 // v_mfma_f32_16x16x32_bf16 (rn_split.hpp): 360 ops with K padded from 360 to
 // 384, 1440 cycles a tile when one wave of each SIMD issues nothing else (the
-// float32 instruction: 450 ops of 32 cycles, 3600).  Split, the weights take
+// float32 instruction: 450 ops of 32 cycles, 3600).  Measured, about twice that
+// (256 105x80 streams all dirty, 540 tiles a CU: 650 us), whatever form the
+// halo takes: the other roles' vector work sets the period as well.  Split, the weights take
 // 184 KB: more than LDS, but they fit the registers of four waves that each
 // hold a quarter of K (three k-steps x 80 channels x three planes, 180
 // registers).  So a block of eight waves splits the work by role, two waves a
@@ -1410,7 +1399,7 @@ __global__ __launch_bounds__(256) void k_conv_mfma_staged(ConvArgs a) {
 // rule of Fig. 1 for general k and s; DQN-style trunks: 8x8/4, 4x4/2, 3x3/1
 // without padding).  A 4x4 output tile reads an E x E input patch, E = 3 s + k,
 // whose corner is input pixel (4 s ty - p, 4 s tx - p); out-of-grid pixels are
-// zero.  Implicit GEMM on v_mfma_f32_16x16x4_f32 (operand layout as in Mfma):
+// zero.  Implicit GEMM on v_mfma_f32_16x16x4_f32 (operand layout above):
 // M = 16 tile pixels (column-major rows), N = COUT, K = k k CIN in (ky, kx, c)
 // order, walked in blocks of 16 K values: in block b, k-step j gives lane group
 // kq the K index 16 b + 4 kq + j, so a lane's four k-steps are consecutive K
@@ -1621,7 +1610,7 @@ __global__ __launch_bounds__(256) void k_conv_gen(ConvArgs a) {
             for (int w = 0; w < G::KSPLIT - 1; ++w)
 #pragma unroll
                 for (int nb = 0; nb < G::NB; ++nb) acc[nb] += part[(w * G::NB + nb) * 64 + lane];
-            epilogue<COUT, -1, false>(a, r, acc, s_bias, halo, lane, t);
+            epilogue<COUT>(a, r, acc, s_bias, halo, lane);
         }
     }
 }

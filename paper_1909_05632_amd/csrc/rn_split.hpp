@@ -1,17 +1,22 @@
 // Float32 operands on the bf16 matrix cores: each float32 value x is split into
 // three bf16 values h + m + l (round to nearest each, 8 significand bits each:
-// the sum is x to 24 bits, at every exponent a float32 product can carry), and
-// a product of two split operands keeps the six terms down to 2^-16 of the
-// leading one, hh + (hm + mh) + (mm + hl + lh); the dropped terms are below a
-// float32 rounding.  The leading term and the five small ones are summed in
-// accumulators of their own, so the large accumulator is rounded once per
-// matrix op and not six times.  Six bf16 matrix ops do the work of 16 (32x32x16)
-// float32 ones in 6/16 of their time.
+// the sum is x to 24 bits for |x| >= 2^-109), and a product of two split
+// operands keeps the six terms down to 2^-16 of the leading one,
+// hh + (hm + mh) + (mm + hl + lh); the dropped terms are below a float32
+// rounding.  Six bf16 matrix ops do the work of 16 (32x32x16) float32 ones in
+// 6/16 of their time.  k_conv_mfma_split sums the leading term and the five
+// small ones in accumulators of their own, so the large accumulator is rounded
+// once per matrix op and not six times; k_conv_mfma_res and k_bwd_dw_split,
+// whose registers hold no second set, keep one and add the small terms first.
+//
+// Operands below 2^-109 (1.5e-33) keep fewer bits, since the last planes leave
+// bf16's range: a layer whose input is of size 2^-110 came out 3.5e-7 from
+// float64, 2^-112 1.3e-6, 2^-120 3.4e-4 (normal sizes 1.0e-7 to 1.2e-7; the
+// float32 instruction 2.3e-7 to 3.0e-7 down to 2^-120).
 //
 // Values that are not finite, or that round up to infinity in bf16, turn the
-// sums they enter into NaN (inf - inf in the split).  The kernels detect any
-// result that is not finite and recompute that one output in plain float32, so
-// infinities and NaN come out as from float32 arithmetic.
+// sums they enter into NaN (inf - inf in the split).  Each kernel says how such
+// results get the value that float32 arithmetic gives.
 #pragma once
 
 #include "rn_device.hpp"

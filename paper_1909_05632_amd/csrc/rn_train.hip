@@ -9,17 +9,18 @@
 //           dz_L = (Wd^T g_i) where a_L > 0 (the ReLU derivative, 0 at the kink);
 //   layer l: dW_l (+)= sum over pixels of dz_l x im2col(a_{l-1}), db_l (+)= sum dz_l,
 //           dz_{l-1} = (transposed conv of dz_l with W_l) where a_{l-1} > 0.
-// Both conv products run on the float32 matrix cores (v_mfma_f32_16x16x4_f32):
+// The conv products run on the matrix cores, those of layers 2..L on the bf16
+// ones with operands split three ways (rn_split.hpp), layer 1's dW on the
+// float32 ones:
 //   dx: per 4x4 tile of layer l-1 an implicit GEMM, M = 16 pixels, N = C_{l-1},
 //       K = 9 C_l, i.e. a forward 3x3 conv of dz_l with the weights transposed
-//       (input <-> output channels) and flipped (kernel position 8 - k);
+//       (input <-> output channels) and flipped (kernel position 8 - k), in
+//       rn_conv_split.hip;
 //   dW: M = C_l, N = 9 C_{l-1} + 1 (the last column, all ones, gives the bias
 //       gradient), K = every pixel of every stream, split over teams of blocks
 //       whose partial sums are added in team order (no atomics, so the result
 //       is deterministic).
 // The SGD step updates every packed copy of a weight in place.
-#include <type_traits>
-
 #include "rn_split.hpp"
 #include "rn_train.hpp"
 
@@ -51,17 +52,15 @@ __global__ __launch_bounds__(256) void k_reinforce(int n, int n_out, const float
 
 // ------------------------------------------------------------------ dense head
 
-// Block (t, c) takes blockDim.x V of the 16 C head inputs of tile position t
-// of the last layer (chunk c); a thread owns V consecutive inputs j (one
-// 16-byte access per stream for V = 4), keeps their NO weights and NO
+// Up to NO logits.  Block (t, c) takes 4 blockDim.x of the 16 C head inputs of
+// tile position t of the last layer (chunk c); a thread owns four consecutive
+// inputs j (one 16-byte access per stream), keeps their NO weights and NO
 // gradient sums in registers and walks the streams (their g rows staged in
-// LDS).  Each input's sums run over o and over the streams in order, whatever
-// V is.
-template <int NO, int V>
+// LDS).  Each input's sums run over o and over the streams in order.
+template <int NO>
 __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
-    static_assert(V == 1 || V == 4, "one float or one float4 per thread");
-    using VT = typename std::conditional<V == 4, float4, float>::type;
-    constexpr int kHeadStreams = NO <= 32 ? 256 : 128;    // streams per LDS stage of g (32 KB at most)
+    constexpr int V = 4;
+    constexpr int kHeadStreams = 256;                     // streams per LDS stage of g
     __shared__ float s_g[kHeadStreams * NO];
     __shared__ int32_t s_slot[kHeadStreams];
     const int t = blockIdx.x;
@@ -90,9 +89,9 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
             if (ok) {
 #pragma unroll 4
                 for (int ii = 0; ii < nc; ++ii) {
-                    const VT in = *reinterpret_cast<const VT *>(a.act + (size_t)s_slot[ii] * a.act_stride + (size_t)t * E + j0);
+                    const float4 in = *reinterpret_cast<const float4 *>(a.act + (size_t)s_slot[ii] * a.act_stride + (size_t)t * E + j0);
                     const float *vin = reinterpret_cast<const float *>(&in);
-                    VT out;
+                    float4 out;
                     float *vout = reinterpret_cast<float *>(&out);
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(512) void k_bwd_head(HeadBwdArgs a) {
                         }
                         vout[v] = vin[v] > 0.f ? da : 0.f;
                     }
-                    *reinterpret_cast<VT *>(a.dz + ((size_t)(i0 + ii) * a.ntiles + t) * E + j0) = out;
+                    *reinterpret_cast<float4 *>(a.dz + ((size_t)(i0 + ii) * a.ntiles + t) * E + j0) = out;
                 }
             }
         }
@@ -869,7 +868,7 @@ hipError_t launch_bwd_head(const HeadBwdArgs &a, hipStream_t s) {
         // weight gradients' stores do (16 streams: 33 us by rows against 47,
         // 24 of 106x92 with 128 channels: 83 against 108).
         const int q = kTilePx * a.C / 4, th = std::min(512, (q + 63) / 64 * 64);
-        hipLaunchKernelGGL((k_bwd_head<8, 4>), dim3(a.ntiles, (q + th - 1) / th), dim3(th), 0, s, a);
+        hipLaunchKernelGGL((k_bwd_head<8>), dim3(a.ntiles, (q + th - 1) / th), dim3(th), 0, s, a);
         return hipGetLastError();
     }
     const dim3 grid((a.ntiles + 7) / 8 * 8, 4), block((4 * a.C + 63) / 64 * 64);

@@ -724,7 +724,7 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                 }
                 const TileRef r = item_of(a, w0, w1, c0, k);
                 const int col_keep = ~((a.W - 1 - (r.tx * kTile + kq)) >> 31);
-                if (__any(!is_finite(most) || least < 0.f)) {
+                if (__builtin_expect(__any(!is_finite(most) || least < 0.f), 0)) {
                     // Results inside the image to be taken again, bit 4 nb + e.
                     uint32_t lost = 0, near = 0;
                     int ln = lane;

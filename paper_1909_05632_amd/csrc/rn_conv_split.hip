@@ -312,7 +312,7 @@ __device__ __attribute__((always_inline)) inline void split_path(const ConvArgs 
                     seen = nonfinite(v[4 * q + e], seen);
                 }
             }
-            if (__any(seen != 0.f)) {                     // NaN: some result is not finite
+            if (__builtin_expect(__any(seen != 0.f), 0)) {   // NaN: some result is not finite
                 const bool wide = s_wide[t] == g;
                 bool again = false;
 #pragma unroll
@@ -342,7 +342,7 @@ __device__ __attribute__((always_inline)) inline void split_path(const ConvArgs 
                 }
             }
         }
-        if (bad) {                                        // uniform per wave
+        if (__builtin_expect(bad, 0)) {                   // uniform per wave
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             for (int k = 4 * wm * C::MB; k < 4 * (wm + 1) * C::MB; ++k) {   // 8 pixels x 8 lanes x 4 channels a pass
                 const int t = k >> 1, p = (k & 1) * 8 + (lane >> 3);

@@ -738,65 +738,68 @@ __global__ __launch_bounds__(512, 2) void k_conv_mfma_res(ConvArgs a) {
                         for (int e = 0; e < 4; ++e) {
                             const uint32_t bit = (col_keep & ~((a.H - 1 - (r.ty * kTile + e)) >> 31)) & (1 << (4 * nb + e));
                             if (!is_finite(acc[nb][e])) lost |= bit;
+                            acc[nb][e] = __builtin_isnan(acc[nb][e]) ? __uint_as_float(0x7fc00000u) : acc[nb][e];   // of either sign
                             if (!VAR && is_finite(acc[nb][e]) && fmaf(size, -kNearZero, fabsf(acc[nb][e])) < 0.f) near |= bit;
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                    // The results wait in LDS, in place of the first partial
-                    // products (head weights and plain sums fill the registers).
-#pragma unroll
-                    for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
-                    float *z = reinterpret_cast<float *>(p);
                     asm volatile("" : "+v"(lost), "+v"(near));
 #pragma unroll
                     for (int nb = 0; nb < R::NB; ++nb) lost &= __builtin_isnan(bias[nb * 16]) ? ~(15u << (4 * nb)) : ~0u;
-                    if (__any(lost != 0)) {
-                        floatx4 lead[R::NB];
-                        res_lead(static_cast<const bf16x8 *>(a.w_split), halo_of(k, t), lead, ln);
+                    if (__any((lost | near) != 0)) {      // not so where every such channel has a NaN weight
+                        // The results wait in LDS, in place of the first partial
+                        // products (head weights and plain sums fill the registers).
 #pragma unroll
-                        for (int nb = 0; nb < R::NB; ++nb)
+                        for (int nb = 0; nb < R::NB; ++nb) p[nb * 64] = acc[nb];
+                        float *z = reinterpret_cast<float *>(p);
+                        if (__any(lost != 0)) {
+                            floatx4 lead[R::NB];
+                            res_lead(static_cast<const bf16x8 *>(a.w_split), halo_of(k, t), lead, ln);
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float b = bias[nb * 16], v = lead[nb][e] + b;
-                                if ((lost >> (4 * nb + e) & 1) && !(is_finite(lead[nb][e]) && is_finite(b))) {
-                                    z[nb * 256 + e] = __builtin_isnan(v) ? __uint_as_float(0x7fc00000u) : v;
-                                    lost &= ~(1u << (4 * nb + e));
+                            for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const float b = bias[nb * 16], v = lead[nb][e] + b;
+                                    if ((lost >> (4 * nb + e) & 1) && !(is_finite(lead[nb][e]) && is_finite(b))) {
+                                        z[nb * 256 + e] = __builtin_isnan(v) ? __uint_as_float(0x7fc00000u) : v;
+                                        lost &= ~(1u << (4 * nb + e));
+                                    }
+                                }
+                        }
+                        int n_lost = 0, n_near = 0;
+#pragma unroll
+                        for (int j = 0; j < 4 * R::NB; ++j) {
+                            n_lost += __popcll(__ballot(lost >> j & 1));
+                            n_near += __popcll(__ballot(near >> j & 1));
+                        }
+                        if (n_near <= kMostSingle) lost |= near;
+                        if (n_lost > kMostSingle) {
+                            floatx4 plain[R::NB];
+                            res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, ln);
+#pragma unroll
+                            for (int nb = 0; nb < R::NB; ++nb)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    if (lost >> (4 * nb + e) & 1) z[nb * 256 + e] = plain[nb][e] + bias[nb * 16];
+                        } else {
+                            float *pairs = reinterpret_cast<float *>(lds + R::OPAIRS) + t * R::PAIRS;
+#pragma unroll 1
+                            for (int j = 0; j < 4 * R::NB; ++j) {
+                                uint64_t which = __ballot(lost >> j & 1);
+                                const int nb = j >> 2, e = j & 3;
+                                while (which) {               // lane i: channel nb * 16 + i % 16, pixel (e, i / 16)
+                                    const int i = __ffsll((long long)which) - 1;
+                                    which &= which - 1;
+                                    const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
+                                                                  nb * 16 + (i & 15), e, i >> 4, ln);
+                                    if (lane == i) z[nb * 256 + e] = f + bias[nb * 16];
                                 }
                             }
-                    }
-                    int n_lost = 0, n_near = 0;
-#pragma unroll
-                    for (int j = 0; j < 4 * R::NB; ++j) {
-                        n_lost += __popcll(__ballot(lost >> j & 1));
-                        n_near += __popcll(__ballot(near >> j & 1));
-                    }
-                    if (n_near <= kMostSingle) lost |= near;
-                    if (n_lost > kMostSingle) {
-                        floatx4 plain[R::NB];
-                        res_plain(static_cast<const float *>(a.w), halo_of(k, t), plain, ln);
-#pragma unroll
-                        for (int nb = 0; nb < R::NB; ++nb)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (lost >> (4 * nb + e) & 1) z[nb * 256 + e] = plain[nb][e] + bias[nb * 16];
-                    } else {
-                        float *pairs = reinterpret_cast<float *>(lds + R::OPAIRS) + t * R::PAIRS;
-#pragma unroll 1
-                        for (int j = 0; j < 4 * R::NB; ++j) {
-                            uint64_t which = __ballot(lost >> j & 1);
-                            const int nb = j >> 2, e = j & 3;
-                            while (which) {               // lane i: channel nb * 16 + i % 16, pixel (e, i / 16)
-                                const int i = __ffsll((long long)which) - 1;
-                                which &= which - 1;
-                                const float f = res_plain_one(static_cast<const float *>(a.w), halo_of(k, t), pairs,
-                                                              nb * 16 + (i & 15), e, i >> 4, ln);
-                                if (lane == i) z[nb * 256 + e] = f + bias[nb * 16];
-                            }
                         }
-                    }
-                    wave_sync();
+                        wave_sync();
 #pragma unroll
-                    for (int nb = 0; nb < R::NB; ++nb) acc[nb] = p[nb * 64];
+                        for (int nb = 0; nb < R::NB; ++nb) acc[nb] = p[nb * 64];
+                    }
                 }
                 // As epilogue(), with the head weights in registers already.
                 const int widx = rr.at(t + k * G);

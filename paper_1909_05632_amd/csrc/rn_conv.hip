@@ -416,8 +416,9 @@ __device__ inline TileRef item_of(const ConvArgs &a, uint32_t w0, uint32_t w1, i
 // v_mfma_f32_16x16x32_bf16 (rn_split.hpp): 360 ops with K padded from 360 to
 // 384, 1440 cycles a tile when one wave of each SIMD issues nothing else (the
 // float32 instruction: 450 ops of 32 cycles, 3600).  Measured, about twice that
-// (256 105x80 streams all dirty, 540 tiles a CU: 650 us), whatever form the
-// halo takes: the other roles' vector work sets the period as well.  Split, the weights take
+// (256 105x80 streams all dirty, 540 tiles a CU: 640 us, the matrix pipe busy
+// 55% of the cycles; 44% in a step's 73 tiles a CU), whatever form the halo
+// takes: the other roles' vector work sets the period as well.  Split, the weights take
 // 184 KB: more than LDS, but they fit the registers of four waves that each
 // hold a quarter of K (three k-steps x 80 channels x three planes, 180
 // registers).  So a block of eight waves splits the work by role, two waves a

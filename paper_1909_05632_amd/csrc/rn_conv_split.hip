@@ -4,7 +4,10 @@
 //
 // Bound: matrix issue.  A tile is 2 * 16 * COUT * 9 CIN flops six times over on
 // v_mfma_f32_32x32x16_bf16 (~2.06 PFLOP/s from one wave per SIMD in a bare loop,
-// 344 TFLOP/s of float32 work; the float32 instruction gives 150).
+// 344 TFLOP/s of float32 work; the float32 instruction gives 150).  Counters of
+// layers 3 and 2 of 1024 210x160 streams: matrix pipe busy 81% and 72% of the
+// cycles, at 1.7 and 1.9 GHz, which this load brings the clock down to; input
+// gradients 80->40 58% at 2.2 GHz (40 channels fill 5/8 of the rows).
 //
 // A block of four waves computes a group of T tiles x all COUT channels, a wave
 // 32 channels of all tiles (of half of them where COUT has two such blocks): T /

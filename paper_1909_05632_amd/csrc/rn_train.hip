@@ -225,8 +225,10 @@ __global__ __launch_bounds__(512) void k_bwd_head_row(HeadBwdArgs a, int vec) {
 // input channel), K = pixels, on v_mfma_f32_16x16x32_bf16, two tiles (32
 // pixels) a step.
 //
-// Bound: matrix issue, 6 x 2 * 16 * CZ * 9 CA flops a tile; the float32
-// instruction needs 16/6 of that time.  A block of eight waves (two per SIMD)
+// Bound: matrix issue, 6 x 2 * 16 * CZ * 9 CA flops a tile (the float32
+// instruction needs 16/6 of that time), but the pipe is busy only 50% of the
+// cycles at 40->80: three waves hold four column blocks, five three, and 40
+// columns a kernel position are padded to 48.  A block of eight waves (two per SIMD)
 // sums CZB output channels x CAB input channels of a team's tiles: the waves
 // share out the 9 x CAB / 16 column blocks, each with all CZB / 16 row blocks
 // in registers (80 accumulator registers).  A team has CA / CAB x CZ / CZB

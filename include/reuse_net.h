@@ -110,10 +110,10 @@ typedef struct {
  *     instructions, so that ReLU decisions, and with them the gradients, are
  *     those of float32 sums.  By default these run on the bf16 ones with
  *     operands split three ways (closer to the exact sums, other roundings).
- *     Steps and full passes of one float32 net give the same bits, with or
- *     without the option but for those layers, and variants too, except that in
- *     a 40->80 layer results within 2^-19 of 0 (relative to partial sums of
- *     their own) are summed in plain float32 by steps and full passes only. */
+ *     Within one float32 net steps, full passes and variants give the same
+ *     bits, but for variants of 40->80 layers: steps and full passes take
+ *     results within 2^-19 of 0 (relative to partial sums of their own) from
+ *     plain float32 sums, variants do not. */
 #define RN_OPT_SEPARATE_FIRST 1
 
 typedef struct {                  /* HOST pointers, float32, read during create only */
